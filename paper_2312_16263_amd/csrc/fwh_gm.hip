@@ -13,7 +13,8 @@
 //     A = Qd_i n_i + Q_i nd_i.  A block computes 16 panels x 16 frames and writes
 //     through an LDS transpose, so that both the time-major reads and the
 //     time-contiguous writes are coalesced.
-//  2. gm_prefilter_kernel, one thread per (panel, channel) row: the natural cubic
+//  2. gm_prefilter_rows_kernel (records beyond kPsMaxN frames: gm_prefilter_kernel, one
+//     thread per row, in chunks), per (panel, channel) row: the natural cubic
 //     spline of each channel in source time as uniform cubic B-spline
 //     coefficients c_{-1..N} (storage index n + 1), in place: c_0 = f_0,
 //     c_{N-1} = f_{N-1}, c_{n-1} + 4 c_n + c_{n+1} = 6 f_n, c_{-1} = 2 c_0 - c_1,
@@ -24,7 +25,7 @@
 //  4. gm_gather_kernel: a wave owns (observer, 64 consecutive samples, panel
 //     range), a block four neighbouring observers at the same samples; per
 //     panel each lane solves tau + M0 |x - Y(tau)| = t_k by Newton steps on the
-//     splined trajectory (started from the linear extrapolation of its
+//     splined trajectory, as cubics of its interval in units of frames (started from the linear extrapolation of its
 //     solutions for the two previous panels; a step below 1e-6 dtau is accepted
 //     without a further check, the iteration being quadratic, and the position
 //     at tau_ret is the last evaluation advanced by that step; the next panel's
@@ -33,7 +34,10 @@
 //     the block copies once into LDS over its joint tap span (each lane loads
 //     its own taps when the span is too wide), and adds the integrand of
 //     Eqs. (pT) + (pL) times dS/(4 pi) in FP64.  Panel ranges (splits) are
-//     summed by gm_reduce_kernel in fixed order.
+//     summed by gm_reduce_kernel in fixed order.  Bound by FP64 issue (65 % of the
+//     cycles), LDS reads (55 %) and the address unit (45 %): 8192 panels x 1024
+//     frames x 72 observers take 9.3 ms; 12.85 ms with the B-spline weights, divides
+//     and taps of every Newton step taken anew.
 #include <climits>
 
 #include "fwh_internal.h"
@@ -220,6 +224,93 @@ __global__ __launch_bounds__(256) void gm_prefilter_kernel(double *coef, int64_t
     }
 }
 
+// The same for records whose rows a block can hold in LDS (N <= kPsMaxN): every coefficient is read and
+// written once.  A block takes `nr` rows; thread (row, segment of kPsT frames) runs the two recurrences
+// over its segment from kPsH frames outside it, started with zero ((2 - sqrt 3)^30 = 7e-18 of the local
+// values is left of that at the segment) or at the record's end, where they are exact.  One position of
+// padding per segment keeps the threads' reads, kPsT positions apart, on different banks.  Memory bound
+// otherwise: 155648 rows of 1024 frames, 0.85 ms, against 1.54 ms by chunks (each read and written twice).
+constexpr int kPsT = 32, kPsH = 30, kPsMaxN = 256 * kPsT + 2;
+__host__ __device__ constexpr int ps_at(int s) { return s + s / kPsT; }
+__host__ __device__ constexpr int ps_segments(int64_t N) { return (int)((N - 2 + kPsT - 1) / kPsT); }
+
+__global__ __launch_bounds__(256) void gm_prefilter_rows_kernel(double *coef, int64_t rows, int N, int nr,
+                                                              const double *__restrict__ inv_beta) {
+    extern __shared__ double lds[];
+    __shared__ double ib[kGmPivots];
+    const int tid = threadIdx.x, NS = N + 2, RS = ps_at(NS) + 1, nseg = ps_segments(N);
+    const int64_t r0 = (int64_t)blockIdx.x * nr;
+    const int nrow = (int)min<int64_t>(nr, rows - r0);
+    double *const base = coef + r0 * NS;
+    const int total = nrow * NS;
+    if (tid < kGmPivots) ib[tid] = inv_beta[tid];
+    for (int i0 = tid; i0 < total; i0 += 256 * 8) {
+        double v[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q)
+            if (i0 + q * 256 < total) v[q] = base[i0 + q * 256];
+#pragma unroll
+        for (int q = 0; q < 8; ++q)
+            if (i0 + q * 256 < total) {
+                const int row = (i0 + q * 256) / NS;
+                lds[row * RS + ps_at(i0 + q * 256 - row * NS)] = v[q];
+            }
+    }
+    __syncthreads();
+    const int row = tid / nseg, seg = tid - row * nseg;
+    const bool active = row < nrow;
+    double *const f = lds + (active ? row : 0) * RS;  // position n + 1: frame n
+    const int n0 = 1 + seg * kPsT, n1 = min(n0 + kPsT - 1, N - 2);
+    const double f0 = f[ps_at(1)], fN1 = f[ps_at(N)];
+    auto pivot = [&](int n) { return ib[min(n, kGmPivots - 1)]; };
+    double x[kPsT];
+    double d = 0.0;
+    auto forward = [&](int n) {
+        double rhs = 6.0 * f[ps_at(n + 1)];
+        if (n == 1) rhs -= f0;
+        if (n == N - 2) rhs -= fN1;
+        d = (rhs - d) * pivot(n);
+    };
+    for (int n = max(1, n0 - kPsH); n < n0; ++n) forward(n);
+#pragma unroll
+    for (int i = 0; i < kPsT; ++i) {
+        if (n0 + i <= n1) forward(n0 + i);
+        x[i] = d;
+    }
+    __syncthreads();
+    if (active) {
+#pragma unroll
+        for (int i = 0; i < kPsT; ++i)
+            if (n0 + i <= n1) f[ps_at(n0 + i + 1)] = x[i];
+    }
+    __syncthreads();
+    double c = 0.0;
+    for (int n = min(N - 2, n1 + kPsH); n > n1; --n) c = f[ps_at(n + 1)] - c * pivot(n);
+#pragma unroll
+    for (int i = kPsT - 1; i >= 0; --i) {
+        if (n0 + i <= n1) c = x[i] - c * pivot(n0 + i);
+        x[i] = c;
+    }
+    __syncthreads();
+    if (active) {
+#pragma unroll
+        for (int i = 0; i < kPsT; ++i)
+            if (n0 + i <= n1) f[ps_at(n0 + i + 1)] = x[i];
+        // c_0 = f_0 and c_{N-1} = f_{N-1} are in place; the end coefficients
+        if (seg == 0) f[ps_at(0)] = 2.0 * f0 - x[0];
+        if (n1 == N - 2) {
+#pragma unroll
+            for (int i = 0; i < kPsT; ++i)
+                if (n0 + i == n1) f[ps_at(N + 1)] = 2.0 * fN1 - x[i];
+        }
+    }
+    __syncthreads();
+    for (int i = tid; i < total; i += 256) {
+        const int rr = i / NS;
+        base[i] = lds[rr * RS + ps_at(i - rr * NS)];
+    }
+}
+
 __global__ __launch_bounds__(256) void gm_window_kernel(GmWinArgs a) {
     const int64_t o = blockIdx.x;
     const double x0 = a.x_obs[3 * o], x1 = a.x_obs[3 * o + 1], x2 = a.x_obs[3 * o + 2];
@@ -254,25 +345,34 @@ __global__ __launch_bounds__(256) void gm_window_kernel(GmWinArgs a) {
 }
 
 // Uniform cubic B-spline weights of frac u for c_{j-1..j+2} and their derivatives.
-__device__ __forceinline__ void bspline_w(double u, double w[4], double dw[4]) {
+__device__ __forceinline__ void bspline_w(double u, double w[4]) {
     const double v = 1.0 - u, u2 = u * u;
     w[0] = v * v * v * (1.0 / 6.0);
     w[1] = (3.0 * u2 * u - 6.0 * u2 + 4.0) * (1.0 / 6.0);
     w[2] = (-3.0 * u2 * u + 3.0 * u2 + 3.0 * u + 1.0) * (1.0 / 6.0);
     w[3] = u2 * u * (1.0 / 6.0);
-    dw[0] = -0.5 * v * v;
-    dw[1] = 1.5 * u2 - 2.0 * u;
-    dw[2] = -1.5 * u2 + u + 0.5;
-    dw[3] = 0.5 * u2;
 }
 
-// Interval j in [0, N-2] and frac u in [0, 1] of source time tau.
-__device__ __forceinline__ int64_t gm_locate(double tau, double tau0, double dtau, int64_t N, double &u) {
-    const double xs = (tau - tau0) / dtau;
-    double jf = floor(xs);
-    jf = fmin(fmax(jf, 0.0), (double)(N - 2));
-    u = fmin(fmax(xs - jf, 0.0), 1.0);
-    return (int64_t)jf;
+// Interval j in [0, N-2] of the source time s, in frames and within [0, N-1]
+__device__ __forceinline__ int gm_interval(double s, int last) { return min((int)s, last); }
+
+// sqrt(x) to the last bit or so, and y = 1/sqrt(x) to about 2^-45: the hardware estimate (2^-24 or better),
+// one coupled step for both, one residual step for the root.
+__device__ __forceinline__ double gm_sqrt(double x, double &y) {
+    const double e0 = __builtin_amdgcn_rsq(x);
+    double g = x * e0, h = 0.5 * e0;
+    const double e = fma(-h, g, 0.5);
+    g = fma(g, e, g);
+    h = fma(h, e, h);
+    y = h + h;
+    return fma(fma(-g, g, x), h, g);
+}
+
+// 1/x: the hardware estimate and two Newton steps
+__device__ __forceinline__ double gm_rcp(double x) {
+    double y = __builtin_amdgcn_rcp(x);
+    y = fma(y, fma(-x, y, 1.0), y);
+    return fma(y, fma(-x, y, 1.0), y);
 }
 
 typedef double gm_d2 __attribute__((ext_vector_type(2), aligned(8)));
@@ -297,6 +397,25 @@ struct GmTraj {
     }
 };
 
+// x - Y(u) of one coordinate on an interval as a cubic in u
+struct GmCubic {
+    double c0, c1, c2, c3;
+    __device__ __forceinline__ void set(double x, const gm_d2 &a, const gm_d2 &b) {
+        c0 = x - (4.0 * a.y + (a.x + b.x)) * (1.0 / 6.0);
+        c1 = 0.5 * (a.x - b.x);
+        c2 = fma(-0.5, a.x + b.x, a.y);
+        c3 = fma(1.0 / 6.0, a.x - b.y, 0.5 * (b.x - a.y));
+    }
+    // value, d = derivative
+    __device__ __forceinline__ double at(double u, double &d) const {
+        double v = fma(c3, u, c2);
+        d = fma(c3, u, v);
+        v = fma(v, u, c1);
+        d = fma(d, u, v);
+        return fma(v, u, c0);
+    }
+};
+
 // Rows GA .. GMSQ (the 16 channels of the integrand) are staged per block in LDS
 // over the block's tap span: kGmSpanB positions per row, two buffers.
 constexpr int kGmStaged = GMSQ + 1;
@@ -305,9 +424,9 @@ typedef __attribute__((address_space(3))) void *gm_lds_ptr_t;
 
 // Block = 4 waves = observers 4 og .. 4 og + 3 (wave wv: observer 4 og + wv), the same 64 samples
 // k0 .. k0 + 63 and panel range; logical blocks run with the observer group fastest, regrouped per XCD.
-__global__ __launch_bounds__(256) void gm_gather_kernel(GmGatherArgs a) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void gm_gather_kernel(GmGatherArgs a) {
     __shared__ double stage[2][kGmStaged][kGmSpanB];
-    __shared__ int span_lo[4], span_hi[4];
+    __shared__ int span_lo[2][4], span_hi[2][4];
     const int lane = threadIdx.x & 63;
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t nkb = a.nkb, O = a.O;
@@ -326,11 +445,13 @@ __global__ __launch_bounds__(256) void gm_gather_kernel(GmGatherArgs a) {
     // last lane of the wave inside the window
     const int last_active = __builtin_amdgcn_readfirstlane((int)max((int64_t)0, min((int64_t)63, nt - 1 - kb * 64)));
     const double x0 = a.x_obs[3 * o], x1 = a.x_obs[3 * o + 1], x2 = a.x_obs[3 * o + 2];
-    const double t = a.t_start[o] + (double)k * a.dtau;
-    const int64_t N = a.N, NS = a.NS;
-    const double M0 = a.mach, c0 = 1.0 / M0, tau0 = a.tau0, dtau = a.dtau;
-    const double tmax = tau0 + (double)(N - 1) * dtau;
-    const double accept = 1e-6 * dtau;
+    // source and observer time in frames: sigma = (tau - tau_0) / dtau
+    const double M0 = a.mach, c0 = 1.0 / M0, idt = 1.0 / a.dtau, m = M0 * idt;
+    const double t = (a.t_start[o] + (double)k * a.dtau - a.tau0) * idt;
+    const int64_t NS = a.NS;
+    const int jlast = (int)a.N - 2;
+    const double smax = (double)(a.N - 1);
+    const double accept = 1e-6;
     const int64_t pb = z * a.p_chunk;
     const int64_t pe = min(pb + a.p_chunk, a.P);
     double acc = 0.0;
@@ -339,64 +460,68 @@ __global__ __launch_bounds__(256) void gm_gather_kernel(GmGatherArgs a) {
         return;
     }
     // first panel of the range: start from the emission time of frame 0's position
-    double tau;
+    double sig;
     {
         const double *cf = a.coef + pb * kGmRows * NS;
         const double d0 = x0 - cf[GY1 * NS + 1], d1 = x1 - cf[GY2 * NS + 1], d2 = x2 - cf[GY3 * NS + 1];
-        tau = fmin(fmax(t - M0 * sqrt(d0 * d0 + d1 * d1 + d2 * d2), tau0), tmax);
+        sig = fmin(fmax(t - m * sqrt(d0 * d0 + d1 * d1 + d2 * d2), 0.0), smax);
     }
     // taps of the current panel at the current guess (loaded ahead: for the next panel they are
     // fetched after this panel's channel taps); the guess for the next panel extrapolates
     // the retarded times of the last two panels (neighbouring panels are visited in order)
-    double tau_prev = 0.0;
+    double sig_prev = 0.0;
+    int j = gm_interval(sig, jlast);
     GmTraj tr;
     {
-        double u;
-        const int64_t j = gm_locate(tau, tau0, dtau, N, u);
         const double *cf = a.coef + pb * kGmRows * NS;
         tr.load(cf + GY1 * NS, cf + GY2 * NS, cf + GY3 * NS, j);
     }
     int buf = 0;
     for (int64_t p = pb; p < pe; ++p, buf ^= 1) {
         const double *cf = a.coef + p * kGmRows * NS;
-        const double *ry0 = cf + GY1 * NS, *ry1 = cf + GY2 * NS, *ry2 = cf + GY3 * NS;
-        // Newton on g(tau) = tau + M0 |x - Y(tau)| - t, g' = 1 - M0 rhat . Y'(tau); the first step
-        // uses the preloaded taps.  Y and dY/dtau of the last evaluation are kept.
-        double Y0, Y1, Y2, V0, V1, V2, taue;
-        for (int it = 0; it < kGmNewtonMax; ++it) {
-            double u;
-            const int64_t j = gm_locate(tau, tau0, dtau, N, u);
-            double w[4], dw[4];
-            bspline_w(u, w, dw);
-            if (it > 0) tr.load(ry0, ry1, ry2, j);
-            Y0 = w[0] * tr.a0.x + w[1] * tr.a0.y + w[2] * tr.b0.x + w[3] * tr.b0.y;
-            Y1 = w[0] * tr.a1.x + w[1] * tr.a1.y + w[2] * tr.b1.x + w[3] * tr.b1.y;
-            Y2 = w[0] * tr.a2.x + w[1] * tr.a2.y + w[2] * tr.b2.x + w[3] * tr.b2.y;
-            const double idt = 1.0 / dtau;
-            V0 = (dw[0] * tr.a0.x + dw[1] * tr.a0.y + dw[2] * tr.b0.x + dw[3] * tr.b0.y) * idt;
-            V1 = (dw[0] * tr.a1.x + dw[1] * tr.a1.y + dw[2] * tr.b1.x + dw[3] * tr.b1.y) * idt;
-            V2 = (dw[0] * tr.a2.x + dw[1] * tr.a2.y + dw[2] * tr.b2.x + dw[3] * tr.b2.y) * idt;
-            taue = tau;
-            const double r0 = x0 - Y0, r1 = x1 - Y1, r2 = x2 - Y2;
-            const double r = sqrt(r0 * r0 + r1 * r1 + r2 * r2);
-            const double g = tau + M0 * r - t;
-            const double gd = 1.0 - M0 * (r0 * V0 + r1 * V1 + r2 * V2) / r;
-            double step = active ? g / gd : 0.0;
-            const double tn = fmin(fmax(tau - step, tau0), tmax);
-            step = tau - tn;
-            tau = tn;
-            // quadratic convergence: after a step below 1e-6 dtau the error is far below rounding
-            const bool done = !(fabs(step) > accept);
-            if (__all(done)) break;
+        // Newton on g(sigma) = sigma + m |x - Y(sigma)| - t, m = M0 / dtau, on the interval's cubics (first
+        // those of the preloaded taps; loaded again by the lanes that leave their interval).
+        // d = x - Y, dd = d'(sigma), r and 1/r of the last evaluation are kept.  The step takes the
+        // hardware's reciprocal: its error, relative to the step, is gone with the next one.
+        double d0, d1, d2, dd0, dd1, dd2, r, ir, ddr, step;
+        GmCubic q0, q1, q2;
+        q0.set(x0, tr.a0, tr.b0);
+        q1.set(x1, tr.a1, tr.b1);
+        q2.set(x2, tr.a2, tr.b2);
+        for (int it = 0;;) {
+            const double u = sig - (double)j;
+            d0 = q0.at(u, dd0);
+            d1 = q1.at(u, dd1);
+            d2 = q2.at(u, dd2);
+            r = gm_sqrt(fma(d0, d0, fma(d1, d1, d2 * d2)), ir);
+            ddr = fma(d0, dd0, fma(d1, dd1, d2 * dd2)) * ir;
+            const double g = fma(m, r, sig - t), gd = fma(m, ddr, 1.0);
+            const double sn = fmin(fmax(sig - (active ? g * __builtin_amdgcn_rcp(gd) : 0.0), 0.0), smax);
+            step = sig - sn;
+            sig = sn;
+            // quadratic convergence: after a step below 1e-6 frames the error is far below rounding
+            if (__all(!(fabs(step) > accept)) || ++it == kGmNewtonMax) break;
+            const int jn = gm_interval(sig, jlast);
+            if (jn != j) {
+                j = jn;
+                tr.load(cf + GY1 * NS, cf + GY2 * NS, cf + GY3 * NS, j);
+                q0.set(x0, tr.a0, tr.b0);
+                q1.set(x1, tr.a1, tr.b1);
+                q2.set(x2, tr.a2, tr.b2);
+            }
         }
-        // position at tau_ret from the last evaluation by its first-order step (the step is below
-        // 1e-6 dtau, the remainder O(step^2 |Y''|) is below rounding)
-        const double dt_last = tau - taue;
-        const double r0 = x0 - (Y0 + V0 * dt_last), r1 = x1 - (Y1 + V1 * dt_last), r2 = x2 - (Y2 + V2 * dt_last);
-        double u;
-        const int64_t j = gm_locate(tau, tau0, dtau, N, u);
-        double w[4], dw[4];
-        bspline_w(u, w, dw);
+        // position, distance and 1/r at tau_ret from the last evaluation by its first-order step (below
+        // 1e-6 frames: the remainder O(step^2 |Y''|) is below rounding)
+        d0 = fma(-step, dd0, d0);
+        d1 = fma(-step, dd1, d1);
+        d2 = fma(-step, dd2, d2);
+        ir = fma(fma(-r, ir, 1.0), ir, ir);
+        const double dr = -step * ddr;
+        r += dr;
+        ir = fma(-ir * ir, dr, ir);
+        j = gm_interval(sig, jlast);
+        double w[4];
+        bspline_w(sig - (double)j, w);
         // The active lanes' intervals do not decrease with the sample (subsonic motion), so a wave's
         // taps of one row span j(lane 0) .. j(last active lane) + 3, and the block's observers, a few
         // degrees apart, have overlapping spans.  When the block's span fits kGmSpanB positions, each
@@ -406,12 +531,13 @@ __global__ __launch_bounds__(256) void gm_gather_kernel(GmGatherArgs a) {
         // a trajectory row for the last one.)  The copies of the next panel go to the other buffer:
         // every wave has read this one before it reaches the next panel's first barrier.
         if (lane == 0) {
-            span_lo[wv] = wave_active ? (int)j : INT_MAX;
-            span_hi[wv] = wave_active ? __builtin_amdgcn_readlane((int)j, last_active) : INT_MIN;
+            span_lo[buf][wv] = wave_active ? j : INT_MAX;
+            span_hi[buf][wv] = wave_active ? __builtin_amdgcn_readlane(j, last_active) : INT_MIN;
         }
         __syncthreads();
-        int lo = min(min(span_lo[0], span_lo[1]), min(span_lo[2], span_lo[3]));
-        int hi = max(max(span_hi[0], span_hi[1]), max(span_hi[2], span_hi[3]));
+        const int *sl4 = span_lo[buf], *sh4 = span_hi[buf];
+        int lo = min(min(sl4[0], sl4[1]), min(sl4[2], sl4[3]));
+        int hi = max(max(sh4[0], sh4[1]), max(sh4[2], sh4[3]));
         if (lo > hi) lo = hi = 0;  // no lane of the block is inside its window
         const int span = hi - lo + 4;
         double cv[kGmStaged];
@@ -429,7 +555,7 @@ __global__ __launch_bounds__(256) void gm_gather_kernel(GmGatherArgs a) {
             }
             __builtin_amdgcn_s_waitcnt(0);  // this wave's copies have landed ...
             __syncthreads();                // ... and every wave's
-            const int sl = active ? (int)j - lo : 0;
+            const int sl = active ? j - lo : 0;
 #pragma unroll
             for (int c = 0; c < kGmStaged; ++c) {
                 const double *q = &stage[buf][c][sl];
@@ -440,29 +566,26 @@ __global__ __launch_bounds__(256) void gm_gather_kernel(GmGatherArgs a) {
             for (int c = 0; c < kGmStaged; ++c) cv[c] = gm_tap(cf + c * NS, j, w);
         }
         // next panel's guess and first Newton taps
-        const double tau_next = p == pb ? tau : fmin(fmax(2.0 * tau - tau_prev, tau0), tmax);
-        tau_prev = tau;
+        const double sig_next = p == pb ? sig : fmin(fmax(2.0 * sig - sig_prev, 0.0), smax);
+        sig_prev = sig;
+        sig = sig_next;
+        j = gm_interval(sig, jlast);
         if (p + 1 < pe) {
-            double un;
-            const int64_t jn = gm_locate(tau_next, tau0, dtau, N, un);
             const double *cn = cf + kGmRows * NS;
-            tr.load(cn + GY1 * NS, cn + GY2 * NS, cn + GY3 * NS, jn);
+            tr.load(cn + GY1 * NS, cn + GY2 * NS, cn + GY3 * NS, j);
         }
-        const double r = sqrt(r0 * r0 + r1 * r1 + r2 * r2);
-        const double ir = 1.0 / r;
-        const double h0 = r0 * ir, h1 = r1 * ir, h2 = r2 * ir;
+        const double h0 = d0 * ir, h1 = d1 * ir, h2 = d2 * ir;
         auto ch = [&](int c) { return cv[c]; };
         const double Mr = ch(GM1) * h0 + ch(GM2) * h1 + ch(GM3) * h2;
         const double Mdr = ch(GMD1) * h0 + ch(GMD2) * h1 + ch(GMD3) * h2;
         const double Lr = ch(GL1) * h0 + ch(GL2) * h1 + ch(GL3) * h2;
         const double Ldr = ch(GLD1) * h0 + ch(GLD2) * h1 + ch(GLD3) * h2;
-        const double iom = 1.0 / (1.0 - Mr);
+        const double iom = gm_rcp(1.0 - Mr);
         const double conv = r * Mdr + c0 * (Mr - ch(GMSQ));
         // A/(r om^2) + Qn conv/(r^2 om^3) + Ld_r/(c0 r om^2) + (L_r - L_M)/(r^2 om^2) + L_r conv/(c0 r^2 om^3)
         const double F =
             ir * iom * iom * (ch(GA) + M0 * Ldr + ir * (Lr - ch(GLM)) + ir * iom * conv * (ch(GQN) + M0 * Lr));
         if (active) acc += F * a.dS[p];
-        tau = tau_next;
     }
     if (obs_ok && k < a.nt_stride) a.part[(z * O + o) * a.nt_stride + k] = active ? acc * (1.0 / (4.0 * kPiD)) : 0.0;
 }
@@ -484,8 +607,15 @@ hipError_t launch_gm_source(const GmChanArgs &a, const double *inv_beta, hipStre
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const int64_t rows = a.P * kGmRows;
-    gm_prefilter_kernel<<<dim3((unsigned)((rows + kPfRows - 1) / kPfRows)), dim3(256), 0, stream>>>(a.coef, rows, a.N,
-                                                                                                  a.NS, inv_beta);
+    if (a.N <= kPsMaxN) {
+        const int nr = 256 / ps_segments(a.N);
+        const size_t shmem = (size_t)nr * (ps_at((int)a.NS) + 1) * sizeof(double);
+        gm_prefilter_rows_kernel<<<dim3((unsigned)((rows + nr - 1) / nr)), dim3(256), shmem, stream>>>(
+            a.coef, rows, (int)a.N, nr, inv_beta);
+    } else {
+        gm_prefilter_kernel<<<dim3((unsigned)((rows + kPfRows - 1) / kPfRows)), dim3(256), 0, stream>>>(
+            a.coef, rows, a.N, a.NS, inv_beta);
+    }
     return hipGetLastError();
 }
 

@@ -1,0 +1,28 @@
+"""General motion at the record lengths where the spline prefilter changes its
+form: one segment of 32 frames and its ends, two segments, rows that fill a
+block's LDS alone, and the first record that is filtered in chunks instead;
+a panel count whose rows do not fill the last block.  Against the FP64 oracle,
+tolerance as in the parity tests of this path."""
+import numpy as np
+import pytest
+
+import oracle
+from test_gpu_gm import TOL, _run_gpu
+from workloads import motion, surfaces
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("N", [4, 33, 34, 35, 66, 67, 131, 8194, 8195])
+def test_prefilter_record_lengths(N):
+    body = surfaces.sphere(1.0, 3, 5)
+    dtau = max(1 / 64, 2.0 / N)
+    ms = motion.moving_surface(body, "orbit", N, dtau, 0.1, spin=0.5)
+    rho, u, pp = motion.quiescent_monopole_series(ms, 0.3, 0.01, 6.0, dtau, 0.1, source=(0.05, 0.02, 0.0))
+    x = np.array([[9.0, 2.0, 1.0], [-7.0, 5.0, -2.0]])
+    print(f"[gm prefilter] N={N} P={ms.n_panels}", flush=True)
+    plan, p = _run_gpu(ms, x, 0.3, dtau, 0.1, rho, u, pp)
+    ref, _, nt = oracle.gm_forward(ms, x, 0.3, dtau, 0.1, rho, u, pp)
+    np.testing.assert_array_equal(plan.window.n_t, nt)
+    assert nt.min() > 0
+    assert np.abs(p - ref).max() <= TOL * np.abs(ref).max()
