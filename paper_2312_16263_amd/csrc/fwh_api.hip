@@ -65,8 +65,11 @@ struct fwh_plan {
     int gather_kind = FWH_GATHER_AUTO;  // kernel chosen by fwh_setup (FP32/BF16 modes)
     int lds_nw = 0, lds_pt = 0;  // staged window length and panels per stage of the LDS gather (0: not usable)
     int tail_nw = 0, tail_pt = 0;  // the same for a last tile of at most 16 observers (2 x 8 wave shape; 0: none)
-    int wmax = 0;                // widest delay-index window over a tile of observers
+    int wmax = 0, w16 = 0;       // widest delay-index window over a tile of 32 / of 16 observers
+    int mfma_few_bpc = 0;        // the same of its form for few blocks
+    int64_t few_blocks = 0;      // blocks that fit the device at once in that form
     int mfma_bpc = 0;            // resident blocks per CU of the matrix-core gather (0: not usable)
+    bool prefer_mfma = false;    // the matrix-core gather is the faster of the tiled ones
     int stream_bpc = 0;          // resident blocks per CU of the streaming gather (0: not usable)
     bool ready = false;
     // workspace layout (byte offsets) and binding
@@ -91,6 +94,18 @@ bool finite3(const double *v) { return std::isfinite(v[0]) && std::isfinite(v[1]
 // Largest number of panel splits of the FP32/BF16 gathers (single-case and batched): at most
 // kMaxPanelSplits and at least kMinSplitPanels panels per split.  The partial-signal region is sized for it.
 constexpr int64_t kMinSplitPanels = 128;
+// asked for by name (fwh_plan_tune), the matrix-core gather takes 32-observer tiles up to this spread of
+// the delay index
+constexpr int kMfmaWmax = 265;
+// Spread over a 16-observer tile up to which FWH_GATHER_AUTO takes it instead of the LDS-staged gather
+// (each panel's product covers 247 + spread indices).
+constexpr int kMfmaBest = 450;
+// Panel-observer-samples of a batch from which it does so in batched calls: a panel of the matrix-core
+// gather is one chain of product, LDS and taps, about 1.2 us long, which few items per CU do not cover.
+// Measured (FP32, forward gather and source stage): 3 cases of 13 observers, 4.2e8 pairs, 2.96 ms against
+// 2.35 ms LDS-staged; 3 cases, 3.9e9 pairs, 3.44 against 3.89 ms; 12 cases, 2.2e10 pairs, 11.7 against
+// 16.9 ms.
+constexpr double kBatchMfmaMin = 1e9;
 int64_t split_cap(int64_t P) {
     return std::max<int64_t>(1, std::min<int64_t>(fwh::kMaxPanelSplits, (P + kMinSplitPanels - 1) / kMinSplitPanels));
 }
@@ -101,6 +116,19 @@ int64_t nt_min(const fwh_plan *pl) {
     int64_t m = pl->n_t_max;
     for (int64_t v : pl->n_t) m = v < m ? v : m;
     return m;
+}
+
+bool mfma_takes(const fwh_plan *pl) { return pl->mfma_bpc > 0 && pl->wmax <= kMfmaWmax; }
+
+// Forward gather of a call.  The matrix-core and the LDS-staged one give the same sums bit for bit in
+// FP32 storage (same splits, same order of the same FMAs).  In BF16 storage they round differently
+// (2e-7 of the signal): a caller with FP64 data gets FP64 gradients, which stay exactly those of the
+// LDS-staged sums; with FP32 data, where that is below the gradients' own rounding, the faster one runs.
+int forward_gather(const fwh_plan *pl, int in_dtype) {
+    if (pl->gather_kind == FWH_GATHER_MFMA && pl->gather_variant == FWH_GATHER_AUTO && pl->mode == FWH_MODE_BF16 &&
+        in_dtype == FWH_F64 && pl->lds_pt > 0)
+        return FWH_GATHER_LDS;
+    return pl->gather_kind;
 }
 
 int layout(fwh_plan *pl) {
@@ -301,6 +329,17 @@ int fwh_setup(fwh_plan *pl, void *workspace, size_t workspace_bytes, void *strea
                                 f64 ? nullptr : pl->at<int2>(pl->off_tw), f64 ? nullptr : pl->at<int32_t>(pl->off_wblk),
                                 st)))
         return hip_fail("fwh_setup: table kernel", e);
+    if (f64) {
+        // widest window over a tile of observers -> the gather's LDS tile (the delay extremes have been read)
+        int *width = pl->at<int>(pl->off_dmm);
+        int w = 0;
+        if ((e = hipMemsetAsync(width, 0, sizeof(int), st)) ||
+            (e = fwh::launch_spread64(pl->at<int32_t>(pl->off_N0), P, O, width, st)) ||
+            (e = hipMemcpyAsync(&w, width, sizeof(int), hipMemcpyDeviceToHost, st)) || (e = hipStreamSynchronize(st)))
+            return hip_fail("fwh_setup: read-back of the tile windows", e);
+        pl->w16 = w;
+        pl->mfma_bpc = fwh::gather64_blocks_per_cu(w);
+    }
     if (!f64) {
         // per (observer tile, panel) windows of n0 (from the table kernel) and their largest width
         // -> LDS staging geometry
@@ -310,8 +349,11 @@ int fwh_setup(fwh_plan *pl, void *workspace, size_t workspace_bytes, void *strea
                                 hipMemcpyDeviceToHost, st)) ||
             (e = hipStreamSynchronize(st)))
             return hip_fail("fwh_setup: read-back of the tile windows", e);
-        int wmax = 0;
-        for (int32_t w : wblk) wmax = w > wmax ? w : wmax;
+        int wmax = 0, w16 = 0;
+        for (int32_t w : wblk) {
+            wmax = std::max(wmax, (int)((uint32_t)w & 0xffffu));
+            w16 = std::max(w16, (int)((uint32_t)w >> 16));
+        }
         const size_t esz = pl->mode == FWH_MODE_F32 ? sizeof(float) : sizeof(uint16_t);
         // window length per channel group: a multiple of 64 elements (whole wave-wide direct loads)
         // (BF16: a multiple of 128, two elements per 16-byte copy unit)
@@ -337,7 +379,7 @@ int fwh_setup(fwh_plan *pl, void *workspace, size_t workspace_bytes, void *strea
                       bpt = (P + fwh::tile_window_panels() - 1) / fwh::tile_window_panels();
         if (O - (n_tiles - 1) * fwh::kObsTile <= fwh::kObsTile / 2) {
             int wt = 0;
-            for (int64_t b = (n_tiles - 1) * bpt; b < n_tiles * bpt; ++b) wt = wblk[b] > wt ? wblk[b] : wt;
+            for (int64_t b = (n_tiles - 1) * bpt; b < n_tiles * bpt; ++b) wt = std::max(wt, (int)((uint32_t)wblk[b] & 0xffffu));
             const int nwt = ((wt + fwh::kLdsShapeK[1] + fwh::kLdsHalo + nwq - 1) / nwq) * nwq;
             int64_t ptt = (int64_t)(fwh::kLdsBudget / (2 * fwh::gather_lds_panel_bytes(ctype, nwt, 1)));
             if (ptt > fwh::kMaxPanelsPerStage) ptt = fwh::kMaxPanelsPerStage;
@@ -349,7 +391,10 @@ int fwh_setup(fwh_plan *pl, void *workspace, size_t workspace_bytes, void *strea
             pl->tail_pt = (int)ptt;
         }
         pl->wmax = wmax;
-        pl->mfma_bpc = fwh::gather_mfma_blocks_per_cu(ctype, wmax);
+        pl->w16 = w16;
+        pl->mfma_bpc = fwh::gather_mfma_blocks_per_cu(ctype, w16, false);
+        pl->mfma_few_bpc = fwh::gather_mfma_blocks_per_cu(ctype, w16, true);
+        pl->prefer_mfma = pl->mfma_bpc > 0 && pl->lds_pt > 0 && w16 <= kMfmaBest;
         pl->stream_bpc = O <= fwh::kLdsWaves ? fwh::gather_stream_blocks_per_cu(ctype, pl->NS, pl->n_t_max) : 0;
         // kernel: the streaming gather for a few observers, else the LDS-staged one when a panel's
         // window over a tile fits its staging, else the matrix-core one, else direct loads
@@ -361,7 +406,7 @@ int fwh_setup(fwh_plan *pl, void *workspace, size_t workspace_bytes, void *strea
                 pl->gather_kind = FWH_GATHER_STREAM;
                 break;
             case FWH_GATHER_MFMA:
-                if (pl->mfma_bpc <= 0)
+                if (!mfma_takes(pl))
                     return fail(FWH_EINVAL, "fwh_setup: the delay windows (%d samples) are too wide for the "
                                             "matrix-core gather", wmax);
                 pl->gather_kind = FWH_GATHER_MFMA;
@@ -375,8 +420,8 @@ int fwh_setup(fwh_plan *pl, void *workspace, size_t workspace_bytes, void *strea
             case FWH_GATHER_DIRECT: pl->gather_kind = FWH_GATHER_DIRECT; break;
             default:
                 pl->gather_kind = pl->stream_bpc > 0 ? FWH_GATHER_STREAM
+                                  : pl->prefer_mfma  ? FWH_GATHER_MFMA
                                   : pl->lds_pt > 0   ? FWH_GATHER_LDS
-                                  : pl->mfma_bpc > 0 ? FWH_GATHER_MFMA
                                                      : FWH_GATHER_DIRECT;
         }
     }
@@ -387,25 +432,33 @@ int fwh_setup(fwh_plan *pl, void *workspace, size_t workspace_bytes, void *strea
     // the largest that keeps B*s within 32 rounds: whole rounds (no last round that leaves most CUs
     // idle), and enough of them that blocks of unequal work even out
     int64_t blocks;
-    const bool tiled = !f64 && pl->gather_kind != FWH_GATHER_DIRECT;  // 32-observer x 244-sample blocks
+    // (the matrix-core gather takes the LDS-staged one's splits: the same sums from either)
+    const bool as_lds = !f64 && pl->lds_pt > 0 &&
+                        (pl->gather_kind == FWH_GATHER_LDS || pl->gather_kind == FWH_GATHER_MFMA);
+    const int64_t tile = as_lds ? fwh::kObsTile : fwh::kYTile;
+    const bool tiled = f64 || pl->gather_kind != FWH_GATHER_DIRECT;  // observer tile x 244-sample blocks
     if (!f64 && pl->gather_kind == FWH_GATHER_STREAM)
         blocks = 1;  // one block per split covers every observer and sample
     else if (tiled)
-        blocks = ((O + fwh::kObsTile - 1) / fwh::kObsTile) * ((pl->n_t_max + fwh::kLdsK - 1) / fwh::kLdsK);
+        blocks = ((O + tile - 1) / tile) * ((pl->n_t_max + fwh::kLdsK - 1) / fwh::kLdsK);
     else
         blocks = ((O + fwh::kGatherObsPerBlock - 1) / fwh::kGatherObsPerBlock) *
                  ((pl->n_t_max + fwh::kGatherK - 1) / fwh::kGatherK);
     int dev = 0, cus = 0;
     if ((e = hipGetDevice(&dev)) || (e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev)))
         return hip_fail("fwh_setup: device query", e);
+    pl->few_blocks = (int64_t)cus * pl->mfma_few_bpc;
     const int ctype_s = pl->mode == FWH_MODE_F32 ? 1 : 2;
     const int64_t resident =
-        (int64_t)cus * (pl->gather_kind == FWH_GATHER_STREAM ? pl->stream_bpc
-                        : pl->gather_kind == FWH_GATHER_MFMA  ? pl->mfma_bpc
-                        : pl->gather_kind == FWH_GATHER_LDS ? fwh::gather_lds_blocks_per_cu(ctype_s, pl->lds_nw,
-                                                                                            pl->lds_pt)
-                                                            : 2);
-    const int64_t smax = split_cap(P);
+        (int64_t)cus * (f64                                    ? std::max(1, pl->mfma_bpc)
+                        : pl->gather_kind == FWH_GATHER_STREAM ? pl->stream_bpc
+                        : as_lds ? fwh::gather_lds_blocks_per_cu(ctype_s, pl->lds_nw, pl->lds_pt)
+                        : pl->gather_kind == FWH_GATHER_MFMA ? pl->mfma_bpc
+                                                             : 2);
+    // (FP64: at least 16 panels per split, the partial signals within the source stage's scratch)
+    const int64_t smax = f64 ? std::max<int64_t>(1, std::min({(int64_t)fwh::kMaxPanelSplits, P / 16,
+                                                              8 * N * P / (O * pl->n_t_max)}))
+                             : split_cap(P);
     auto rounds = [&](int64_t c) { return (double)((blocks * c + resident - 1) / resident) / (double)c; };
     double best = 1e300;
     for (int64_t c = 1; c <= smax; ++c) best = std::min(best, rounds(c));
@@ -474,30 +527,36 @@ int fwh_forward(fwh_plan *pl, int32_t in_dtype, const void *rho, const void *u, 
     hipError_t e;
     {
         StageScope sc(pl, FWH_STAGE_SOURCE, st);
-        e = fwh::launch_source(in_dtype == FWH_F64 ? 0 : 1, coef_type, rho, u, pp, pl->at<double>(pl->off_n), pl->P,
-                               pl->N, pl->NS, pl->flow, pl->at<double>(pl->off_cp), pl->scratch(),
-                               pl->ws + pl->off_coef, st);
+        e = coef_type == 0
+                ? fwh::launch_source64(in_dtype == FWH_F64 ? 0 : 1, rho, u, pp, pl->at<double>(pl->off_n), pl->P, pl->N,
+                                       pl->NS, pl->flow, pl->at<double>(pl->off_cp), pl->scratch(),
+                                       pl->ws + pl->off_coef, st)
+                : fwh::launch_source(in_dtype == FWH_F64 ? 0 : 1, coef_type, rho, u, pp, pl->at<double>(pl->off_n),
+                                     pl->P, pl->N, pl->NS, pl->flow, pl->at<double>(pl->off_cp),
+                                     pl->ws + pl->off_coef, st);
     }
     if (e) return hip_fail("fwh_forward: source kernel", e);
     if (pl->mode == FWH_MODE_F64) {
         StageScope sc(pl, FWH_STAGE_GATHER, st);
-        e = fwh::launch_gather_f64(pl->at<double>(pl->off_K64), pl->at<double>(pl->off_W64),
-                                   pl->at<int32_t>(pl->off_N0), pl->at<int32_t>(pl->off_nt),
-                                   pl->at<double>(pl->off_coef), pl->P, pl->O, pl->NS, pl->n_t_max,
-                                   static_cast<double *>(p_out), st);
+        // the panel ranges' sums take the place of the source stage's scratch
+        e = fwh::launch_gather64(pl->at<double>(pl->off_K64), pl->at<double>(pl->off_W64),
+                                 pl->at<int32_t>(pl->off_N0), pl->at<int32_t>(pl->off_nt),
+                                 pl->at<double>(pl->off_coef), pl->P, pl->O, pl->NS, pl->n_t_max, pl->w16, pl->splits,
+                                 pl->at<double>(pl->off_scr), static_cast<double *>(p_out), st);
     } else {
+        const int kind = forward_gather(pl, in_dtype);
         {
             StageScope sc(pl, FWH_STAGE_GATHER, st);
-            if (pl->gather_kind == FWH_GATHER_STREAM)
+            if (kind == FWH_GATHER_STREAM)
                 e = fwh::launch_gather_stream(coef_type, pl->at<fwh::PairRec>(pl->off_rec_op), pl->rbf(),
                                               pl->at<int32_t>(pl->off_nt), pl->ws + pl->off_coef, pl->P, pl->O,
                                               pl->NS, pl->n_t_max, pl->splits, pl->at<float>(pl->off_part), st);
-            else if (pl->gather_kind == FWH_GATHER_MFMA)
+            else if (kind == FWH_GATHER_MFMA)
                 e = fwh::launch_gather_mfma(coef_type, pl->at<fwh::PairRec>(pl->off_rec_op), pl->rbf(),
-                                            pl->at<int2>(pl->off_tw), pl->at<int32_t>(pl->off_nt),
-                                            pl->ws + pl->off_coef, pl->P, pl->O, pl->NS, pl->n_t_max, pl->splits,
-                                            pl->wmax, pl->at<float>(pl->off_part), st);
-            else if (pl->gather_kind == FWH_GATHER_LDS) {
+                                            pl->at<int32_t>(pl->off_nt), pl->ws + pl->off_coef, pl->P, pl->O, pl->NS,
+                                            pl->n_t_max, pl->splits, pl->w16, pl->few_blocks, pl->at<float>(pl->off_part),
+                                            st);
+            else if (kind == FWH_GATHER_LDS) {
                 // full tiles with the 4 x 4 wave shape; a last tile of at most 16 observers with 2 x 8
                 const int64_t n_tiles = (pl->O + fwh::kObsTile - 1) / fwh::kObsTile;
                 const int64_t t_full = pl->tail_pt > 0 ? n_tiles - 1 : n_tiles;
@@ -543,10 +602,11 @@ int fwh_adjoint(fwh_plan *pl, int32_t in_dtype, const void *rho, const void *u, 
     {
     StageScope sc(pl, FWH_STAGE_ADJ_GATHER, st);
     if (f64)
-        e = fwh::launch_adj_gather_f64(pl->at<double>(pl->off_K64), pl->at<double>(pl->off_W64),
-                                       pl->at<int32_t>(pl->off_N0), pl->at<int32_t>(pl->off_nt),
-                                       static_cast<const double *>(grad_p), pl->P, pl->O, pl->NS, pl->n_t_max,
-                                       pl->at<double>(pl->off_coef), st);
+        e = fwh::launch_adj_gather64(pl->at<double>(pl->off_K64), pl->at<double>(pl->off_W64),
+                                     pl->at<int32_t>(pl->off_N0), pl->at<int32_t>(pl->off_nt),
+                                     static_cast<const double *>(grad_p), pl->P, pl->O, pl->N, pl->NS, pl->n_t_max,
+                                     pl->at<double>(pl->off_scr), (size_t)(8 * pl->N * pl->P) * sizeof(double),
+                                     pl->at<double>(pl->off_coef), st);
     else
         e = fwh::launch_adj_gather(pl->at<fwh::PairRec>(pl->off_rec_op), pl->at<int32_t>(pl->off_nt),
                                        static_cast<const float *>(grad_p), pl->P, pl->O, pl->N, pl->NS,
@@ -556,9 +616,12 @@ int fwh_adjoint(fwh_plan *pl, int32_t in_dtype, const void *rho, const void *u, 
     if (e) return hip_fail("fwh_adjoint: transposed gather", e);
     {
         StageScope sc(pl, FWH_STAGE_SOURCE_ADJ, st);
-        e = fwh::launch_source_adjoint(f64 ? 0 : 1, in_dtype == FWH_F64 ? 0 : 1, pl->ws + pl->off_coef, rho, u,
-                                       pl->at<double>(pl->off_n), pl->P, pl->N, pl->NS, pl->flow,
-                                       pl->at<double>(pl->off_cp), pl->scratch(), g_rho, g_u, g_p, st);
+        e = f64 ? fwh::launch_source_adjoint64(in_dtype == FWH_F64 ? 0 : 1, pl->ws + pl->off_coef, rho, u,
+                                               pl->at<double>(pl->off_n), pl->P, pl->N, pl->NS, pl->flow,
+                                               pl->at<double>(pl->off_cp), pl->scratch(), g_rho, g_u, g_p, st)
+                : fwh::launch_source_adjoint(in_dtype == FWH_F64 ? 0 : 1, pl->ws + pl->off_coef, rho, u,
+                                             pl->at<double>(pl->off_n), pl->P, pl->N, pl->NS, pl->flow,
+                                             pl->at<double>(pl->off_cp), g_rho, g_u, g_p, st);
     }
     if (e) return hip_fail("fwh_adjoint: source adjoint", e);
     (void)pp;
@@ -623,7 +686,6 @@ struct fwh_batch {
     double item_units = 4.0e6;
     int blocks_per_cu = 2;
     int kind = FWH_GATHER_MFMA;        // forward gather of every case (matrix-core or LDS-staged)
-    int umax = 0;                      // matrix units per wave the persistent kernel is compiled for
     std::vector<double> case_units;    // per case: target panel-observer-samples per forward item
     std::vector<int> case_rows;        // per case: rows of 61 samples per block (matrix-core gather)
     int64_t max_items = 0, n_items = 0, units = 0, grid = 0;
@@ -663,13 +725,13 @@ int fwh_batch_create(const fwh_batch_case *cases, int32_t n, int32_t in_dtype, f
             return fail(FWH_EINVAL, "fwh_batch_create: case %d uses the plain FP64 mode (batches run FP32/BF16)", c);
         if (mode < 0) mode = k.plan->mode;
         if (k.plan->mode != mode) return fail(FWH_EINVAL, "fwh_batch_create: cases mix FP32 and BF16 modes");
-        if (k.plan->lds_pt <= 0 && k.plan->mfma_bpc <= 0)
+        if (k.plan->lds_pt <= 0 && !mfma_takes(k.plan))
             return fail(FWH_EINVAL, "fwh_batch_create: case %d has delay windows too wide for the batched gathers", c);
         // k blocks of at least 2 rows (matrix-core gather), 4 rows (LDS-staged gather)
-        const int64_t tiles = ceil_div(k.plan->O, fwh::kObsTile),
+        const int64_t tiles = ceil_div(k.plan->O, fwh::kYTile),
                       kbs = ceil_div(k.plan->n_t_max, 2 * fwh::kLdsLanesOut);
         max_items += tiles * kbs * k.plan->max_splits;
-        const int64_t nib = fwh::adj_blocks(k.plan->NS);
+        const int64_t nib = fwh::adj_blocks(k.plan->N);
         max_adj_items += ceil_div(k.plan->P * nib, 4);
     }
     if (max_adj_items > INT32_MAX) return fail(FWH_ESIZE, "fwh_batch_create: too many adjoint work items");
@@ -682,20 +744,25 @@ int fwh_batch_create(const fwh_batch_case *cases, int32_t n, int32_t in_dtype, f
     b->mode = mode;
     b->max_items = max_items;
     b->max_adj_items = max_adj_items;
-    // the LDS-staged gather when every case can take it, unless every plan asked for the matrix-core
-    // one (fwh_plan_tune); the matrix-core gather when only it takes the windows of every case
-    bool all_mfma = true, all_lds = true, want_mfma = true;
+    // the matrix-core gather when it is the faster one for every case and the batch is large enough to
+    // fill the device with its items, every plan asked for it (fwh_plan_tune) or only it takes the windows
+    // of every case; else the LDS-staged one
+    double pairs = 0.0;
+    bool all_mfma = true, all_lds = true, want_mfma = true, all_prefer = true;
     for (int c = 0; c < n; ++c) {
-        all_mfma = all_mfma && cases[c].plan->mfma_bpc > 0;
+        all_mfma = all_mfma && mfma_takes(cases[c].plan);
         all_lds = all_lds && cases[c].plan->lds_pt > 0;
+        all_prefer = all_prefer && cases[c].plan->prefer_mfma && cases[c].plan->gather_variant != FWH_GATHER_LDS;
         want_mfma = want_mfma && cases[c].plan->gather_variant == FWH_GATHER_MFMA;
-        b->umax = std::max(b->umax, fwh::gather_mfma_umax(cases[c].plan->wmax));
+        pairs += (double)cases[c].plan->P * (double)cases[c].plan->O * (double)cases[c].plan->n_t_max;
     }
     if (!all_mfma && !all_lds) {
         delete b;
         return fail(FWH_EINVAL, "fwh_batch_create: no batched gather takes the delay windows of every case");
     }
-    b->kind = all_mfma && (want_mfma || !all_lds) ? FWH_GATHER_MFMA : FWH_GATHER_LDS;
+    // (in BF16 storage with FP64 data the LDS-staged one, as in single-case calls)
+    const bool prefer = all_prefer && pairs >= kBatchMfmaMin && (mode == FWH_MODE_F32 || in_dtype == FWH_F32);
+    b->kind = prefer || (all_mfma && (want_mfma || !all_lds)) ? FWH_GATHER_MFMA : FWH_GATHER_LDS;
     b->case_units.assign((size_t)n, b->item_units);
     b->case_rows.assign((size_t)n, fwh::kLdsSub);
     size_t off = 0;
@@ -779,26 +846,29 @@ int fwh_batch_bind(fwh_batch *b, void *workspace, size_t workspace_bytes, void *
         const bool mfma = b->kind == FWH_GATHER_MFMA;
         const int rows = mfma ? b->case_rows[(size_t)c] : fwh::kLdsSub;
         const int64_t kstep = (int64_t)fwh::kLdsLanesOut * rows;
-        const int64_t tiles = ceil_div(O, fwh::kObsTile), kbs = ceil_div(ntm, kstep);
-        // panel splits: work per item close to the case's target
+        const int64_t tile = mfma ? fwh::kYTile : fwh::kObsTile;  // observers per item
+        const int64_t tiles = ceil_div(O, tile), kbs = ceil_div(ntm, kstep);
+        // panel splits: work per 32-observer item close to the case's target, the same for both gathers
+        // (so that their sums are)
         const double tile_units = (double)P * std::min<int64_t>(O, fwh::kObsTile) * std::min<int64_t>(ntm, kstep);
         int64_t S = (int64_t)std::ceil(tile_units / b->case_units[(size_t)c]);
         S = std::max<int64_t>(1, std::min<int64_t>(S, pl->max_splits));
         const int64_t p_chunk = ceil_div(P, S);
         const int64_t LR = fwh::adj_pad_row(N, NS), padlo = fwh::adj_pad_lo(N);
-        const int64_t nib = fwh::adj_blocks(NS);
+        const int64_t nib = fwh::adj_blocks(N);
         fwh::BatchCase &d = desc[c];
         d.src = fwh::SrcFwdArgs{k.rho, k.u, k.p_prime, pl->at<double>(pl->off_n), P, N, NS, pl->flow,
                                 pl->at<double>(pl->off_cp), pl->scratch(), pl->ws + pl->off_coef};
         d.gat = fwh::GatherArgs{pl->at<fwh::PairRec>(pl->off_rec_op), pl->rbf(), pl->at<int2>(pl->off_tw),
                                 pl->at<int32_t>(pl->off_nt), pl->ws + pl->off_coef, P, O, NS, ntm, p_chunk,
-                                mfma ? fwh::gather_mfma_y_row(pl->wmax) : pl->lds_nw, pl->lds_pt, (int)S,
+                                mfma ? fwh::gather_mfma_y_row(pl->w16) : pl->lds_nw, pl->lds_pt, (int)S,
                                 pl->at<float>(pl->off_part), rows};
         d.red = fwh::ReduceArgs{pl->at<float>(pl->off_part), (int)S, O * ntm, static_cast<float *>(k.p_out)};
         d.pad = fwh::PadArgs{static_cast<const float *>(k.grad_p), pl->at<int32_t>(pl->off_nt), O, ntm, LR, padlo,
                              pl->at<float>(pl->off_gpad)};
-        d.adj = fwh::AdjArgs{pl->at<fwh::PairRec>(pl->off_rec_op), pl->at<float>(pl->off_gpad), P, O, NS, LR, padlo,
-                             nib, pl->at<float>(pl->off_coef), ntm, N - nt_min(pl), nt_min(pl) + 2};
+        d.adj = fwh::AdjArgs{pl->at<fwh::PairRec>(pl->off_rec_op), pl->at<int32_t>(pl->off_nt),
+                             pl->at<float>(pl->off_gpad), P, O, N, NS, LR, padlo, nib, pl->at<float>(pl->off_coef),
+                             N - nt_min(pl), nt_min(pl) + 2};
         d.sadj = fwh::SrcAdjArgs{pl->at<float>(pl->off_coef), k.rho, k.u, pl->at<double>(pl->off_n), P, N, NS,
                                  pl->flow, pl->at<double>(pl->off_cp), k.g_rho, k.g_u, k.g_p};
         const int64_t src_int = fwh::src_interior_chunks(N);
@@ -810,13 +880,13 @@ int fwh_batch_bind(fwh_batch *b, void *workspace, size_t workspace_bytes, void *
         const int64_t adj_int = fwh::adj_interior_chunks(N);
         s_sadj[c + 1] = s_sadj[c] + ceil_div(P, fwh::kSrcPanels) * adj_int;
         s_sadjg[c + 1] = s_sadjg[c] + ceil_div(P, fwh::kSrcPanels) * (fwh::adj_chunks(N) - adj_int);
-        b->shmem = std::max(b->shmem, mfma ? fwh::gather_mfma_shmem(pl->wmax)
+        b->shmem = std::max(b->shmem, mfma ? fwh::gather_mfma_shmem(pl->w16)
                                            : fwh::gather_lds_shmem(coef_type, pl->lds_nw, pl->lds_pt));
         for (int64_t t = 0; t < tiles; ++t)
             for (int64_t kb = 0; kb < kbs; ++kb)
                 for (int64_t z = 0; z < S; ++z) {
                     const int64_t np = std::max<int64_t>(0, std::min(P, (z + 1) * p_chunk) - z * p_chunk);
-                    const int64_t no = std::min<int64_t>(fwh::kObsTile, O - t * fwh::kObsTile);
+                    const int64_t no = std::min<int64_t>(tile, O - t * tile);
                     const int64_t nk = std::min<int64_t>(kstep, ntm - kb * kstep);
                     items.push_back({(double)np * no * nk, make_int4(c, (int)t, (int)kb, (int)z)});
                 }
@@ -852,7 +922,8 @@ int fwh_batch_bind(fwh_batch *b, void *workspace, size_t workspace_bytes, void *
     hipError_t e;
     if ((e = hipGetDevice(&dev)) || (e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev)))
         return hip_fail("fwh_batch_bind: device query", e);
-    b->grid = (int64_t)cus * b->blocks_per_cu;
+    // blocks_per_cu counts blocks of kLdsWaves waves; the matrix-core gather's are smaller
+    b->grid = (int64_t)cus * b->blocks_per_cu * (b->kind == FWH_GATHER_MFMA ? fwh::kLdsWaves / fwh::kYWaves : 1);
     b->ws = static_cast<char *>(workspace);
     if ((e = hipMemcpyAsync(b->at<fwh::BatchCase>(b->off_cases), desc.data(), desc.size() * sizeof(fwh::BatchCase),
                             hipMemcpyHostToDevice, st)) ||
@@ -879,7 +950,7 @@ int fwh_batch_forward(fwh_batch *b, void *stream_) {
     g_last_error.clear();
     if (!b || !b->bound) return fail(FWH_ESTATE, "fwh_batch_forward: batch is not bound");
     hipError_t e = fwh::launch_batch_forward(b->in_dtype == FWH_F64 ? 0 : 1, b->mode == FWH_MODE_F32 ? 1 : 2,
-                                             b->kind == FWH_GATHER_MFMA ? b->umax : 0,
+                                             b->kind == FWH_GATHER_MFMA,
                                              b->at<fwh::BatchCase>(b->off_cases), batch_index(b),
                                              b->at<int4>(b->off_items), (int)b->n_items, b->at<int>(b->off_counter),
                                              (int)b->grid, b->shmem, b->blocks_src, b->blocks_srcg, b->blocks_red,

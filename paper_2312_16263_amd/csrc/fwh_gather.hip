@@ -12,75 +12,14 @@
 //   g_{o,p}(i) = sum_c K_c(o,p) coef_c(p, i).
 // The forward kernels combine the channels first (8 FMA per new index) and then
 // apply the 4 taps (4 FMA per output): 12 FMA per (panel, observer, sample); the
-// contraction over channels has length 8 and each pair has its own shift.  The
-// transposed gather sums over observers, a contraction of length O for every
-// (panel, index): it runs on the matrix cores.
+// contraction over channels has length 8 and each pair has its own shift.  (The
+// transposed gather, fwh_adj.hip, sums over observers.)
 #include <type_traits>
 
 #include "fwh_internal.h"
 
 namespace fwh {
 namespace {
-
-// ---------------------------------------------------------- plain FP64 forms
-
-// One thread per (observer, sample): loop over panels, interpolate each channel.
-__global__ __launch_bounds__(256) void gather_f64_kernel(const double *__restrict__ K64,
-                                                         const double *__restrict__ W64,
-                                                         const int32_t *__restrict__ N0,
-                                                         const int32_t *__restrict__ nt,
-                                                         const double *__restrict__ coef, int64_t P, int64_t NS,
-                                                         int64_t nt_max, int64_t kblocks, double *__restrict__ out) {
-    const int64_t o = blockIdx.x / kblocks;
-    const int64_t k = (blockIdx.x - o * kblocks) * blockDim.x + threadIdx.x;
-    if (k >= nt_max) return;
-    if (k >= nt[o]) {
-        out[o * nt_max + k] = 0.0;
-        return;
-    }
-    double acc = 0.0;
-    for (int64_t p = 0; p < P; ++p) {
-        const int64_t pr = o * P + p;
-        const int64_t base = (int64_t)N0[pr] + k;
-        double s = 0.0;
-        for (int jj = 0; jj < 4; ++jj) {
-            double g = 0.0;
-            for (int c = 0; c < 8; ++c) g += K64[pr * 8 + c] * coef[((p * 2 + (c >> 2)) * NS + base + jj) * 4 + (c & 3)];
-            s += W64[pr * 4 + jj] * g;
-        }
-        acc += s;
-    }
-    out[o * nt_max + k] = acc;
-}
-
-// One thread per (panel, coefficient index i): loop over observers,
-//   cbar_c(p, i) = sum_o K_c(o,p) sum_jj w_jj(o,p) gbar(o, i - n0(o,p) - jj),
-// with gbar taken as zero outside 0 <= k < N_t(o).
-__global__ __launch_bounds__(256) void adj_gather_f64_kernel(const double *__restrict__ K64,
-                                                             const double *__restrict__ W64,
-                                                             const int32_t *__restrict__ N0,
-                                                             const int32_t *__restrict__ nt,
-                                                             const double *__restrict__ gbar, int64_t P, int64_t O,
-                                                             int64_t NS, int64_t nt_max, int64_t iblocks,
-                                                             double *__restrict__ cbar) {
-    const int64_t p = blockIdx.x / iblocks;
-    const int64_t i = (blockIdx.x - p * iblocks) * blockDim.x + threadIdx.x;
-    if (i >= NS) return;
-    double acc[8];
-    for (int c = 0; c < 8; ++c) acc[c] = 0.0;
-    for (int64_t o = 0; o < O; ++o) {
-        const int64_t pr = o * P + p;
-        const int64_t kb = i - (int64_t)N0[pr];
-        const int64_t ntl = nt[o];
-        double h = 0.0;
-        for (int jj = 0; jj < 4; ++jj) {
-            const int64_t k = kb - jj;
-            if (k >= 0 && k < ntl) h += W64[pr * 4 + jj] * gbar[o * nt_max + k];
-        }
-        for (int c = 0; c < 8; ++c) acc[c] += K64[pr * 8 + c] * h;
-    }
-    for (int c = 0; c < 8; ++c) cbar[((int64_t)c * P + p) * NS + i] = acc[c];
-}
 
 // ---------------------------------------------------------------- tuned FP32
 
@@ -131,13 +70,21 @@ __global__ __launch_bounds__(256) void gather_tuned_kernel(const PairRec *__rest
     const int64_t pb = z * p_chunk;
     const int64_t pe = pb + p_chunk < P ? pb + p_chunk : P;
     const int64_t kl = k0 + kGatherKT * lane;
-    const PairRec *rr = rec + o * P;
+    const int64_t t = o / kYTile;
+    const int s = (int)(o - t * kYTile), nc = rec_tile_obs(t, O);
     float acc[4] = {0.f, 0.f, 0.f, 0.f};
     double accd[4] = {0.0, 0.0, 0.0, 0.0};
     int cnt = 0;
     for (int64_t p = pb; p < pe; ++p) {
-        const PairRec r = rr[p];
-        int64_t base = (int64_t)r.n0 + kl;
+        const uint32_t *blk = rec_block(rec, t, p, P, nc);
+        struct {
+            float K[8], w[4];
+        } r;
+#pragma unroll
+        for (int c = 0; c < 8; ++c) r.K[c] = __uint_as_float(blk[rec_dword(c, s, nc)]);
+#pragma unroll
+        for (int jj = 0; jj < 4; ++jj) r.w[jj] = __uint_as_float(blk[kRecW * nc + 4 * s + jj]);
+        int64_t base = (int64_t)(int32_t)blk[kRecN0 * nc + s] + kl;
         if (base > NS - 4) base = NS - 4;  // only lanes whose samples are past N_t(o) reach the clamp
         const TS *c0 = coef + ((p * 2) * NS + base) * 4;   // group 0 quads at base .. base+3
         const TS *c1 = c0 + NS * 4;                        // group 1
@@ -276,6 +223,7 @@ __device__ __forceinline__ void gather_lds_body(const GatherArgs &a, int64_t t, 
                                                 unsigned char *stA, unsigned char *stB) {
     constexpr int TILE = kLdsWaves * OPW;         // observer slots of the block
     constexpr int KB = SUBW * kLdsLanesOut;       // samples of the block
+    constexpr int kTiles = TILE / kYTile;         // pair-table tiles of the block's observers
     const PairRec *__restrict__ rec = a.rec;
     const int2 *__restrict__ tw = a.tw;
     const int32_t *__restrict__ nt = a.nt;
@@ -305,6 +253,8 @@ __device__ __forceinline__ void gather_lds_body(const GatherArgs &a, int64_t t, 
     // j < nobs.
     auto slot_of = [&](int j) { return ADJ ? wv * OPW + j : j * kLdsWaves + wv; };
 
+    const PairRec *const rec_t = rec + tbase * P;
+    const PairBf *const rbf_t = a.rbf + tbase * P;
     // issue the loads of the stage starting at panel ps into the stage buffer `base`
     auto fill = [&](int64_t ps, unsigned char *base) {
         const int np = (int)(pe - ps < PT ? pe - ps : PT);
@@ -323,16 +273,19 @@ __device__ __forceinline__ void gather_lds_body(const GatherArgs &a, int64_t t, 
                 copy_to_lds<16>(src, last, base + q * win_bytes + g * NW * EB, units, wv, lane);
             }
         }
-        // records: for panel q, observer slot j -> 64 bytes at [q][j]
+        // pair tables (blocks of fwh_internal.h): for panel q, observer slot j 64 bytes at [q][j]: its 8 K, its
+        // 4 taps and the 4 n0w of its group of 4 slots, 16 bytes per lane; slots past the last one repeat it.
+        // (Pairs of one tile count below 2^32: beyond, its table and P coefficient rows exceed the memory.)
         unsigned char *rbase = base + (size_t)PT * win_bytes;
-        const int runits = np * TILE * 4;  // 16-byte units
+        const int runits = np * TILE * 4;
         for (int ci = wv; ci * 64 < runits; ci += kLdsWaves) {
-            int u = ci * 64 + lane;
-            u = u < runits ? u : runits - 1;
-            const int q = u / (TILE * 4), r = u - q * (TILE * 4);
-            const int64_t jj = (r >> 2) < ot_last ? (r >> 2) : ot_last;
-            const float4 *srec = reinterpret_cast<const float4 *>(rec + (tbase + jj) * P + ps + q) + (r & 3);
-            __builtin_amdgcn_global_load_lds((const void *)srec, (lds_ptr_t)(rbase + ci * 64 * 16), 16, 0, 0);
+            int l = lane;
+            asm volatile("" : "+v"(l));  // not hoisted out of the panel loop: its registers are all in use
+            const int q = ci / kTiles, j = min(ci % kTiles * kYTile + (l >> 2), (int)ot_last), uu = l & 3;
+            const int h = j & ~(kYTile - 1), c = min((int)(O - tbase) - h, kYTile), js = j & (kYTile - 1);
+            const int at = uu < 2 ? 2 * js + uu : (uu == 2 ? kRecW / 4 * c + js : (kRecN0w * c) / 4 + (js >> 2));
+            const float4 *sr = reinterpret_cast<const float4 *>(rec_t + ((uint32_t)h * (uint32_t)P + (uint32_t)(ps + q) * c)) + at;
+            __builtin_amdgcn_global_load_lds((const void *)sr, (lds_ptr_t)(rbase + ci * 64 * 16), 16, 0, 0);
         }
         if constexpr (kBf) {
             // split weights: for panel q, observer slot j -> 32 bytes at [q][j]
@@ -340,10 +293,12 @@ __device__ __forceinline__ void gather_lds_body(const GatherArgs &a, int64_t t, 
             const int bunits = np * TILE * 2;
             for (int ci = wv; ci * 64 < bunits; ci += kLdsWaves) {
                 int u = ci * 64 + lane;
+                asm volatile("" : "+v"(u));
                 u = u < bunits ? u : bunits - 1;
-                const int q = u / (TILE * 2), r = u - q * (TILE * 2);
-                const int64_t jj = (r >> 1) < ot_last ? (r >> 1) : ot_last;
-                const uint4 *sb = reinterpret_cast<const uint4 *>(a.rbf + (tbase + jj) * P + ps + q) + (r & 1);
+                const int q = u / (TILE * 2), j = min((u - q * (TILE * 2)) >> 1, (int)ot_last);
+                const int h = j & ~(kYTile - 1), c = min((int)(O - tbase) - h, kYTile);
+                const uint4 *sb = reinterpret_cast<const uint4 *>(
+                    rbf_t + ((uint32_t)h * (uint32_t)P + (uint32_t)(ps + q) * c + (j & (kYTile - 1)))) + (u & 1);
                 __builtin_amdgcn_global_load_lds((const void *)sb, (lds_ptr_t)(bbase + ci * 64 * 16), 16, 0, 0);
             }
         }
@@ -399,7 +354,7 @@ __device__ __forceinline__ void gather_lds_body(const GatherArgs &a, int64_t t, 
             const int slot = q * TILE + slot_of(j);
             const float4 *R = lrec + slot * 4;
             const float4 W = R[2];
-            const int b0 = qb + __float_as_int(R[3].y);
+            const int b0 = qb + reinterpret_cast<const int *>(R + 3)[slot_of(j) & 3];
             const QT *P0 = reinterpret_cast<const QT *>(sb + b0);
             const QT *P1 = reinterpret_cast<const QT *>(sb + (b0 + NW * EB));
             float4 Ka, Kb;
@@ -409,8 +364,10 @@ __device__ __forceinline__ void gather_lds_body(const GatherArgs &a, int64_t t, 
                 Kh = B[0];
                 Kl = B[1];
             } else {
-                Ka = R[0];
-                Kb = R[1];
+                // K_0, K_4, K_1, K_5, K_2, K_6, K_3, K_7
+                const float4 k0 = R[0], k1 = R[1];
+                Ka = make_float4(k0.x, k0.z, k1.x, k1.z);
+                Kb = make_float4(k0.y, k0.w, k1.y, k1.w);
             }
 #pragma unroll
             for (int m = 0; m < NSUB; ++m) {
@@ -621,19 +578,22 @@ __global__ __launch_bounds__(kStreamWaves * 64) void gather_stream_kernel(Gather
         const unsigned char *src = reinterpret_cast<const unsigned char *>(a.coef) + (size_t)p * 2 * row_bytes;
         const int units = (int)(2 * row_bytes / 16);
         copy_to_lds<16, kStreamWaves>(src, units - 1, base, units, wv, lane);
-        // records of the observers (slots past the last observer repeat it): 4 pieces of 16 bytes each
+        // records of the observers (all in one tile; slots past the last observer repeat it), one dword
+        // per lane: waves 0 and 1 (records), 2 (BF16 split weights)
         unsigned char *rb = base + 2 * row_bytes;
-        if (wv == 0 && lane < kLdsWaves * 4) {
-            const int64_t j = (lane >> 2) < o_last ? (lane >> 2) : o_last;
-            const float4 *sr = reinterpret_cast<const float4 *>(rec + j * P + p) + (lane & 3);
-            __builtin_amdgcn_global_load_lds((const void *)sr, (lds_ptr_t)rb, 16, 0, 0);
+        const int nc = (int)O;
+        if (wv < 2) {
+            const int u = wv * 64 + lane, j = u >> 4;
+            const uint32_t *sr = rec_block(rec, 0, p, P, nc) + rec_dword(u & 15, j < (int)o_last ? j : (int)o_last, nc);
+            __builtin_amdgcn_global_load_lds((const void *)sr, (lds_ptr_t)(rb + wv * 256), 4, 0, 0);
         }
         if constexpr (kBf) {
-            if (wv == 1 && lane < kLdsWaves * 2) {
-                const int64_t j = (lane >> 1) < o_last ? (lane >> 1) : o_last;
-                const uint4 *sb = reinterpret_cast<const uint4 *>(a.rbf + j * P + p) + (lane & 1);
-                __builtin_amdgcn_global_load_lds((const void *)sb, (lds_ptr_t)(rb + kLdsWaves * sizeof(PairRec)),
-                                                 16, 0, 0);
+            if (wv == 2) {
+                const int j = lane >> 3;
+                const uint32_t *sb =
+                    rbf_block(a.rbf, 0, p, P, nc) + 8 * (j < (int)o_last ? j : (int)o_last) + (lane & 7);
+                __builtin_amdgcn_global_load_lds((const void *)sb, (lds_ptr_t)(rb + kLdsWaves * sizeof(PairRec)), 4,
+                                                 0, 0);
             }
         }
     };
@@ -683,7 +643,7 @@ __global__ __launch_bounds__(kStreamWaves * 64) void gather_stream_kernel(Gather
             const float4 W = R[2];
             // both groups' rows addressed from the buffer base (formed as P0 + NS, the second would make
             // the compiler wait for the copies into the other buffer before reading it)
-            const int e0 = __float_as_int(R[3].x) + r0 * kLdsLanesOut + lane;
+            const int e0 = __float_as_int(R[3].y) + r0 * kLdsLanesOut + lane;
             const QT *P0 = reinterpret_cast<const QT *>(cur) + e0;
             const QT *P1 = reinterpret_cast<const QT *>(cur + row_bytes) + e0;
             float4 Ka, Kb;
@@ -758,213 +718,6 @@ __global__ __launch_bounds__(kStreamWaves * 64) void gather_stream_kernel(Gather
 
 __global__ void reset_counter_kernel(int *counter) { counter[0] = 0; }
 
-// Zero-padded copy of dJ/dp': gpad[o][k + padlo] = gbar[o][k] for 0 <= k < N_t(o), 0 elsewhere.
-__device__ __forceinline__ void pad_grad_body(const PadArgs &a, int64_t i) {
-    if (i >= a.O * a.LR) return;
-    const int64_t o = i / a.LR;
-    const int64_t k = i - o * a.LR - a.padlo;
-    a.gpad[i] = (k >= 0 && k < a.nt[o]) ? a.gbar[o * a.nt_max + k] : 0.f;
-}
-
-__global__ __launch_bounds__(256) void pad_grad_kernel(PadArgs a) {
-    pad_grad_body(a, (int64_t)blockIdx.x * 256 + threadIdx.x);
-}
-
-__global__ __launch_bounds__(256) void pad_grad_batched(const BatchCase *__restrict__ cases,
-                                                        const int64_t *__restrict__ start, int n) {
-    const int c = find_case(start, n, blockIdx.x);
-    pad_grad_body(cases[c].pad, ((int64_t)blockIdx.x - start[c]) * 256 + threadIdx.x);
-}
-
-// Transposed gather on the matrix cores.  For panel p and coefficient index i,
-//   cbar_c(p, i) = sum_o K_c(o, p) H(o, i),  H(o, i) = sum_j w_j(o, p) gbar(o, i - n0(o, p) - j),
-// a contraction over observers, one 16x16x4 FP32 MFMA per 4 observers and 16
-// indices: A[m][k] = H(observer o + k, index m), B[k][n] = K_n(o + k, p) (zero for
-// n >= 8), D[m][n] = the cbar contribution of channel n at index m.  The taps
-// stay on the VALU: lane (q, s) of the wave (q = lane / 16, s = lane % 16) owns
-// observer o + q and the 4 indices ib + 4 s + t (t = 0..3), loads gbar at the 4
-// shifted positions with one 16-byte load, takes the 3 positions below from lane
-// s - 1 of its row (a row shift; lane s = 0 takes them from lane 15's load of
-// the previous block of 64, by a row rotation, and loads them for the first
-// block), and forms H for its 4 indices.  MFMA t takes the rows m = s as index ib + 4 m + t, so lane (q', n)
-// of its output holds channel n at indices ib + 16 q' + 4 r + t (r = 0..3): 16
-// consecutive indices per lane over t and r, stored as 4 float4.
-//
-// A wave owns panel p and kAdjMW blocks of 64 indices.  Waves go in tiles of
-// kAdjPT panels x all index blocks, panels fastest: the 4 waves of a block (and
-// neighbouring blocks on one XCD) read the same observers' gbar windows a few
-// samples apart and adjacent pair records, and a tile's records stay in L2 for
-// all its index blocks.  Each row q fetches its pair record with one dword per lane (lane s:
-// dword s of the 64-byte record, so lanes s < 8 hold K_s) and takes the taps and
-// n0 from lanes 8..12 of the row by row broadcasts.
-typedef float floatx4_t __attribute__((ext_vector_type(4)));
-
-__device__ __forceinline__ float adj_row_rot(float x) {
-    // lane s of each row of 16 receives lane s - 1 (mod 16); every lane has a source, so no old value
-    // (and no move to set one) is needed
-    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0x121 /* row_ror:1 */, 0xF, 0xF, false));
-}
-
-__device__ __forceinline__ float adj_row_prev(float x, float old) {
-    // lane s of each row of 16 receives lane s - 1's x; lane 0 keeps `old`
-    return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(old), __float_as_int(x), 0x111 /* row_shr:1 */,
-                                                      0xF, 0xF, false));
-}
-
-template <int LANE>
-__device__ __forceinline__ float adj_row_bcast(float x) {
-    // every lane of each row of 16 receives lane LANE of its row (no old value needed)
-    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0x150 + LANE /* row_newbcast */, 0xF, 0xF, false));
-}
-
-struct __attribute__((packed, aligned(4))) AdjF4 {
-    float x, y, z, w;
-};
-
-// One group of 4 observers (one per row q of the wave): the row's pair record
-// spread over its 16 lanes, and the gbar windows.
-struct AdjGroup {
-    float rv;          // dword s of the record of (o + q, p)
-    AdjF4 x[kAdjMW];   // gbar at e .. e + 3, e = ib + 64 u + 4 s - n0
-    AdjF4 pv;          // gbar at e - 4 .. e - 1 of block u = 0 (lane s = 0 only)
-};
-
-__device__ __forceinline__ void adj_gather_mfma_body(const AdjArgs &a, int64_t wave_id) {
-    const int64_t P = a.P, O = a.O, NS = a.NS, LR = a.LR, nib = a.nib;
-    if (wave_id >= P * nib) return;
-    // tile of kAdjPT panels (the last one narrower) x nib index blocks, panels fastest
-    const int64_t tile = wave_id / (kAdjPT * nib);
-    const int64_t r = wave_id - tile * (kAdjPT * nib);
-    const int64_t tw = min<int64_t>(kAdjPT, P - tile * kAdjPT);
-    const int64_t bi = r / tw;
-    const int64_t p = tile * kAdjPT + (r - bi * tw);
-    const int64_t ib = bi * (64 * kAdjMW);
-    const int nsub = (int)min<int64_t>(kAdjMW, (NS - ib) >> 6);  // NS is a multiple of 64
-    const int lane = threadIdx.x & 63, q = lane >> 4, s = lane & 15;
-    const float *g = a.gpad + a.padlo + ib + 4 * s;
-    const float *rp = reinterpret_cast<const float *>(a.rec + p) + s;
-    // index blocks past nsub load the last one again (in bounds) and skip their MFMAs
-    int uoff[kAdjMW];
-#pragma unroll
-    for (int u = 0; u < kAdjMW; ++u) uoff[u] = 64 * min(u, nsub - 1);
-    floatx4_t acc[kAdjMW][4];
-#pragma unroll
-    for (int u = 0; u < kAdjMW; ++u)
-#pragma unroll
-        for (int t = 0; t < 4; ++t) acc[u][t] = floatx4_t{0.f, 0.f, 0.f, 0.f};
-    // Loads run ahead of the arithmetic: while group o is on the VALU and the matrix cores, the
-    // gbar windows of group o + 4 and the records of group o + 8 are in flight.  Observers past O
-    // are clamped to O - 1 for the loads and get K = 0.
-    constexpr int64_t kRecDwords = sizeof(PairRec) / 4;
-    auto load_rec = [&](int64_t o) { return rp[min(o + q, O - 1) * P * kRecDwords]; };
-    auto load_x = [&](int64_t o, AdjGroup &b) {
-        const int n0 = __float_as_int(adj_row_bcast<12>(b.rv));
-        const float *go = g + min(o + q, O - 1) * LR - n0;
-#pragma unroll
-        for (int u = 0; u < kAdjMW; ++u) b.x[u] = *reinterpret_cast<const AdjF4 *>(go + uoff[u]);
-        // only lane 0 of each row uses pv; every lane loads it (in bounds: the row's lead pad holds
-        // N + 4 floats and n0 <= N), so the register is not merged with its old value
-        b.pv = *reinterpret_cast<const AdjF4 *>(go - 4);
-    };
-    // Waves near either end of the index range (check): 64-index blocks u_lo .. u_hi, those
-    // that some observer of the group reaches (observer o + q adds to indices [n0, n0 + N_t + 2]
-    // only; n0 from dword 12 of each row's record, N_t bounded by the longest window); the others
-    // would get exact zeros and are skipped.  Inside [edge_lo, edge_hi] every block is reached.
-    const bool check = ib < a.edge_lo || ib + 64 * kAdjMW - 1 > a.edge_hi;  // wave-uniform
-    auto compute = [&](int64_t o, const AdjGroup &b) {
-        const float kb = (o + q < O && s < 8) ? b.rv : 0.f;
-        const float w0 = adj_row_bcast<8>(b.rv), w1 = adj_row_bcast<9>(b.rv), w2 = adj_row_bcast<10>(b.rv),
-                    w3 = adj_row_bcast<11>(b.rv);
-        int u_lo = 0, u_hi = nsub - 1;
-        if (check) {
-            int n0lo = __builtin_amdgcn_readlane(__float_as_int(b.rv), 12), n0hi = n0lo;
-#pragma unroll
-            for (int r = 1; r < 4; ++r) {
-                const int v = __builtin_amdgcn_readlane(__float_as_int(b.rv), 16 * r + 12);
-                n0lo = min(n0lo, v);
-                n0hi = max(n0hi, v);
-            }
-            const int ibi = (int)ib;
-            u_lo = max(0, (n0lo - ibi) >> 6);
-            u_hi = min(nsub - 1, (n0hi + (int)a.nt_max + 2 - ibi) >> 6);
-        }
-#pragma unroll
-        for (int u = 0; u < kAdjMW; ++u) {
-            if (u >= u_lo && u <= u_hi) {
-                const AdjF4 xv = b.x[u];
-                // lane 0's values below e: its own load (u = 0) or lane 15's of block u - 1
-                const AdjF4 &xp = b.x[u > 0 ? u - 1 : 0];
-                const float o1 = u == 0 ? b.pv.w : adj_row_rot(xp.w);
-                const float o2 = u == 0 ? b.pv.z : adj_row_rot(xp.z);
-                const float o3 = u == 0 ? b.pv.y : adj_row_rot(xp.y);
-                const float m1 = adj_row_prev(xv.w, o1);  // gbar at e - 1
-                const float m2 = adj_row_prev(xv.z, o2);  // e - 2
-                const float m3 = adj_row_prev(xv.y, o3);  // e - 3
-                const float h0 = fmaf(w3, m3, fmaf(w2, m2, fmaf(w1, m1, w0 * xv.x)));
-                const float h1 = fmaf(w3, m2, fmaf(w2, m1, fmaf(w1, xv.x, w0 * xv.y)));
-                const float h2 = fmaf(w3, m1, fmaf(w2, xv.x, fmaf(w1, xv.y, w0 * xv.z)));
-                const float h3 = fmaf(w3, xv.x, fmaf(w2, xv.y, fmaf(w1, xv.z, w0 * xv.w)));
-                acc[u][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(h0, kb, acc[u][0], 0, 0, 0);
-                acc[u][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(h1, kb, acc[u][1], 0, 0, 0);
-                acc[u][2] = __builtin_amdgcn_mfma_f32_16x16x4f32(h2, kb, acc[u][2], 0, 0, 0);
-                acc[u][3] = __builtin_amdgcn_mfma_f32_16x16x4f32(h3, kb, acc[u][3], 0, 0, 0);
-            }
-        }
-    };
-    // before step(o, cur, nxt): cur holds the record and windows of group o, nxt the record of
-    // group o + 4.  Loads complete in issue order, so the record of o + 8 goes first: the next
-    // step waits for it without waiting for the windows issued after it.
-    auto step = [&](int64_t o, AdjGroup &cur, AdjGroup &nxt) {
-        const float rnew = load_rec(o + 8);
-        load_x(o + 4, nxt);
-        compute(o, cur);
-        cur.rv = rnew;
-    };
-    AdjGroup A, B;
-    A.pv = B.pv = AdjF4{0.f, 0.f, 0.f, 0.f};
-    A.rv = load_rec(0);
-    B.rv = load_rec(4);
-    load_x(0, A);
-#pragma unroll 1
-    for (int64_t o = 0; o < O; o += 8) {
-        step(o, A, B);
-        if (o + 4 >= O) break;
-        step(o + 4, B, A);
-    }
-    if (s < 8) {
-        float *out = a.cbar + ((int64_t)s * P + p) * NS + ib + 16 * q;
-#pragma unroll
-        for (int u = 0; u < kAdjMW; ++u)
-            if (u < nsub) {
-#pragma unroll
-                for (int rr = 0; rr < 4; ++rr)
-                    *reinterpret_cast<float4 *>(out + 64 * u + 4 * rr) =
-                        make_float4(acc[u][0][rr], acc[u][1][rr], acc[u][2][rr], acc[u][3][rr]);
-            }
-    }
-}
-
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void adj_gather_mfma_kernel(AdjArgs a) {
-    // consecutive blocks (neighbouring index blocks and panels) regrouped per XCD
-    adj_gather_mfma_body(a, xcd_block(blockIdx.x, gridDim.x) * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6));
-}
-
-// Batched transposed gather over a longest-first work list: block b runs item b,
-// (case c, group g) = the waves 4 g .. 4 g + 3 of case c, wave w being (panel
-// w / nib, index block w % nib); waves past the case's P * nib return at once.
-// The items are sorted by their work (the paper's greedy partition by size) and
-// blocks are dispatched in order, so every compute unit takes the longest item
-// left when one of its blocks ends.  (A persistent form pulling items through a
-// counter keeps the case arguments live across items: it needs more registers per
-// lane than the three waves per SIMD this launch runs with allow.)
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void adj_gather_listed(const BatchCase *__restrict__ cases,
-                                                         const int2 *__restrict__ items) {
-    const int2 w = items[blockIdx.x];
-    const int c = __builtin_amdgcn_readfirstlane(w.x);
-    const int64_t g = __builtin_amdgcn_readfirstlane(w.y);
-    adj_gather_mfma_body(cases[c].adj, g * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6));
-}
-
 // out[o][k] = sum_z partial[z][o][k] in fixed order.  Eight loads are issued before they are
 // added (the sum keeps its order), so each thread has eight reads in flight instead of one.
 __device__ __forceinline__ float sum_splits(const float *__restrict__ partial, int splits, int64_t total,
@@ -1001,15 +754,6 @@ __global__ __launch_bounds__(256) void reduce_splits_kernel(const float *__restr
 }
 
 }  // namespace
-
-hipError_t launch_gather_f64(const double *K64, const double *W64, const int32_t *N0, const int32_t *nt,
-                             const double *coef, int64_t P, int64_t O, int64_t NS, int64_t nt_max, double *out,
-                             hipStream_t stream) {
-    const int64_t kblocks = (nt_max + 255) / 256;
-    gather_f64_kernel<<<dim3((unsigned)(kblocks * O)), dim3(256), 0, stream>>>(K64, W64, N0, nt, coef, P, NS, nt_max,
-                                                                              kblocks, out);
-    return hipGetLastError();
-}
 
 hipError_t launch_gather_tuned(int coef_type, const PairRec *rec_op, const int32_t *nt, const void *coef, int64_t P,
                                int64_t O, int64_t NS, int64_t nt_max, int splits, float *partial,
@@ -1161,31 +905,7 @@ hipError_t launch_reduce_splits(const float *partial, int splits, int64_t total,
     return hipGetLastError();
 }
 
-hipError_t launch_adj_gather_f64(const double *K64, const double *W64, const int32_t *N0, const int32_t *nt,
-                                 const double *gbar, int64_t P, int64_t O, int64_t NS, int64_t nt_max, double *cbar,
-                                 hipStream_t stream) {
-    const int64_t iblocks = (NS + 255) / 256;
-    adj_gather_f64_kernel<<<dim3((unsigned)(iblocks * P)), dim3(256), 0, stream>>>(K64, W64, N0, nt, gbar, P, O, NS,
-                                                                                  nt_max, iblocks, cbar);
-    return hipGetLastError();
-}
-
-hipError_t launch_adj_gather(const PairRec *rec_op, const int32_t *nt, const float *gbar, int64_t P, int64_t O,
-                                 int64_t N, int64_t NS, int64_t nt_min, int64_t nt_max, float *gpad, float *cbar,
-                                 hipStream_t stream) {
-    const int64_t edge_lo = N - nt_min, edge_hi = nt_min + 2;
-    const int64_t LR = adj_pad_row(N, NS), padlo = adj_pad_lo(N);
-    const PadArgs pa{gbar, nt, O, nt_max, LR, padlo, gpad};
-    pad_grad_kernel<<<dim3((unsigned)((O * LR + 255) / 256)), dim3(256), 0, stream>>>(pa);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    const int64_t nib = adj_blocks(NS);
-    const AdjArgs aa{rec_op, gpad, P, O, NS, LR, padlo, nib, cbar, nt_max, edge_lo, edge_hi};
-    adj_gather_mfma_kernel<<<dim3((unsigned)((P * nib + 3) / 4)), dim3(256), 0, stream>>>(aa);
-    return hipGetLastError();
-}
-
-hipError_t launch_batch_forward(int in_dtype, int coef_type, int umax, const BatchCase *cases, BatchIndex idx,
+hipError_t launch_batch_forward(int in_dtype, int coef_type, bool mfma, const BatchCase *cases, BatchIndex idx,
                                 const int4 *items, int n_items, int *counter, int grid, size_t shmem,
                                 int64_t blocks_src, int64_t blocks_srcg, int64_t blocks_red, hipStream_t stream) {
     hipError_t e =
@@ -1193,8 +913,8 @@ hipError_t launch_batch_forward(int in_dtype, int coef_type, int umax, const Bat
     if (e != hipSuccess) return e;
     reset_counter_kernel<<<1, 1, 0, stream>>>(counter);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    if (umax > 0)
-        e = launch_gather_mfma_persistent(coef_type, umax, cases, items, n_items, counter, grid, shmem, stream);
+    if (mfma)
+        e = launch_gather_mfma_persistent(coef_type, cases, items, n_items, counter, grid, shmem, stream);
     else {
         // stage buffers of the widest case: shmem holds both of them
         int sb = 0;
@@ -1226,17 +946,6 @@ hipError_t launch_batch_forward(int in_dtype, int coef_type, int umax, const Bat
     if ((e = hipGetLastError()) != hipSuccess) return e;
     reduce_batched<<<dim3((unsigned)blocks_red), dim3(256), 0, stream>>>(cases, idx.red, idx.n);
     return hipGetLastError();
-}
-
-hipError_t launch_batch_adjoint(int in_dtype, const BatchCase *cases, BatchIndex idx, int64_t blocks_pad,
-                                const int2 *adj_items, int n_adj_items, int64_t blocks_sadj, int64_t blocks_sadjg,
-                                hipStream_t stream) {
-    pad_grad_batched<<<dim3((unsigned)blocks_pad), dim3(256), 0, stream>>>(cases, idx.pad, idx.n);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    adj_gather_listed<<<dim3((unsigned)n_adj_items), dim3(256), 0, stream>>>(cases, adj_items);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    return launch_batch_source_adjoint(in_dtype, cases, idx.sadj, idx.sadjg, idx.n, blocks_sadj, blocks_sadjg, stream);
 }
 
 }  // namespace fwh

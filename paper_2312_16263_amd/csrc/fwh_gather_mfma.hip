@@ -5,30 +5,26 @@
 //   p'(o, k) = sum_p sum_jj w_jj(o,p) Y_p(o, n0(o,p) + k + jj),
 //   Y_p(o, i) = sum_c K_c(o,p) coef_c(p, i),
 // with fixed taps w, weights K and delay index n0 per (observer, panel) pair.
-// For one panel and a tile of 32 observers, Y_p over a window of coefficient
-// indices is a small dense product (32 observers x 8 channels) x (8 channels x
-// window): that part runs as matrix-core instructions, 16 observers x 16
-// indices per unit (v_mfma_f32_16x16x4f32, twice, in FP32 storage;
+// For one panel and a tile of 16 observers, Y_p over a window of coefficient
+// indices is a small dense product (window x 8 channels) x (8 channels x 16
+// observers), which runs as matrix-core instructions, 16 indices x 16 observers
+// per unit (v_mfma_f32_16x16x4f32, twice, in FP32 storage;
 // v_mfma_f32_16x16x16bf16_1k with the weights split into bfloat16 high and low
 // parts, once, in BF16 storage: products of bfloat16 values are exact in FP32,
 // so both forms accumulate exact products in FP32).  Y goes through LDS; each
-// observer then reads it at its own delay index and applies the four taps on
-// the vector ALU (one LDS read, three wavefront shifts, four FMA per lane and
-// 61 outputs), where the LDS-staged gather spent two 16-byte LDS reads and 12
-// FMA per output.
+// observer then reads it at its own delay index and applies the four taps on the
+// vector ALU.
 //
-// Block = kLdsWaves waves, observer tile t (32 observers), samples k0 ..
-// k0 + 61 * kLdsSub - 1, panels [z*p_chunk, ...).  Per panel:
-//   1. matrix units: unit u = (observer half u & 1, index block u >> 1) of the
-//      panel's window [lo + k0, lo + k0 + 16 * nblk), lo = min n0 over the tile;
-//      wave w takes u = w, w + 8, ...; operands were loaded during the previous
-//      panel; the 16 x 16 result goes to Y[observer][index] in LDS;
-//   2. barrier; the operands of the next panel are loaded meanwhile;
-//   3. taps: wave w, observers w, w + 8, w + 16, w + 24 of the tile (the valid
-//      ones), lane l of row m reads Y[j][n0_j - lo + 61 m + l];
+// Block = kYWaves waves, observer tile t (16 observers), samples k0 ..
+// k0 + 61 * rows - 1, panels [z*p_chunk, ...).  Per panel:
+//   1. matrix units of the panel's window [lo + k0, lo + k0 + need), lo = min n0 over the tile,
+//      `need` from the panel's own spread of n0, in blocks of 64 indices over the waves; the
+//      16 x 16 results go to Y[observer][index] in LDS (one 16-byte write per lane); coefficients
+//      and weights were loaded a panel ahead;
+//   2. barrier;
+//   3. taps: each wave for its observers of the tile, lane l of row m reads
+//      Y[j][n0_j - lo + 61 m + l];
 //   4. barrier (Y is rewritten by the next panel).
-// FP32 sums over kLdsChunk panels go into the split's partial signal, as in the
-// other gathers; the split sums are added in FP64 by the reduction kernel.
 #include <type_traits>
 
 #include "fwh_internal.h"
@@ -38,326 +34,372 @@ namespace {
 
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef short shortx4 __attribute__((ext_vector_type(4)));
+typedef unsigned int uintx2 __attribute__((ext_vector_type(2)));
+typedef unsigned int uintx4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(4))) const uint32_t *const_u32_t;  // uniform loads stay scalar
 
-constexpr int kMfmaChunk = 256;  // panels summed in FP32 before adding into the partial signal
+constexpr int kYChunk = 256;  // panels summed in FP32 before adding into the partial signal
+constexpr int kYBlk = 64;     // coefficient indices of one operand load
 
-// Value of lane l+1 (wavefront shift by one lane; lane 63 receives 0).
-__device__ __forceinline__ float next_lane(float x) {
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x130 /* wave_shl:1 */, 0xF, 0xF, true));
-}
-
-// Barrier for LDS data only: the waves' LDS writes are complete and visible
-// after it; outstanding global loads (the next panel's operands) stay in flight.
+// Barrier for LDS data only: the waves' LDS accesses are complete and visible after it;
+// outstanding global loads (the next panel's operands) stay in flight.
 __device__ __forceinline__ void lds_barrier() {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
-// Operands of one matrix unit: the lane's coefficient values (A) for the unit's
-// 16 indices.  FP32: lane (li, lq) holds channel lq of group 0 and of group 1 at
-// index li; BF16: the four channels of group lq & 1 at index li (lanes 32..63
-// repeat lanes 0..31 against the low parts of the weights).
+// Value of lane l+1 (wavefront shift by one lane; lane 63 receives 0).
+__device__ __forceinline__ float next_lane(float x) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x130 /* wave_shl:1 */, 0xF, 0xF, true));
+}
+
+// Taps 1 and 3 of NSUB rows: a += w1 g', b += w3 g' with g' the next lane's g (a DPP source of the FMA:
+// the shift costs no instruction).  A DPP read needs two wait states after a VALU write of its
+// source: g comes from LDS, and the s_nop covers a register copy in between.
+template <int NSUB>
+__device__ __forceinline__ void taps_next(float (&acc)[NSUB][2], const float (&g)[NSUB], float w1, float w3) {
+    if constexpr (NSUB == 4) {
+        asm("s_nop 1\n\t"
+            "v_fmac_f32_dpp %0, %8, %12 wave_shl:1 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
+            "v_fmac_f32_dpp %1, %8, %13 wave_shl:1 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
+            "v_fmac_f32_dpp %2, %9, %12 wave_shl:1 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
+            "v_fmac_f32_dpp %3, %9, %13 wave_shl:1 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
+            "v_fmac_f32_dpp %4, %10, %12 wave_shl:1 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
+            "v_fmac_f32_dpp %5, %10, %13 wave_shl:1 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
+            "v_fmac_f32_dpp %6, %11, %12 wave_shl:1 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
+            "v_fmac_f32_dpp %7, %11, %13 wave_shl:1 row_mask:0xf bank_mask:0xf bound_ctrl:1"
+            : "+v"(acc[0][0]), "+v"(acc[0][1]), "+v"(acc[1][0]), "+v"(acc[1][1]), "+v"(acc[2][0]), "+v"(acc[2][1]),
+              "+v"(acc[3][0]), "+v"(acc[3][1])
+            : "v"(g[0]), "v"(g[1]), "v"(g[2]), "v"(g[3]), "v"(w1), "v"(w3));
+    } else {
+#pragma unroll
+        for (int m = 0; m < NSUB; ++m)
+            asm("s_nop 1\n\t"
+                "v_fmac_f32_dpp %0, %2, %3 wave_shl:1 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
+                "v_fmac_f32_dpp %1, %2, %4 wave_shl:1 row_mask:0xf bank_mask:0xf bound_ctrl:1"
+                : "+v"(acc[m][0]), "+v"(acc[m][1])
+                : "v"(g[m]), "v"(w1), "v"(w3));
+    }
+}
+
+// Coefficients of kYBlk indices (four matrix units of 16) of both channel groups.  The loads go
+// through a buffer descriptor of the panel's two rows (indices past them read zero), consecutive
+// lanes reading consecutive memory; unit(t) turns unit t into the A operand by row swaps.  (Loading
+// the operand lanes directly, channel lane / 16 of index lane % 16, made every 16 lanes touch 256
+// bytes for 64 bytes of data and held the kernel at the texture addresser: 15.1 ms against 10.2 ms
+// for the LDS-staged gather on the 32768-panel, 360-observer sphere.)
 template <typename TS>
-struct MfmaA;
+struct YBlock;
 template <>
-struct MfmaA<float> {
-    float a0, a1;
+struct YBlock<float> {
+    uintx4 x0, x1;  // lane l: the 4 channels of group 0, 1 at index l
+    static __device__ __forceinline__ int lane_offset(int lane, int) { return lane * 16; }
+    static __device__ __forceinline__ int lane_index(int lane) { return lane; }  // lowest index the lane loads
+    __device__ __forceinline__ void load(__amdgpu_buffer_rsrc_t r, int voff, int soff, int rowb) {
+        x0 = __builtin_amdgcn_raw_buffer_load_b128(r, voff, soff, 0);
+        x1 = __builtin_amdgcn_raw_buffer_load_b128(r, voff, soff + rowb, 0);
+    }
+    // 4 x 4 transposes of (register = channel, row of 16 lanes = unit): then register t holds, in row
+    // q, channel q of unit t
+    static __device__ __forceinline__ void transpose(uintx4 &x) {
+        const auto a = __builtin_amdgcn_permlane32_swap(x[0], x[2], false, false);
+        const auto b = __builtin_amdgcn_permlane32_swap(x[1], x[3], false, false);
+        const auto c = __builtin_amdgcn_permlane16_swap(a[0], b[0], false, false);
+        const auto d = __builtin_amdgcn_permlane16_swap(a[1], b[1], false, false);
+        x = uintx4{c[0], c[1], d[0], d[1]};
+    }
+    __device__ __forceinline__ void prepare() {
+        transpose(x0);
+        transpose(x1);
+    }
+    template <int T>
+    __device__ __forceinline__ floatx4 unit(uintx2 b) const {
+        floatx4 d = {0.f, 0.f, 0.f, 0.f};
+        d = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(x0[T]), __uint_as_float(b.x), d, 0, 0, 0);
+        return __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(x1[T]), __uint_as_float(b.y), d, 0, 0, 0);
+    }
 };
 template <>
-struct MfmaA<uint16_t> {
-    uint2 a;
+struct YBlock<uint16_t> {
+    // x[h]: lane (row q, li): the 4 channels of group q & 1 at index 32 h + 16 (q >> 1) + li
+    uintx2 x[2];
+    static __device__ __forceinline__ int lane_offset(int lane, int rowb) {
+        return (lane & 15) * 8 + (lane >> 5) * 128 + ((lane >> 4) & 1) * rowb;
+    }
+    static __device__ __forceinline__ int lane_index(int lane) { return (lane & 15) + (lane >> 5) * 16; }
+    __device__ __forceinline__ void load(__amdgpu_buffer_rsrc_t r, int voff, int soff, int) {
+        x[0] = __builtin_amdgcn_raw_buffer_load_b64(r, voff, soff, 0);
+        x[1] = __builtin_amdgcn_raw_buffer_load_b64(r, voff + 256, soff, 0);
+    }
+    __device__ __forceinline__ void prepare() {}
+    // unit T: its two rows (groups 0 and 1) against the high parts of the weights, and again against
+    // the low parts
+    template <int T>
+    __device__ __forceinline__ floatx4 unit(uintx2 b) const {
+        const uintx2 v = x[T >> 1];
+        const auto p = __builtin_amdgcn_permlane32_swap(v.x, v.x, false, false);
+        const auto q = __builtin_amdgcn_permlane32_swap(v.y, v.y, false, false);
+        const uintx2 a = {p[T & 1], q[T & 1]};
+        const floatx4 d = {0.f, 0.f, 0.f, 0.f};
+        return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(shortx4, a), __builtin_bit_cast(shortx4, b),
+                                                         d, 0, 0, 0);
+    }
 };
 
-template <typename TS, int UMAX>
-__device__ __forceinline__ void gather_mfma_body(const GatherArgs &a, int64_t t, int64_t kb, int64_t z,
-                                                 float *__restrict__ Y) {
+template <int I, int N, typename F>
+__device__ __forceinline__ void unroll(F &&f) {
+    if constexpr (I < N) {
+        f(std::integral_constant<int, I>{});
+        unroll<I + 1, N>(f);
+    }
+}
+
+// One (tile, k block, split): NSUB rows of 61 samples have an output inside some window of the
+// tile; FULL: all kYTile observers exist.
+template <typename TS, int NSUB, bool FULL, int AHEAD>
+__device__ __forceinline__ void gather_y_panels(const GatherArgs &a, int64_t t, int nobs, int64_t k0, int64_t z,
+                                                float *__restrict__ Y) {
     constexpr bool kBf = std::is_same<TS, uint16_t>::value;
-    const PairRec *__restrict__ rec = a.rec;
-    const int2 *__restrict__ tw = a.tw;
-    const int32_t *__restrict__ nt = a.nt;
-    const TS *__restrict__ coef = static_cast<const TS *>(a.coef);
-    const int64_t P = a.P, O = a.O, NS = a.NS, nt_max = a.nt_max, p_chunk = a.p_chunk;
-    const int YR = a.NW;      // row length (floats) of the Y tile
-    const int rows = a.rows;  // rows of 61 samples per block
-    float *__restrict__ partial = a.partial;
-    // the tile's pair records (and BF16 split weights) of one panel, two buffers after the Y tile
-    unsigned char *recs = reinterpret_cast<unsigned char *>(Y + kObsTile * YR);
+    constexpr int EB = 4 * (int)sizeof(TS);                 // bytes of one index of one channel group
+    constexpr int OPW = kYTile / kYWaves;                   // observers per wave (at most)
+    // operand blocks per wave that every panel needs; with a single one (NSUB = 1) every wave loads it, and
+    // any further one, and does one of its four units
+    constexpr bool kShare = NSUB == 1;
+    static_assert(kYWaves == 4, "a block of 64 indices is four units");
+    constexpr int MW = (NSUB + kYWaves - 1) / kYWaves;
     const int lane = threadIdx.x & 63;
     const int li = lane & 15, lq = lane >> 4;
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int64_t k0 = kb * kLdsLanesOut * rows;
-    const int64_t pb = z * p_chunk;
-    const int64_t pe = pb + p_chunk < P ? pb + p_chunk : P;
-    const int64_t tbase = t * kObsTile;
-    const int2 *twt = tw + t * P;
-    const int64_t ot_last = (O - 1 - tbase) < kObsTile - 1 ? (O - 1 - tbase) : kObsTile - 1;
+    const int64_t P = a.P, O = a.O, nt_max = a.nt_max, tbase = t * kYTile;
+    const int64_t pb = z * a.p_chunk, pe = pb + a.p_chunk < P ? pb + a.p_chunk : P;
+    const int YR = a.NW;
+    const int rowb = (int)a.NS * EB;
+    // lane li of each row of 16 lanes is observer slot li: its column of the matrix product (slots past
+    // the last observer repeat it), its row of Y; the wave's own observers are slots own0 + j
+    const int slot = FULL ? li : (li < nobs ? li : nobs - 1);
+    const int per_wave = FULL ? OPW : (nobs + kYWaves - 1) / kYWaves;
+    const int own0 = wv * per_wave;
+    const int nown = FULL ? OPW : (nobs - own0 < per_wave ? (nobs > own0 ? nobs - own0 : 0) : per_wave);
 
-    // rows of 61 samples below the longest window of the tile (the matrix units cover them) and,
-    // for this wave's observers (a prefix j < nobs of wv, wv + 8, ...), below the longest of theirs
-    int nt_tile = 0, nt_wave = 0, nobs = 0;
-    for (int j = 0; j <= ot_last; ++j) {
-        const int n = nt[tbase + j];
-        nt_tile = n > nt_tile ? n : nt_tile;
-        if ((j & (kLdsWaves - 1)) == wv) {
-            nt_wave = n > nt_wave ? n : nt_wave;
-            nobs = j / kLdsWaves + 1;
-        }
-    }
-    auto rows_below = [&](int n) {
-        int r = (int)((n - k0 + kLdsLanesOut - 1) / kLdsLanesOut);
-        return __builtin_amdgcn_readfirstlane(r < 0 ? 0 : (r > rows ? rows : r));
-    };
-    const int nsub_blk = rows_below(nt_tile);
-    const int nsub = rows_below(nt_wave);
-    nobs = __builtin_amdgcn_readfirstlane(nobs);
+    float acc[OPW][NSUB][2];
+#pragma unroll
+    for (int j = 0; j < OPW; ++j)
+#pragma unroll
+        for (int m = 0; m < NSUB; ++m) acc[j][m][0] = acc[j][m][1] = 0.f;
 
-    // this wave's outputs of observer slot j: the split's partial signal row (uniform) and the lane's
-    // sample offsets k0 + 61 m + lane; the row address is formed where it is used (an empty asm makes
-    // it opaque, so that it is not kept live across the panel loop)
-    auto out_row = [&](int j) -> float * {
-        float *row = partial + (z * O + tbase + j * kLdsWaves + wv) * nt_max;
-        asm volatile("" : "+s"(row));
-        return row;
-    };
-    const int k_lane = (int)k0 + lane;
-    const bool lane_out = lane < kLdsLanesOut;
-
-    // window start and width of panel p (lane q of `win` holds panel ps + q)
+    // window start (n0 - d16) and width of panel p, lane q: panel ps + q
+    int wlo = 0, wwd = 0;
     auto load_win = [&](int64_t ps) {
         const int64_t q = ps + lane < pe ? ps + lane : pe - 1;
-        return twt[q];
+        const uint32_t *blk = rec_block(a.rec, t, q, P, nobs);
+        wlo = (int)(blk[kRecN0 * nobs] - blk[kRecD16 * nobs]);
+        wwd = (int)blk[kRecW16 * nobs];
     };
-    auto n_units = [&](int width) {
-        return 2 * ((width + kLdsLanesOut * nsub_blk + kLdsHalo + 15) / 16);
+    const int voff = YBlock<TS>::lane_offset(lane, rowb);
+    const uint32_t *kp = (kBf ? rbf_block(a.rbf, t, pb, P, nobs) : rec_block(a.rec, t, pb, P, nobs)) + 8 * slot + 2 * lq;
+    // Taps and window offsets of the wave's own observers, wave-uniform.  AHEAD = 1: scalar loads at the
+    // panel's start.  Else (few waves to hide their latency behind) one vector load with the operands,
+    // lane 4 j + q: w_q of own observer j, lane 4 OPW + j: its offset, moved to scalars when used.
+    struct Taps {
+        float w[OPW][4];
+        int d[OPW];
     };
-
-    // Records of a panel through registers: waves 0 and 1 load the 32 records (128 pieces of 16
-    // bytes), wave 2 in BF16 the 32 split weights (64 pieces), while the taps of the previous panel
-    // run, and write them to the panel's record buffer afterwards.  (Direct global->LDS loads would
-    // make the compiler wait for them before the taps' LDS reads.)
-    constexpr int kRecBytes = kObsTile * (int)sizeof(PairRec);
-    constexpr int kRecBuf = kRecBytes + (kBf ? kObsTile * (int)sizeof(PairBf) : 0);
-    uint4 rstage = make_uint4(0u, 0u, 0u, 0u);
-    auto load_recs = [&](int64_t p) {
-        if (wv < 2) {
-            const int u = wv * 64 + lane, j = u >> 2;
-            const int64_t o = tbase + (j < ot_last ? j : ot_last);
-            rstage = reinterpret_cast<const uint4 *>(rec + o * P + p)[u & 3];
-        } else if (kBf && wv == 2) {
-            const int j = lane >> 1;
-            const int64_t o = tbase + (j < ot_last ? j : ot_last);
-            rstage = reinterpret_cast<const uint4 *>(a.rbf + o * P + p)[lane & 1];
-        }
-    };
-    auto store_recs = [&](int b) {
-        unsigned char *rb = recs + b * kRecBuf;
-        if (wv < 2) reinterpret_cast<uint4 *>(rb)[wv * 64 + lane] = rstage;
-        else if (kBf && wv == 2) reinterpret_cast<uint4 *>(rb + kRecBytes)[lane] = rstage;
-    };
-
-    MfmaA<TS> A[UMAX];
-    // issue the coefficient loads of panel p (window start lo, width) for this wave's units: a
-    // uniform base per channel group and 32-bit byte offsets within the panel's rows
-    const uint32_t row_bytes = (uint32_t)NS * 4u * (uint32_t)sizeof(TS);
-    const int ci_max = (int)NS - 1;
-    const int ci_lane = (int)k0 + li;
-    auto load_ops = [&](int64_t p, int lo, int width) {
-        const int nu = n_units(width);
-        const unsigned char *g0 = reinterpret_cast<const unsigned char *>(coef) + (size_t)p * 2 * row_bytes;
-        const unsigned char *g1 = g0 + row_bytes;
+    static_assert(5 * OPW <= 64, "taps of a wave in one load");
+    const int tap_j = lane < 4 * OPW ? lane >> 2 : (lane < 5 * OPW ? lane - 4 * OPW : 0);
+    const int tap_s = own0 + tap_j < nobs ? own0 + tap_j : nobs - 1;
+    const uint32_t *tp = rec_block(a.rec, t, pb, P, nobs) +
+                         (lane < 4 * OPW ? kRecW * nobs + 4 * tap_s + (lane & 3) : kRecD16 * nobs + tap_s);
+    auto load_taps = [&](int64_t p, Taps &x) {
+        const_u32_t blk = (const_u32_t)rec_block(a.rec, t, p, P, nobs);
 #pragma unroll
-        for (int s = 0; s < UMAX; ++s) {
-            const int u = wv + kLdsWaves * s;
-            if (u < nu) {
-                int ci = lo + ci_lane + 16 * (u >> 1);
-                ci = ci < ci_max ? ci : ci_max;  // indices past the row are never read by valid outputs
-                if constexpr (kBf) {
-                    const uint32_t off = (uint32_t)ci * 8u;
-                    A[s].a = *reinterpret_cast<const uint2 *>(((lq & 1) ? g1 : g0) + off);
-                } else {
-                    const uint32_t off = ((uint32_t)ci * 4u + (uint32_t)lq) * 4u;
-                    A[s].a0 = *reinterpret_cast<const float *>(g0 + off);
-                    A[s].a1 = *reinterpret_cast<const float *>(g1 + off);
-                }
+        for (int j = 0; j < OPW; ++j)
+            if (FULL || j < nown) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) x.w[j][q] = __uint_as_float(blk[kRecW * nobs + 4 * (own0 + j) + q]);
+                x.d[j] = (int)blk[kRecD16 * nobs + own0 + j];
             }
+    };
+    auto unpack_taps = [&](uint32_t v, Taps &x) {
+#pragma unroll
+        for (int j = 0; j < OPW; ++j) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) x.w[j][q] = __int_as_float(__builtin_amdgcn_readlane((int)v, 4 * j + q));
+            x.d[j] = __builtin_amdgcn_readlane((int)v, 4 * OPW + j);
         }
     };
-    // matrix units of the panel whose operands are loaded: Y[16 h + li][16 (u >> 1) + 4 lq + r], the
-    // weights (B operand) of observer 16 h + li read from the record buffer: FP32 channels lq and
-    // 4 + lq; BF16 the high (lq < 2) or low parts of channel block lq & 1.  All products are issued
-    // before the first result is written.
-    const int h = wv & 1;
-    float *ybase = Y + (16 * h + li) * YR + 4 * lq;
-    auto mma_units = [&](int width, int b) {
-        const int nu = n_units(width);
-        const unsigned char *rb = recs + b * kRecBuf;
-        uint2 bb = make_uint2(0u, 0u);
-        float b0 = 0.f, b1 = 0.f;
-        if constexpr (kBf) {
-            bb = reinterpret_cast<const uint2 *>(rb + kRecBytes + (16 * h + li) * sizeof(PairBf))[lq];
-        } else {
-            const float *K = reinterpret_cast<const float *>(rb + (16 * h + li) * sizeof(PairRec));
-            b0 = K[lq];
-            b1 = K[4 + lq];
+    // operands of one panel: the blocks every panel needs, and one block past them per wave, in turn
+    struct Operands {
+        YBlock<TS> A[MW], T;
+        uintx2 Bk;
+        uint32_t taps;  // AHEAD > 1
+        int need, soff, tb;
+        __amdgpu_buffer_rsrc_t rsrc;
+    };
+    // panel p (its window in lane p - pb & 63 of wlo, wwd)
+    auto load_panel = [&](int64_t p, Operands &X) {
+        const int q = (int)((p - pb) & 63);
+        if (q == 0) load_win(p);
+        const int lo = __builtin_amdgcn_readlane(wlo, q), wd = __builtin_amdgcn_readlane(wwd, q);
+        X.need = wd + kLdsLanesOut * NSUB + kLdsHalo;
+        X.soff = (lo + (int)k0) * EB;
+        X.rsrc = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<unsigned char *>(static_cast<const unsigned char *>(a.coef)) + (size_t)p * 2 * (size_t)rowb, 0,
+            2 * rowb, 0x00020000);
+        X.Bk = *reinterpret_cast<const uintx2 *>(kp);
+        kp += nobs * (kBf ? 8 : 16);
+        if constexpr (AHEAD > 1) {
+            X.taps = *tp;
+            tp += nobs * 16;
         }
-        // two units at a time: their products are issued before either result is written
 #pragma unroll
-        for (int s = 0; s < UMAX; s += 2) {
-            const bool v0 = wv + kLdsWaves * s < nu, v1 = wv + kLdsWaves * (s + 1) < nu;
-            floatx4 d0 = {0.f, 0.f, 0.f, 0.f}, d1 = {0.f, 0.f, 0.f, 0.f};
-            if constexpr (kBf) {
-                if (v0)
-                    d0 = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(shortx4, A[s].a),
-                                                                   __builtin_bit_cast(shortx4, bb), d0, 0, 0, 0);
-                if (v1)
-                    d1 = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(shortx4, A[s + 1].a),
-                                                                   __builtin_bit_cast(shortx4, bb), d1, 0, 0, 0);
-            } else {
-                if (v0) d0 = __builtin_amdgcn_mfma_f32_16x16x4f32(A[s].a0, b0, d0, 0, 0, 0);
-                if (v1) d1 = __builtin_amdgcn_mfma_f32_16x16x4f32(A[s + 1].a0, b0, d1, 0, 0, 0);
-                if (v0) d0 = __builtin_amdgcn_mfma_f32_16x16x4f32(A[s].a1, b1, d0, 0, 0, 0);
-                if (v1) d1 = __builtin_amdgcn_mfma_f32_16x16x4f32(A[s + 1].a1, b1, d1, 0, 0, 0);
-            }
-            if (v0) *reinterpret_cast<floatx4 *>(ybase + 16 * ((wv + kLdsWaves * s) >> 1)) = d0;
-            if (v1) *reinterpret_cast<floatx4 *>(ybase + 16 * ((wv + kLdsWaves * (s + 1)) >> 1)) = d1;
+        for (int i = 0; i < MW; ++i)
+            if (kShare || (i + 1) * kYWaves <= NSUB || wv + i * kYWaves < NSUB)
+                X.A[i].load(X.rsrc, voff, X.soff + (kShare ? 0 : wv + i * kYWaves) * kYBlk * EB, rowb);
+        X.tb = kShare ? 1 : NSUB + ((wv + (int)p) & (kYWaves - 1));
+        if (YBlock<TS>::lane_index(lane) < X.need - X.tb * kYBlk)
+            X.T.load(X.rsrc, voff, X.soff + X.tb * kYBlk * EB, rowb);
+    };
+    // the units of block b (indices 64 b ..) into Y, those below `need` if `part`
+    float *const ybase = Y + li * YR + 4 * lq;
+    auto units = [&](YBlock<TS> &B, const Operands &X, int b, auto part) {
+        B.prepare();
+        unroll<0, 4>([&](auto tc) {
+            constexpr int U = decltype(tc)::value;
+            if ((!kShare || U == wv) && (!decltype(part)::value || b * kYBlk + U * 16 < X.need))
+                *reinterpret_cast<floatx4 *>(ybase + b * kYBlk + U * 16) = B.template unit<U>(X.Bk);
+        });
+    };
+    auto multiply = [&](Operands &X) {
+#pragma unroll
+        for (int i = 0; i < MW; ++i)
+            if (kShare || (i + 1) * kYWaves <= NSUB || wv + i * kYWaves < NSUB)
+                units(X.A[i], X, kShare ? 0 : wv + i * kYWaves, std::false_type{});
+        if (X.tb * kYBlk < X.need) units(X.T, X, X.tb, std::true_type{});
+        // wide windows: blocks beyond those loaded ahead
+        for (int b = kShare ? 2 : NSUB + kYWaves + wv; b * kYBlk < X.need; b += kShare ? 1 : kYWaves) {
+            YBlock<TS> B;
+            B.load(X.rsrc, voff, X.soff + b * kYBlk * EB, rowb);
+            units(B, X, b, std::true_type{});
         }
     };
-
-    float acc[kObsPerWave][kLdsSub];
+    const float *const yown = Y + own0 * YR + lane;
+    auto flush = [&](bool add, bool last) {
 #pragma unroll
-    for (int j = 0; j < kObsPerWave; ++j)
-#pragma unroll
-        for (int m = 0; m < kLdsSub; ++m) acc[j][m] = 0.f;
-
-    // the panel loop, compiled once per (observers, rows) of the wave; a wave without taps (NOBS = 0)
-    // still does its matrix units and record staging and meets every barrier
-    auto panel_loop = [&](auto nobs_c, auto nsub_c) {
-        constexpr int NOBS = decltype(nobs_c)::value;
-        constexpr int NSUB = decltype(nsub_c)::value;
-        int cnt = 0;
-        bool flushed = false;
-        int2 win = make_int2(0, 0);
-        if (pb < pe) {  // an empty split (possible when P < splits * p_chunk) loads nothing
-            load_recs(pb);
-            win = load_win(pb);
-            const int lo = __builtin_amdgcn_readlane(win.x, 0), hi = __builtin_amdgcn_readlane(win.y, 0);
-            load_ops(pb, lo, hi - lo);
-            store_recs(0);
-            lds_barrier();
-        }
-        for (int64_t p = pb; p < pe; ++p) {
-            const int q = (int)((p - pb) & 63), b = (int)((p - pb) & 1);
-            const int lo = __builtin_amdgcn_readlane(win.x, q), hi = __builtin_amdgcn_readlane(win.y, q);
-            mma_units(hi - lo, b);
-            // next panel's records, window and operands, in flight during the taps
-            const bool more = p + 1 < pe;
-            if (more) {
-                load_recs(p + 1);
-                if (q == 63) win = load_win(p + 1);
-                const int q1 = (int)((p + 1 - pb) & 63);
-                const int lo1 = __builtin_amdgcn_readlane(win.x, q1), hi1 = __builtin_amdgcn_readlane(win.y, q1);
-                load_ops(p + 1, lo1, hi1 - lo1);
-            }
-            lds_barrier();
-            // taps, weights and delay indices of this wave's observers from the record buffer
-            const unsigned char *rb = recs + b * kRecBuf;
-#pragma unroll
-            for (int j = 0; j < NOBS; ++j) {
-                const unsigned char *r = rb + (j * kLdsWaves + wv) * sizeof(PairRec);
-                const float4 W = *reinterpret_cast<const float4 *>(r + 32);
-                const int d = *reinterpret_cast<const int *>(r + 48) - lo;
-                const float *y = Y + (j * kLdsWaves + wv) * YR + d + lane;
+        for (int j = 0; j < OPW; ++j) {
+            if (FULL || j < nown) {
+                const int64_t o = tbase + own0 + j;
+                float *row = a.partial + (z * O + o) * nt_max;
+                const int ntl = last ? a.nt[o] : 0;
 #pragma unroll
                 for (int m = 0; m < NSUB; ++m) {
-                    const float g = y[m * kLdsLanesOut];
-                    const float g1 = next_lane(g);
-                    const float g2 = next_lane(g1);
-                    const float g3 = next_lane(g2);
-                    float ac = acc[j][m];
-                    ac = fmaf(W.x, g, ac);
-                    ac = fmaf(W.y, g1, ac);
-                    ac = fmaf(W.z, g2, ac);
-                    ac = fmaf(W.w, g3, ac);
-                    acc[j][m] = ac;
+                    const float v = acc[j][m][0] + next_lane(next_lane(acc[j][m][1]));
+                    const int64_t k = k0 + m * kLdsLanesOut + lane;
+                    if (lane < kLdsLanesOut && k < nt_max) {
+                        const float s = (add ? row[k] : 0.f) + v;
+                        row[k] = !last || k < ntl ? s : 0.f;
+                    }
+                    acc[j][m][0] = acc[j][m][1] = 0.f;
                 }
             }
-            if (more) store_recs(b ^ 1);
-            lds_barrier();
-            if (++cnt == kMfmaChunk) {
+        }
+    };
+
+    int cnt = 0;
+    bool flushed = false;
+    Taps now;
+    Operands X[AHEAD];
 #pragma unroll
-                for (int j = 0; j < NOBS; ++j) {
-                    float *row = out_row(j);
+    for (int i = 0; i < AHEAD; ++i)
+        if (pb + i < pe) load_panel(pb + i, X[i]);
+    for (int64_t ps = pb; ps < pe; ps += AHEAD) {
+#pragma unroll
+        for (int i = 0; i < AHEAD; ++i) {
+            const int64_t p = ps + i;
+            if (p >= pe) break;
+            if constexpr (AHEAD > 1) unpack_taps(X[i].taps, now);
+            else load_taps(p, now);
+            lds_barrier();  // every wave has read the previous panel's Y (and, first time round, another item's)
+            multiply(X[i]);
+            if (p + AHEAD < pe) load_panel(p + AHEAD, X[i]);
+            lds_barrier();
+#pragma unroll
+            for (int j = 0; j < OPW; ++j) {
+                if (FULL || j < nown) {
+                    const float *y = yown + j * YR + now.d[j];
+                    float g[NSUB];
+#pragma unroll
+                    for (int m = 0; m < NSUB; ++m) g[m] = y[m * kLdsLanesOut];
 #pragma unroll
                     for (int m = 0; m < NSUB; ++m) {
-                        const int k = k_lane + m * kLdsLanesOut;
-                        if (lane_out && k < nt_max) row[k] = (flushed ? row[k] : 0.f) + acc[j][m];
-                        acc[j][m] = 0.f;
+                        acc[j][m][0] = fmaf(now.w[j][0], g[m], acc[j][m][0]);
+                        acc[j][m][1] = fmaf(now.w[j][2], g[m], acc[j][m][1]);
                     }
+                    taps_next<NSUB>(acc[j], g, now.w[j][1], now.w[j][3]);
                 }
+            }
+            if (++cnt == kYChunk) {
+                flush(flushed, false);
                 flushed = true;
                 cnt = 0;
             }
         }
-        // final sums; outputs past an observer's window are zero (only this block's `rows` rows: the
-        // next ones belong to the next k block)
-#pragma unroll
-        for (int j = 0; j < kObsPerWave; ++j) {
-            if (tbase + j * kLdsWaves + wv >= O) continue;
-            const int ntl = nt[tbase + j * kLdsWaves + wv];
-            float *row = out_row(j);
-#pragma unroll
-            for (int m = 0; m < kLdsSub; ++m) {
-                const int k = k_lane + m * kLdsLanesOut;
-                if (m < rows && lane_out && k < nt_max) {
-                    const float prev = (j < NOBS && m < NSUB && flushed) ? row[k] : 0.f;
-                    row[k] = k < ntl ? prev + acc[j][m] : 0.f;
-                }
-            }
-        }
-    };
-    auto by_sub = [&](auto nobs_c) {
-        switch (nsub) {
-            case 1: panel_loop(nobs_c, std::integral_constant<int, 1>{}); break;
-            case 2: panel_loop(nobs_c, std::integral_constant<int, 2>{}); break;
-            case 3: panel_loop(nobs_c, std::integral_constant<int, 3>{}); break;
-            default: panel_loop(nobs_c, std::integral_constant<int, kLdsSub>{}); break;
-        }
-    };
-    if (nsub_blk == 0) {
-        // no sample of this block lies in a window of the tile: zeros (every wave, no barrier)
-#pragma unroll
-        for (int j = 0; j < kObsPerWave; ++j) {
-            if (tbase + j * kLdsWaves + wv >= O) continue;
-            float *row = out_row(j);
-#pragma unroll
-            for (int m = 0; m < kLdsSub; ++m) {
-                const int k = k_lane + m * kLdsLanesOut;
-                if (m < rows && lane_out && k < nt_max) row[k] = 0.f;
-            }
-        }
-        return;
     }
-    if (nobs == 0 || nsub == 0) {
-        panel_loop(std::integral_constant<int, 0>{}, std::integral_constant<int, 0>{});
+    flush(flushed, true);
+}
+
+template <typename TS, int AHEAD>
+__device__ __forceinline__ void gather_y_body(const GatherArgs &a, int64_t t, int64_t kb, int64_t z,
+                                              float *__restrict__ Y) {
+    const int64_t tbase = t * kYTile, k0 = kb * kLdsLanesOut * a.rows;
+    const int nobs = (int)(a.O - tbase < kYTile ? a.O - tbase : kYTile);
+    int nt_tile = 0;
+    for (int j = 0; j < nobs; ++j) {
+        const int n = a.nt[tbase + j];
+        nt_tile = n > nt_tile ? n : nt_tile;
+    }
+    int nsub = (int)((nt_tile - k0 + kLdsLanesOut - 1) / kLdsLanesOut);
+    nsub = __builtin_amdgcn_readfirstlane(nsub < 0 ? 0 : (nsub > a.rows ? a.rows : nsub));
+    // rows past the tile's windows, of the block's `rows` rows, are zero
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    for (int m = nsub; m < a.rows; ++m)
+        for (int j = wv; j < nobs; j += kYWaves) {
+            const int64_t k = k0 + m * kLdsLanesOut + lane;
+            if (lane < kLdsLanesOut && k < a.nt_max) a.partial[(z * a.O + tbase + j) * a.nt_max + k] = 0.f;
+        }
+    if (nobs == kYTile) {
+        switch (nsub) {
+            case 0: break;
+            case 1: gather_y_panels<TS, 1, true, AHEAD>(a, t, nobs, k0, z, Y); break;
+            case 2: gather_y_panels<TS, 2, true, AHEAD>(a, t, nobs, k0, z, Y); break;
+            case 3: gather_y_panels<TS, 3, true, AHEAD>(a, t, nobs, k0, z, Y); break;
+            default: gather_y_panels<TS, 4, true, AHEAD>(a, t, nobs, k0, z, Y); break;
+        }
     } else {
-        switch (nobs) {
-            case 1: by_sub(std::integral_constant<int, 1>{}); break;
-            case 2: by_sub(std::integral_constant<int, 2>{}); break;
-            default: by_sub(std::integral_constant<int, kObsPerWave>{}); break;
+        switch (nsub) {
+            case 0: break;
+            case 1: gather_y_panels<TS, 1, false, AHEAD>(a, t, nobs, k0, z, Y); break;
+            case 2: gather_y_panels<TS, 2, false, AHEAD>(a, t, nobs, k0, z, Y); break;
+            case 3: gather_y_panels<TS, 3, false, AHEAD>(a, t, nobs, k0, z, Y); break;
+            default: gather_y_panels<TS, 4, false, AHEAD>(a, t, nobs, k0, z, Y); break;
         }
     }
 }
 
-// four waves per SIMD (two blocks per compute unit): at most 128 VGPRs, a few of them spilled
-template <typename TS, int UMAX>
-__global__ __launch_bounds__(kLdsWaves * 64) __attribute__((amdgpu_waves_per_eu(4))) void gather_mfma_kernel(
-    GatherArgs a, int64_t tiles, int64_t kblocks) {
+// Waves per SIMD the registers are held to, for operands loaded AHEAD panels ahead.
+template <typename TS, int AHEAD>
+constexpr int y_waves_per_eu() {
+    constexpr bool f32 = std::is_same<TS, float>::value;
+    return AHEAD == 1 ? (f32 ? 5 : 6) : AHEAD == 2 ? (f32 ? 4 : 5) : (f32 ? 3 : 4);
+}
+template <typename TS, int AHEAD>
+__global__ __launch_bounds__(kYWaves * 64) __attribute__((amdgpu_waves_per_eu(y_waves_per_eu<TS, AHEAD>())))
+void gather_y_kernel(GatherArgs a, int64_t tiles, int64_t kblocks) {
     extern __shared__ __align__(16) float ysm[];
     // 1-D grid, block order (tile fastest, k block, split) regrouped per XCD
     const int64_t L = xcd_block(blockIdx.x, gridDim.x);
     const int64_t t = L % tiles, rest = L / tiles;
-    gather_mfma_body<TS, UMAX>(a, t, rest % kblocks, rest / kblocks, ysm);
+    gather_y_body<TS, AHEAD>(a, t, rest % kblocks, rest / kblocks, ysm);
 }
 
 // Persistent batched form: blocks pull work items (case, tile, k block, split) in
@@ -365,11 +407,10 @@ __global__ __launch_bounds__(kLdsWaves * 64) __attribute__((amdgpu_waves_per_eu(
 // exhausted; each item runs the body above on its case's arguments.  The Y tile
 // is reused from item to item (the loop-top barrier orders the last reads of one
 // item before the first writes of the next).
-template <typename TS, int UMAX>
-__global__ __launch_bounds__(kLdsWaves * 64) __attribute__((amdgpu_waves_per_eu(4))) void gather_mfma_persistent(
-    const BatchCase *__restrict__ cases,
-                                                                         const int4 *__restrict__ items, int n_items,
-                                                                         int *__restrict__ counter) {
+template <typename TS, int AHEAD>
+__global__ __launch_bounds__(kYWaves * 64) __attribute__((amdgpu_waves_per_eu(y_waves_per_eu<TS, AHEAD>())))
+void gather_y_persistent(const BatchCase *__restrict__ cases, const int4 *__restrict__ items, int n_items,
+                         int *__restrict__ counter) {
     extern __shared__ __align__(16) float ysm[];
     __shared__ int cur;
     for (;;) {
@@ -380,99 +421,62 @@ __global__ __launch_bounds__(kLdsWaves * 64) __attribute__((amdgpu_waves_per_eu(
         if (it >= n_items) break;
         const int4 w = items[it];
         const int c = __builtin_amdgcn_readfirstlane(w.x);
-        gather_mfma_body<TS, UMAX>(cases[c].gat, __builtin_amdgcn_readfirstlane(w.y),
-                                   __builtin_amdgcn_readfirstlane(w.z), __builtin_amdgcn_readfirstlane(w.w), ysm);
+        gather_y_body<TS, AHEAD>(cases[c].gat, __builtin_amdgcn_readfirstlane(w.y), __builtin_amdgcn_readfirstlane(w.z),
+                                 __builtin_amdgcn_readfirstlane(w.w), ysm);
     }
 }
 
-template <typename TS, int UMAX>
-const void *persistent_ptr() {
-    return reinterpret_cast<const void *>(&gather_mfma_persistent<TS, UMAX>);
-}
-
-template <typename TS, int UMAX>
-const void *mfma_kernel_ptr() {
-    return reinterpret_cast<const void *>(&gather_mfma_kernel<TS, UMAX>);
-}
+constexpr int kYAheadFull = 1, kYAheadFew = 4, kYAheadBatch = 2;
 
 }  // namespace
 
-int gather_mfma_umax(int wmax) {
-    const int nu = 2 * ((wmax + kLdsK + kLdsHalo + 15) / 16);
-    const int per_wave = (nu + kLdsWaves - 1) / kLdsWaves;
-    return per_wave <= 4 ? 4 : (per_wave <= 6 ? 6 : (per_wave <= 8 ? 8 : 0));
-}
-
-int gather_mfma_blocks_per_cu(int coef_type, int wmax) {
-    const int umax = gather_mfma_umax(wmax);
-    if (umax == 0) return 0;
-    const size_t shmem = gather_mfma_shmem(wmax);
-    const void *k = nullptr;
-    if (coef_type == 1) k = umax == 4 ? mfma_kernel_ptr<float, 4>() : umax == 6 ? mfma_kernel_ptr<float, 6>()
-                                                                               : mfma_kernel_ptr<float, 8>();
-    else k = umax == 4 ? mfma_kernel_ptr<uint16_t, 4>() : umax == 6 ? mfma_kernel_ptr<uint16_t, 6>()
-                                                                    : mfma_kernel_ptr<uint16_t, 8>();
+template <typename TS, int AHEAD>
+static int y_blocks_per_cu(size_t shmem) {
     int n = 0;
-    const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k, kLdsWaves * 64, shmem);
+    const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
+        &n, reinterpret_cast<const void *>(&gather_y_kernel<TS, AHEAD>), kYWaves * 64, shmem);
     return e == hipSuccess && n > 0 ? n : 0;
 }
 
-hipError_t launch_gather_mfma(int coef_type, const PairRec *rec_op, const PairBf *rbf, const int2 *tw,
-                              const int32_t *nt, const void *coef, int64_t P, int64_t O, int64_t NS, int64_t nt_max,
-                              int splits, int wmax, float *partial, hipStream_t stream) {
-    const int64_t p_chunk = (P + splits - 1) / splits;
-    const int YR = gather_mfma_y_row(wmax);
-    const GatherArgs a{rec_op, rbf, tw, nt, coef, P, O, NS, nt_max, p_chunk, YR, 0, splits, partial, kLdsSub};
-    const int64_t tiles = (O + kObsTile - 1) / kObsTile, kblocks = (nt_max + kLdsK - 1) / kLdsK;
-    const dim3 n1((unsigned)(tiles * kblocks * splits));
-    const size_t shmem = gather_mfma_shmem(wmax);
-    const int umax = gather_mfma_umax(wmax);
-    const dim3 blk(kLdsWaves * 64);
+int gather_mfma_blocks_per_cu(int coef_type, int w16, bool few) {
+    const size_t shmem = gather_mfma_shmem(w16);
+    if (shmem > kYShmemMax) return 0;
+    if (few)
+        return coef_type == 1 ? y_blocks_per_cu<float, kYAheadFew>(shmem) : y_blocks_per_cu<uint16_t, kYAheadFew>(shmem);
+    return coef_type == 1 ? y_blocks_per_cu<float, kYAheadFull>(shmem) : y_blocks_per_cu<uint16_t, kYAheadFull>(shmem);
+}
+
+hipError_t launch_gather_mfma(int coef_type, const PairRec *rec_op, const PairBf *rbf, const int32_t *nt,
+                              const void *coef, int64_t P, int64_t O, int64_t NS, int64_t nt_max, int splits, int w16,
+                              int64_t few_blocks, float *partial, hipStream_t stream) {
+    const int64_t p_chunk = (P + splits - 1) / splits, tiles = (O + kYTile - 1) / kYTile;
+    // rows of 61 samples per block: 4, fewer where all blocks still fit the device at once (a short launch
+    // lasts as long as one block's chain of panels, and a panel's product and taps are shorter with fewer rows)
+    int rows = kLdsSub;
+    auto blocks = [&](int r) { return tiles * ((nt_max + kLdsLanesOut * r - 1) / (kLdsLanesOut * r)) * splits; };
+    while (rows > 1 && blocks(rows / 2) <= few_blocks) rows /= 2;
+    const int64_t kblocks = (nt_max + kLdsLanesOut * rows - 1) / (kLdsLanesOut * rows);
+    const GatherArgs a{rec_op, rbf, nullptr, nt, coef, P, O, NS, nt_max, p_chunk, gather_mfma_y_row(w16), 0, splits,
+                       partial, rows};
+    const dim3 n1((unsigned)(tiles * kblocks * splits)), blk(kYWaves * 64);
+    const size_t shmem = gather_mfma_shmem(w16);
+    const bool few = blocks(rows) <= few_blocks;
     if (coef_type == 1) {
-        if (umax == 4) gather_mfma_kernel<float, 4><<<n1, blk, shmem, stream>>>(a, tiles, kblocks);
-        else if (umax == 6) gather_mfma_kernel<float, 6><<<n1, blk, shmem, stream>>>(a, tiles, kblocks);
-        else if (umax == 8) gather_mfma_kernel<float, 8><<<n1, blk, shmem, stream>>>(a, tiles, kblocks);
-        else return hipErrorInvalidValue;
+        if (few) gather_y_kernel<float, kYAheadFew><<<n1, blk, shmem, stream>>>(a, tiles, kblocks);
+        else gather_y_kernel<float, kYAheadFull><<<n1, blk, shmem, stream>>>(a, tiles, kblocks);
     } else {
-        if (umax == 4) gather_mfma_kernel<uint16_t, 4><<<n1, blk, shmem, stream>>>(a, tiles, kblocks);
-        else if (umax == 6) gather_mfma_kernel<uint16_t, 6><<<n1, blk, shmem, stream>>>(a, tiles, kblocks);
-        else if (umax == 8) gather_mfma_kernel<uint16_t, 8><<<n1, blk, shmem, stream>>>(a, tiles, kblocks);
-        else return hipErrorInvalidValue;
+        if (few) gather_y_kernel<uint16_t, kYAheadFew><<<n1, blk, shmem, stream>>>(a, tiles, kblocks);
+        else gather_y_kernel<uint16_t, kYAheadFull><<<n1, blk, shmem, stream>>>(a, tiles, kblocks);
     }
     return hipGetLastError();
 }
 
-}  // namespace fwh
-
-namespace fwh {
-
-int gather_mfma_persistent_blocks_per_cu(int coef_type, int umax, size_t shmem) {
-    const void *k = nullptr;
-    if (coef_type == 1) k = umax == 4 ? persistent_ptr<float, 4>() : umax == 6 ? persistent_ptr<float, 6>()
-                                                                              : persistent_ptr<float, 8>();
-    else k = umax == 4 ? persistent_ptr<uint16_t, 4>() : umax == 6 ? persistent_ptr<uint16_t, 6>()
-                                                                   : persistent_ptr<uint16_t, 8>();
-    int n = 0;
-    const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k, kLdsWaves * 64, shmem);
-    return e == hipSuccess && n > 0 ? n : 0;
-}
-
-hipError_t launch_gather_mfma_persistent(int coef_type, int umax, const BatchCase *cases, const int4 *items,
-                                         int n_items, int *counter, int grid, size_t shmem, hipStream_t stream) {
-    const dim3 g((unsigned)grid), blk(kLdsWaves * 64);
-    if (coef_type == 1) {
-        if (umax == 4) gather_mfma_persistent<float, 4><<<g, blk, shmem, stream>>>(cases, items, n_items, counter);
-        else if (umax == 6) gather_mfma_persistent<float, 6><<<g, blk, shmem, stream>>>(cases, items, n_items, counter);
-        else if (umax == 8) gather_mfma_persistent<float, 8><<<g, blk, shmem, stream>>>(cases, items, n_items, counter);
-        else return hipErrorInvalidValue;
-    } else {
-        if (umax == 4) gather_mfma_persistent<uint16_t, 4><<<g, blk, shmem, stream>>>(cases, items, n_items, counter);
-        else if (umax == 6)
-            gather_mfma_persistent<uint16_t, 6><<<g, blk, shmem, stream>>>(cases, items, n_items, counter);
-        else if (umax == 8)
-            gather_mfma_persistent<uint16_t, 8><<<g, blk, shmem, stream>>>(cases, items, n_items, counter);
-        else return hipErrorInvalidValue;
-    }
+hipError_t launch_gather_mfma_persistent(int coef_type, const BatchCase *cases, const int4 *items, int n_items,
+                                         int *counter, int grid, size_t shmem, hipStream_t stream) {
+    const dim3 g((unsigned)grid), blk(kYWaves * 64);
+    if (coef_type == 1)
+        gather_y_persistent<float, kYAheadBatch><<<g, blk, shmem, stream>>>(cases, items, n_items, counter);
+    else gather_y_persistent<uint16_t, kYAheadBatch><<<g, blk, shmem, stream>>>(cases, items, n_items, counter);
     return hipGetLastError();
 }
 

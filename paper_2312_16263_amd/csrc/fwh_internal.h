@@ -10,30 +10,49 @@ namespace fwh {
 
 constexpr int kChannels = 8;  // [Qdot, Q, Ldot_1, Ldot_2, Ldot_3, L_1, L_2, L_3]
 
-// One (observer, panel) pair of the FP32 gather: integrand weights of the 8
-// source channels (dS/(4 pi) included), the four cubic B-spline taps of the
-// fixed fractional delay and the integer part of the delay index.  64 bytes, so
-// a wave fetches a record with one scalar load.
+// Pair tables of the FP32/BF16 forms: per (observer, panel) pair 16 dwords -- the integrand weights of
+// the 8 source channels (dS/(4 pi) included), the four cubic B-spline taps of the fixed fractional
+// delay, the integer part n0 of the delay index, n0w, d16 and w16 (below).  Observers go in tiles of
+// kYTile; the pairs of tile t (c observers, c < kYTile only in a last tile) with panel p form one block
+// of 16 c consecutive dwords, in it, for observer slot s, at dword
+//   8 s + 2 q + e: K_{q + 4 e} (q = 0 .. 3, e = 0, 1); 8 c + 4 s + j: tap w_j; 12 c + s: n0;
+//   13 c + s: n0w; 14 c + s: d16; 15 c + s: w16
+// so that the 16 observers' values lie together: the matrix-core kernels take an operand with one load
+// over a few cache lines (of [O][P] records of 64 bytes each lane touched a line of its own, and the
+// texture addresser was the limit), and the LDS-staged gather copies a panel's block as it is.
 struct alignas(64) PairRec {
-    float K[8];
-    float w[4];
-    int32_t n0;
-    // byte offset of the pair's element n0 in its panel's staged window of the LDS-staged gather:
-    // (n0 - lo) x 16 (FP32) or x 8 (BF16), lo = min n0 over the pair's 32-observer tile
-    int32_t n0w;
-    int32_t pad[2];
+    uint32_t dw[16];
 };
-static_assert(sizeof(PairRec) == 64, "PairRec must be 64 bytes");
+static_assert(sizeof(PairRec) == 64, "16 dwords per pair");
+constexpr int kYTile = 16;
+// n0w: byte offset of the pair's element n0 in its panel's staged window of the LDS-staged gather:
+// (n0 - lo) x 16 (FP32) or x 8 (BF16), lo = min n0 over the pair's 32-observer tile.  d16 = n0 - lo16,
+// w16 = hi16 - lo16 (lo16, hi16: min and max n0 over the pair's 16-observer tile).
+constexpr int kRecW = 8, kRecN0w = 12, kRecN0 = 13, kRecD16 = 14, kRecW16 = 15;
+__host__ __device__ __forceinline__ int rec_tile_obs(int64_t t, int64_t O) {
+    return (int)(O - t * kYTile < kYTile ? O - t * kYTile : kYTile);
+}
+// block of (tile t, panel p)
+__host__ __device__ __forceinline__ const uint32_t *rec_block(const PairRec *rec, int64_t t, int64_t p, int64_t P, int c) {
+    return reinterpret_cast<const uint32_t *>(rec + t * kYTile * P + p * c);
+}
+// dword of slot s's field f (0 .. 7: K_f, 8 .. 11: w_{f - 8}, then n0w, n0, d16, w16) within its block; the
+// n0w row starts on 16 bytes for every c
+__host__ __device__ __forceinline__ int rec_dword(int f, int s, int c) {
+    return f < kRecW ? 8 * s + 2 * (f & 3) + (f >> 2) : f < kRecN0w ? kRecW * c + 4 * s + (f - kRecW) : f * c + s;
+}
 
-// BF16 mode: the 8 weights K_c of a pair as bfloat16 high and low parts
-// (K ~ hi + lo to 2^-17 relative), channels (2i, 2i + 1) in word i (even channel
-// in the low half), for the packed bf16 dot products of the forward gather.
+// BF16 mode: the 8 weights K_c of a pair as bfloat16 high and low parts (K ~ hi + lo to 2^-17
+// relative), channels (2i, 2i + 1) in one word (even channel in the low half), for the packed bf16
+// products of the forward gathers: words hi[0..3], lo[0..3] of slot s from word 8 s of the block of
+// (tile t, panel p), 8 c words.
 struct alignas(32) PairBf {
-    uint32_t hi[4];
-    uint32_t lo[4];
+    uint32_t w[8];
 };
 static_assert(sizeof(PairBf) == 32, "PairBf must be 32 bytes");
-
+__host__ __device__ __forceinline__ const uint32_t *rbf_block(const PairBf *rbf, int64_t t, int64_t p, int64_t P, int c) {
+    return reinterpret_cast<const uint32_t *>(rbf + t * kYTile * P + p * c);
+}
 // Geometry and flow constants passed by value to kernels.
 struct Flow {
     double M0, ca, sa, beta2, dtau, tau0;
@@ -94,7 +113,7 @@ struct SrcFwdArgs {
 
 struct GatherArgs {
     const PairRec *rec;
-    const PairBf *rbf;  // BF16 mode: [O][P] split weights (null in FP32 mode)
+    const PairBf *rbf;  // BF16 mode: split weights (null in FP32 mode)
     const int2 *tw;
     const int32_t *nt;
     const void *coef;
@@ -119,11 +138,11 @@ struct PadArgs {
 };
 
 struct AdjArgs {
-    const PairRec *rec;  // [O][P]
+    const PairRec *rec;
+    const int32_t *nt;
     const float *gpad;
-    int64_t P, O, NS, LR, padlo, nib;
+    int64_t P, O, N, NS, LR, padlo, nib;
     float *cbar;
-    int64_t nt_max;  // longest observer window (bounds the indices an observer's gradient reaches)
     // every observer's gradient reaches every index in [edge_lo, edge_hi] (N - shortest window, and
     // shortest window + 2): index blocks inside need no check for blocks that get only zeros
     int64_t edge_lo, edge_hi;
@@ -189,7 +208,7 @@ struct BatchIndex {
 hipError_t launch_delay(const double *y, const double *x_obs, int64_t P, int64_t O, Flow f, double *D,
                         hipStream_t stream);
 hipError_t launch_minmax(const double *D, int64_t P, int64_t O, double *dmm, hipStream_t stream);
-// mode 0: FP64 tables (K64 [O][P][8], W64 [O][P][4], N0 [O][P]); mode 1/2: PairRec [O][P] (and
+// mode 0: FP64 tables (8, 4 doubles and an index per pair; layout in fwh_f64.hip); mode 1/2: the pair tables (and
 // rbf, if not null), plus per (observer tile t, panel p) the lo/hi of n0 over the tile's observers
 // -> tw[t][p], and per block of tile_window_panels() panels of one tile the largest hi - lo ->
 // wblk[block] (tile_window_blocks(P, O) blocks, tile-major).
@@ -241,15 +260,32 @@ __host__ __device__ inline int64_t adj_chunks(int64_t N) { return (N + kSrcTC - 
 
 // Source terms + derivatives + natural-spline prefilter -> coefficients [P][2][NS][4]
 // (channel c = 4 g + cc at ((p*2 + g)*NS + i)*4 + cc).
-// in_dtype 0 = double, 1 = float; coef_type 0 = double, 1 = float, 2 = bf16; scratch is
-// [8][N][P] of double (coef_type 0) or float (otherwise).
+// in_dtype 0 = double, 1 = float; coef_type 1 = float, 2 = bf16.
 hipError_t launch_source(int in_dtype, int coef_type, const void *rho, const void *u, const void *pp,
-                         const double *normal, int64_t P, int64_t N, int64_t NS, Flow f, const double *cp,
-                         void *scratch, void *coef, hipStream_t stream);
+                         const double *normal, int64_t P, int64_t N, int64_t NS, Flow f, const double *cp, void *coef,
+                         hipStream_t stream);
 
-hipError_t launch_gather_f64(const double *K64, const double *W64, const int32_t *N0, const int32_t *nt,
-                             const double *coef, int64_t P, int64_t O, int64_t NS, int64_t nt_max, double *out,
-                             hipStream_t stream);
+// Plain FP64 form (fwh_f64.hip).  scratch: [8][N][P] doubles.
+hipError_t launch_source64(int in_dtype, const void *rho, const void *u, const void *pp, const double *normal, int64_t P,
+                           int64_t N, int64_t NS, Flow f, const double *cp, void *scratch, void *coef,
+                           hipStream_t stream);
+// coefficient adjoints cbar [8][P][NS] (overwritten) -> gradients (time-major, in_dtype)
+hipError_t launch_source_adjoint64(int in_dtype, void *cbar, const void *rho, const void *u, const double *normal,
+                                   int64_t P, int64_t N, int64_t NS, Flow f, const double *cp, void *scratch, void *g_rho,
+                                   void *g_u, void *g_p, hipStream_t stream);
+// *width (zeroed by the caller) = widest spread of n0 over a tile of kYTile observers
+hipError_t launch_spread64(const int32_t *N0, int64_t P, int64_t O, int *width, hipStream_t stream);
+// resident blocks per CU of the tiled gather; 0: windows too wide for it (one launch over all panels)
+int gather64_blocks_per_cu(int w16);
+// splits > 1: panel ranges summed separately into partial [splits][O][nt_max] doubles, then added
+hipError_t launch_gather64(const double *K64, const double *W64, const int32_t *N0, const int32_t *nt,
+                           const double *coef, int64_t P, int64_t O, int64_t NS, int64_t nt_max, int w16, int splits,
+                           double *partial, double *out, hipStream_t stream);
+// pad (pad_bytes): room for a zero-padded copy of gbar, O x adj_pad_row(N, NS) doubles (else a slower form)
+hipError_t launch_adj_gather64(const double *K64, const double *W64, const int32_t *N0, const int32_t *nt,
+                               const double *gbar, int64_t P, int64_t O, int64_t N, int64_t NS, int64_t nt_max,
+                               double *pad, size_t pad_bytes, double *cbar, hipStream_t stream);
+
 // coef_type 1 = float, 2 = bf16.  partial: [splits][O][nt_max] floats.
 hipError_t launch_gather_tuned(int coef_type, const PairRec *rec_op, const int32_t *nt, const void *coef, int64_t P,
                                int64_t O, int64_t NS, int64_t nt_max, int splits, float *partial,
@@ -278,26 +314,26 @@ hipError_t launch_gather_lds(int coef_type, const PairRec *rec_op, const PairBf 
                              const void *coef, int64_t P, int64_t O, int64_t NS, int64_t nt_max, int splits, int NW,
                              int PT, float *partial, hipStream_t stream, int64_t t0 = 0, int64_t t1 = -1,
                              int shape = 0);
-// Matrix-core gather (fwh_gather_mfma.hip): per panel a Y tile [kObsTile][YR] floats in LDS covering
-// the window of the widest tile (wmax = largest n0 spread over a tile's observers).
-inline int gather_mfma_y_row(int wmax) { return ((wmax + kLdsK + kLdsHalo + 15) / 16) * 16 + 4; }
-// Y tile, then two record buffers of the tile (pair records and, in BF16, split weights)
-inline size_t gather_mfma_shmem(int wmax) {
-    return (size_t)kObsTile * gather_mfma_y_row(wmax) * sizeof(float) + 2 * (size_t)kObsTile * (sizeof(PairRec) + sizeof(PairBf));
-}
-// matrix units per wave and panel the kernel is compiled for (4, 6 or 8; 0: windows too wide)
-int gather_mfma_umax(int wmax);
-// resident blocks per CU (0 when the kernel does not apply)
-int gather_mfma_blocks_per_cu(int coef_type, int wmax);
-hipError_t launch_gather_mfma(int coef_type, const PairRec *rec_op, const PairBf *rbf, const int2 *tw,
-                              const int32_t *nt, const void *coef, int64_t P, int64_t O, int64_t NS, int64_t nt_max,
-                              int splits, int wmax, float *partial, hipStream_t stream);
+// Matrix-core gather (fwh_gather_mfma.hip): blocks of kYWaves waves on tiles of kYTile observers; per
+// panel a Y tile [kYTile][row] floats in LDS covering the widest window (w16: largest n0 spread
+// over a tile's observers).  Rows are a multiple of 16 plus 4 floats: the 16-byte writes of 16
+// neighbouring observers then fall into different banks.
+constexpr int kYWaves = 4;
+constexpr size_t kYShmemMax = 72 * 1024;  // LDS bytes of a block, at most
+inline int gather_mfma_y_row(int w16) { return ((w16 + kLdsK + kLdsHalo + 15) / 16) * 16 + 4; }
+inline size_t gather_mfma_shmem(int w16) { return (size_t)kYTile * gather_mfma_y_row(w16) * sizeof(float); }
+// resident blocks per CU (0 when the windows are too wide for it); few: of the form for launches that
+// leave blocks' room unused, which loads its operands further ahead in more registers
+int gather_mfma_blocks_per_cu(int coef_type, int w16, bool few);
+// few_blocks: blocks up to which that form runs
+hipError_t launch_gather_mfma(int coef_type, const PairRec *rec_op, const PairBf *rbf, const int32_t *nt,
+                              const void *coef, int64_t P, int64_t O, int64_t NS, int64_t nt_max, int splits, int w16,
+                              int64_t few_blocks, float *partial, hipStream_t stream);
 // Persistent batched form: `grid` blocks pull (case, tile, k block, split) items through counter[0]
 // (reset by the caller's stream order); every case's GatherArgs carries its Y row length in NW and
-// its rows per block; umax as for the widest case, shmem its Y tile.
-int gather_mfma_persistent_blocks_per_cu(int coef_type, int umax, size_t shmem);
-hipError_t launch_gather_mfma_persistent(int coef_type, int umax, const BatchCase *cases, const int4 *items,
-                                         int n_items, int *counter, int grid, size_t shmem, hipStream_t stream);
+// its rows per block; shmem: the largest Y tile of the cases.
+hipError_t launch_gather_mfma_persistent(int coef_type, const BatchCase *cases, const int4 *items, int n_items,
+                                         int *counter, int grid, size_t shmem, hipStream_t stream);
 // Streaming gather for O <= kLdsWaves observers: whole coefficient rows of each panel staged in LDS
 // (two buffers), two waves per observer, every sample in registers (rows of 61, up to 32 rows).
 // Grid: one block per panel split.  0 blocks per CU when it does not apply (rows or LDS).
@@ -310,27 +346,27 @@ hipError_t launch_gather_stream(int coef_type, const PairRec *rec_op, const Pair
 // out[i] = sum over splits of partial[z][i], in FP64 and fixed order, rounded to float.
 hipError_t launch_reduce_splits(const float *partial, int splits, int64_t total, float *out, hipStream_t stream);
 
-hipError_t launch_adj_gather_f64(const double *K64, const double *W64, const int32_t *N0, const int32_t *nt,
-                                 const double *gbar, int64_t P, int64_t O, int64_t NS, int64_t nt_max, double *cbar,
-                                 hipStream_t stream);
 // Transposed gather via a zero-padded copy of gbar (gpad: [O][adj_pad_row(N, NS)] floats).
 inline int64_t adj_pad_lo(int64_t N) { return N + 4; }
-// blocks of 64 coefficient indices per wave of the transposed gather; a gpad row covers every
-// position it reads (from -n0 - 4 to NS - 1 - n0 past padlo, n0 < N)
-constexpr int kAdjMW = 5;
+// A wave of the transposed gather owns kAdjMW blocks of kAdjIdx coefficient indices (lane l: indices
+// 4 l - 4 .. 4 l - 1 of a block; lane 0 only supplies the values below lane 1's); a gpad row covers every
+// position it reads: from -n0 - 4 to N + 253 - n0 past padlo, n0 < N (a wave's second block is read only
+// if it starts below N + 2).
+constexpr int kAdjMW = 2;
+constexpr int kAdjIdx = 252;
 constexpr int kAdjPT = 64;  // panels per tile of the transposed gather's wave order
-inline int64_t adj_blocks(int64_t NS) { return (NS + 64 * kAdjMW - 1) / (64 * kAdjMW); }
-inline int64_t adj_pad_row(int64_t N, int64_t NS) { return ((N + NS + 8 + 64 * (kAdjMW + 1) + 63) / 64) * 64; }
+// waves per panel: the indices 0 .. N + 1
+inline int64_t adj_blocks(int64_t N) { return (N + 2 + kAdjMW * kAdjIdx - 1) / (kAdjMW * kAdjIdx); }
+inline int64_t adj_pad_row(int64_t N, int64_t NS) { return ((N + NS + 8 + 64 * 6 + 63) / 64) * 64; }
 // nt_min, nt_max: shortest and longest observer window
 hipError_t launch_adj_gather(const PairRec *rec_op, const int32_t *nt, const float *gbar, int64_t P, int64_t O,
                                  int64_t N, int64_t NS, int64_t nt_min, int64_t nt_max, float *gpad, float *cbar,
                                  hipStream_t stream);
 
-// Adjoint of the source stage: coefficient adjoints [8][P][NS] -> gradients (time-major, in_dtype).
-// real_type 0 = double (cbar and scratch double), 1 = float.
-hipError_t launch_source_adjoint(int real_type, int in_dtype, const void *cbar, const void *rho, const void *u,
-                                 const double *normal, int64_t P, int64_t N, int64_t NS, Flow f, const double *cp,
-                                 void *scratch, void *g_rho, void *g_u, void *g_p, hipStream_t stream);
+// Adjoint of the source stage: coefficient adjoints [8][P][NS] floats -> gradients (time-major, in_dtype).
+hipError_t launch_source_adjoint(int in_dtype, const void *cbar, const void *rho, const void *u, const double *normal,
+                                 int64_t P, int64_t N, int64_t NS, Flow f, const double *cp, void *g_rho, void *g_u,
+                                 void *g_p, hipStream_t stream);
 
 // Batched launches over n cases (device arrays `cases`, prefix tables in `idx`).
 // coef_type 1 = float, 2 = bf16; in_dtype 0 = double, 1 = float.  The forward gather
@@ -343,9 +379,9 @@ hipError_t launch_batch_source(int in_dtype, int coef_type, const BatchCase *cas
 hipError_t launch_batch_source_adjoint(int in_dtype, const BatchCase *cases, const int64_t *start_int,
                                        const int64_t *start_gen, int n, int64_t blocks_int, int64_t blocks_gen,
                                        hipStream_t stream);
-// forward: chunked source stage of all cases, counter reset, the persistent gather (matrix-core with
-// `umax` units per wave, or LDS-staged when umax is 0), then the split sums of all cases
-hipError_t launch_batch_forward(int in_dtype, int coef_type, int umax, const BatchCase *cases, BatchIndex idx,
+// forward: chunked source stage of all cases, counter reset, the persistent gather (matrix-core
+// or LDS-staged), then the split sums of all cases
+hipError_t launch_batch_forward(int in_dtype, int coef_type, bool mfma, const BatchCase *cases, BatchIndex idx,
                                 const int4 *items, int n_items, int *counter, int grid, size_t shmem,
                                 int64_t blocks_src, int64_t blocks_srcg, int64_t blocks_red, hipStream_t stream);
 // adjoint: zero-padded dJ/dp' of all cases, then the transposed gather over adj_items (case, group of

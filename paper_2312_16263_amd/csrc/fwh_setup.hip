@@ -124,95 +124,137 @@ __device__ __forceinline__ PairTab pair_tables(const double *__restrict__ y, con
     return pt;
 }
 
-// plain FP64 form: the tables as FP64 arrays [O][P]
+// plain FP64 form: the tables as FP64 arrays in tiles of kYTile observers (layout in fwh_f64.hip);
+// observer slots fastest, so that neighbouring threads write neighbouring elements
 __global__ __launch_bounds__(256) void tables_f64_kernel(const double *__restrict__ y, const double *__restrict__ dS,
                                                          const double *__restrict__ x_obs,
                                                          const double *__restrict__ t_start,
                                                          const int32_t *__restrict__ nt, int64_t P, int64_t O,
                                                          int64_t N, Flow f, double *__restrict__ K64,
                                                          double *__restrict__ W64, int32_t *__restrict__ N0) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;  // pair index: tile, panel, slot
     if (i >= P * O) return;
-    const int64_t o = i / P, p = i - o * P;
-    const PairTab pt = pair_tables(y, dS, x_obs, t_start, nt, N, f, o, p);
-    for (int c = 0; c < 8; ++c) K64[i * 8 + c] = pt.K[c];
+    const int64_t t = i / (kYTile * P);
+    const int c = rec_tile_obs(t, O);
+    const int64_t e = i - t * kYTile * P, p = e / c;
+    const int s = (int)(e - p * c);
+    const PairTab pt = pair_tables(y, dS, x_obs, t_start, nt, N, f, t * kYTile + s, p);
+    double *K = K64 + (i - s) * 8;
+    for (int f8 = 0; f8 < 8; ++f8) K[f8 * c + s] = pt.K[f8];
     for (int j = 0; j < 4; ++j) W64[i * 4 + j] = pt.w[j];
     N0[i] = pt.n0;
 }
 
-// FP32/BF16 forms: block = one observer tile (kObsTile observers) x kTabPanels panels; thread
-// (observer slot j, panel q) computes the pair's tables, the block reduces n0 over the tile's
-// observers per panel: tw[t][p] = (lo, hi) = (min n0, max n0), and wblk[block] = the widest window
-// of the block's panels (blocks t * bpt .. t * bpt + bpt - 1 belong to tile t, bpt = ceil(P /
-// kTabPanels)); then each thread writes its pair record [o][p] with n0 - lo in staged bytes (and,
-// with rbf, the bfloat16 high/low split of the weights).
+// FP32/BF16 forms: block = two observer tiles (kObsTile = 2 kYTile observers) x kTabPanels panels; thread
+// (observer slot j, panel q) computes the pair's tables, the block reduces n0 over the observers
+// per panel: tw[t][p] = (lo, hi) = (min n0, max n0), and wblk[block] = the widest window of the
+// block's panels over the 32 observers, and over its 16-observer tiles in the high 16 bits (blocks
+// t * bpt .. t * bpt + bpt - 1 belong to 32-observer tile t, bpt = ceil(P / kTabPanels)).  The pair
+// tables leave through LDS: a tile's blocks of the kTabPanels panels are one contiguous piece of
+// memory (16 c dwords per panel), written by consecutive lanes.
 constexpr int kTabPanels = 256 / kObsTile;
+static_assert(kObsTile == 2 * kYTile, "the table kernel handles two 16-observer tiles");
 __global__ __launch_bounds__(256) void tables_tile_kernel(const double *__restrict__ y, const double *__restrict__ dS,
                                                           const double *__restrict__ x_obs,
                                                           const double *__restrict__ t_start,
                                                           const int32_t *__restrict__ nt, int64_t P, int64_t O,
-                                                          int64_t N, Flow f, int64_t bpt, PairRec *__restrict__ rec_op,
+                                                          int64_t N, Flow f, int64_t bpt, PairRec *__restrict__ rec,
                                                           PairBf *__restrict__ rbf, int2 *__restrict__ tw,
                                                           int32_t *__restrict__ wblk) {
     const int64_t t = blockIdx.x / bpt;
-    const int j = threadIdx.x / kTabPanels, q = threadIdx.x % kTabPanels;
-    const int64_t o = t * kObsTile + j, p = (blockIdx.x - t * bpt) * kTabPanels + q;
-    __shared__ int sn0[kObsTile][kTabPanels];
-    __shared__ int slo[kTabPanels];
+    const int j = threadIdx.x % kObsTile, q = threadIdx.x / kObsTile;
+    const int64_t p0 = (blockIdx.x - t * bpt) * kTabPanels;
+    const int64_t o = t * kObsTile + j, p = p0 + q;
+    const int h = j / kYTile, s = j % kYTile;  // 16-observer tile 2 t + h, slot s
+    __shared__ int sn0[kTabPanels][kObsTile + 1];
+    __shared__ int slo[kTabPanels], slo16[2][kTabPanels], sw16[2][kTabPanels];
     __shared__ int sw[kTabPanels];
+    __shared__ uint32_t out[2][kTabPanels * kYTile * 16];
+    const int64_t nobs = O - t * kObsTile < kObsTile ? O - t * kObsTile : kObsTile;
+    const int np = (int)(P - p0 < kTabPanels ? P - p0 : kTabPanels);
+    const int c0 = (int)(nobs < kYTile ? nobs : kYTile), c1 = (int)nobs - c0;
+    const int c = h == 0 ? c0 : c1;
     const bool valid = o < O && p < P;
     PairTab pt;
     if (valid) pt = pair_tables(y, dS, x_obs, t_start, nt, N, f, o, p);
-    sn0[j][q] = valid ? pt.n0 : 0;
+    sn0[q][j] = valid ? pt.n0 : 0;
     __syncthreads();
     if (threadIdx.x < kTabPanels) {
-        const int64_t nobs = O - t * kObsTile < kObsTile ? O - t * kObsTile : kObsTile;
-        int lo = INT_MAX, hi = INT_MIN;
-        for (int jj = 0; jj < nobs; ++jj) {
-            lo = sn0[jj][q] < lo ? sn0[jj][q] : lo;
-            hi = sn0[jj][q] > hi ? sn0[jj][q] : hi;
+        const int qq = threadIdx.x;
+        int lo = INT_MAX, hi = INT_MIN, w16 = 0;
+        for (int hh = 0; hh < 2; ++hh) {
+            int l = INT_MAX, u = INT_MIN;
+            for (int jj = hh * kYTile; jj < (hh + 1) * kYTile && jj < nobs; ++jj) {
+                l = sn0[qq][jj] < l ? sn0[qq][jj] : l;
+                u = sn0[qq][jj] > u ? sn0[qq][jj] : u;
+            }
+            const int w = l <= u ? u - l : 0;
+            slo16[hh][qq] = l;
+            sw16[hh][qq] = w;
+            w16 = w > w16 ? w : w16;
+            lo = l < lo ? l : lo;
+            hi = u > hi ? u : hi;
         }
         int width = 0;
-        if (p < P) {
-            tw[t * P + p] = make_int2(lo, hi);
-            width = hi - lo;
+        if (p0 + qq < P) {
+            tw[t * P + p0 + qq] = make_int2(lo, hi);
+            width = (hi - lo) | (w16 << 16);
         }
-        sw[q] = width;
-        slo[q] = lo;
+        sw[qq] = width;
+        slo[qq] = lo;
     }
     __syncthreads();
     if (valid) {
-        PairRec r;
-        for (int c = 0; c < 8; ++c) r.K[c] = (float)pt.K[c];
-        for (int jj = 0; jj < 4; ++jj) r.w[jj] = (float)pt.w[jj];
-        r.n0 = pt.n0;
-        r.n0w = (pt.n0 - slo[q]) * (rbf ? 8 : 16);
-        r.pad[0] = r.pad[1] = 0;
-        const int64_t i = o * P + p;
-        rec_op[i] = r;
-        if (rbf) {
+        uint32_t *blk = out[h] + q * 16 * c;
+        for (int cc = 0; cc < 8; ++cc) blk[rec_dword(cc, s, c)] = __float_as_uint((float)pt.K[cc]);
+        for (int jj = 0; jj < 4; ++jj) blk[kRecW * c + 4 * s + jj] = __float_as_uint((float)pt.w[jj]);
+        blk[kRecN0 * c + s] = (uint32_t)pt.n0;
+        blk[kRecN0w * c + s] = (uint32_t)((pt.n0 - slo[q]) * (rbf ? 8 : 16));
+        blk[kRecD16 * c + s] = (uint32_t)(pt.n0 - slo16[h][q]);
+        blk[kRecW16 * c + s] = (uint32_t)sw16[h][q];
+    }
+    __syncthreads();
+    for (int hh = 0; hh < 2; ++hh) {
+        const int cc = hh == 0 ? c0 : c1;
+        const int n16 = np * cc * 4;  // 16-byte pieces
+        uint4 *dst = reinterpret_cast<uint4 *>(rec + (2 * t + hh) * kYTile * P + p0 * cc);
+        for (int u = threadIdx.x; u < n16; u += 256) dst[u] = reinterpret_cast<const uint4 *>(out[hh])[u];
+    }
+    if (rbf) {
+        __syncthreads();
+        if (valid) {
             // bfloat16 by round-to-nearest-even of the FP32 value (weights are finite)
             auto bf16 = [](double v) {
                 const uint32_t b = __float_as_uint((float)v);
                 return (b + 0x7fffu + ((b >> 16) & 1u)) >> 16;
             };
-            PairBf qb;
-            for (int c = 0; c < 4; ++c) {
-                uint32_t h[2], l[2];
+            uint32_t *blk = out[h] + q * 8 * c;
+            for (int cc = 0; cc < 4; ++cc) {
+                uint32_t hb[2], lb[2];
                 for (int e = 0; e < 2; ++e) {
-                    h[e] = bf16(pt.K[2 * c + e]);
-                    l[e] = bf16(pt.K[2 * c + e] - (double)__uint_as_float(h[e] << 16));
+                    hb[e] = bf16(pt.K[2 * cc + e]);
+                    lb[e] = bf16(pt.K[2 * cc + e] - (double)__uint_as_float(hb[e] << 16));
                 }
-                qb.hi[c] = h[0] | (h[1] << 16);
-                qb.lo[c] = l[0] | (l[1] << 16);
+                blk[8 * s + cc] = hb[0] | (hb[1] << 16);
+                blk[8 * s + 4 + cc] = lb[0] | (lb[1] << 16);
             }
-            rbf[i] = qb;
+        }
+        __syncthreads();
+        for (int hh = 0; hh < 2; ++hh) {
+            const int cc = hh == 0 ? c0 : c1;
+            const int n16 = np * cc * 2;
+            uint4 *dst = reinterpret_cast<uint4 *>(rbf + (2 * t + hh) * kYTile * P + p0 * cc);
+            for (int u = threadIdx.x; u < n16; u += 256) dst[u] = reinterpret_cast<const uint4 *>(out[hh])[u];
         }
     }
     if (threadIdx.x == 0) {
-        int m = 0;
-        for (int qq = 0; qq < kTabPanels; ++qq) m = sw[qq] > m ? sw[qq] : m;
-        wblk[blockIdx.x] = m;
+        unsigned m = 0, m16 = 0;
+        for (int qq = 0; qq < kTabPanels; ++qq) {
+            const unsigned w = (unsigned)sw[qq];
+            m = (w & 0xffffu) > m ? w & 0xffffu : m;
+            m16 = (w >> 16) > m16 ? w >> 16 : m16;
+        }
+        wblk[blockIdx.x] = (int32_t)(m | (m16 << 16));
     }
 }
 

@@ -12,14 +12,9 @@
 // the Thomas algorithm with the precomputed pivots cp[r] (cp[1] = 1/4,
 // cp[r] = 1/(4 - cp[r-1])).
 //
-// Layout: one thread per (panel, channel), a wave = 64 consecutive panels of one
-// channel and a block = the 4 channels of one channel group, so every time step
-// is one coalesced load per input variable.  The forward elimination streams
-// the inputs in time order and writes the reduced right-hand sides to a
-// time-major scratch [8][N][P]; back substitution runs in reverse time order and
-// the coefficients go out panel-major with the 4 channels of a group
-// interleaved, coef[P][2][NS][4] (one 4-channel quad per time index), through a
-// block-wide LDS transpose.  All arithmetic FP64.
+// FP32 and BF16 coefficient storage (the plain FP64 form is in fwh_f64.hip): chunks of the record,
+// coefficients out panel-major with the 4 channels of a group interleaved, coef[P][2][NS][4] (one
+// 4-channel quad per time index).  All arithmetic FP64.
 #include "fwh_internal.h"
 
 namespace fwh {
@@ -29,182 +24,8 @@ struct bf16s {
     uint16_t bits;
 };
 
-template <typename T>
-struct Store;
-template <>
-struct Store<double> {
-    static __device__ __forceinline__ double put(double v) { return v; }
-};
-template <>
-struct Store<float> {
-    static __device__ __forceinline__ float put(double v) { return (float)v; }
-};
-template <>
-struct Store<bf16s> {
-    // double -> float (round to nearest even) -> bfloat16 (round to nearest even)
-    static __device__ __forceinline__ bf16s put(double v) {
-        const float x = (float)v;
-        uint32_t u = __float_as_uint(x);
-        bf16s r;
-        if ((u & 0x7fffffffu) > 0x7f800000u) {
-            r.bits = (uint16_t)((u >> 16) | 0x40u);
-        } else {
-            u += 0x7fffu + ((u >> 16) & 1u);
-            r.bits = (uint16_t)(u >> 16);
-        }
-        return r;
-    }
-};
-
-// Channel c: base quantity (0 = Q, 1..3 = L_i) and whether it is the derivative.
-__device__ __forceinline__ int channel_base(int c) { return c <= 1 ? 0 : (c <= 4 ? c - 1 : c - 4); }
-__device__ __forceinline__ bool channel_deriv(int c) { return c == 0 || (c >= 2 && c <= 4); }
-
-struct PanelFrame {
-    double nx, ny, nz, U0n;
-};
-
-// Source term of the given base at time-major index idx (Eqs. (Qn_New_nd), (Li_New_nd)):
-//   Q = rho u.n - U0.n,  L_i = p' n_i + rho (u_i - U0_i) u.n
-template <typename TIn>
-__device__ __forceinline__ double source_term(int base, const TIn *__restrict__ rho, const TIn *__restrict__ u,
-                                              const TIn *__restrict__ pp, int64_t idx, int64_t NP,
-                                              const PanelFrame &pf, const Flow &f) {
-    const double r = (double)rho[idx];
-    const double u1 = (double)u[idx], u2 = (double)u[NP + idx], u3 = (double)u[2 * NP + idx];
-    const double un = u1 * pf.nx + u2 * pf.ny + u3 * pf.nz;
-    if (base == 0) return r * un - pf.U0n;
-    const double pv = (double)pp[idx];
-    if (base == 1) return pv * pf.nx + r * (u1 - f.ca) * un;
-    if (base == 2) return pv * pf.ny + r * (u2 - f.sa) * un;
-    return pv * pf.nz + r * u3 * un;
-}
-
-template <typename TIn, typename TScr, typename TOut>
-__device__ __forceinline__ void source_fwd_body(const SrcFwdArgs &a, int64_t bx, int by) {
-    const TIn *__restrict__ rho = static_cast<const TIn *>(a.rho);
-    const TIn *__restrict__ u = static_cast<const TIn *>(a.u);
-    const TIn *__restrict__ pp = static_cast<const TIn *>(a.pp);
-    const double *__restrict__ normal = a.normal;
-    const int64_t P = a.P, N = a.N, NS = a.NS;
-    const Flow f = a.f;
-    const double *__restrict__ cp = a.cp;
-    TScr *__restrict__ scr = static_cast<TScr *>(a.scr);
-    TOut *__restrict__ coef = static_cast<TOut *>(a.coef);
-    constexpr int CH = 128 / (int)sizeof(TOut);  // time indices per flush (128-byte row segments per channel)
-    constexpr int PF = 8;                        // time steps loaded ahead
-    constexpr int RS = CH * 4 + 1;               // padded LDS row: [CH][4 channels] + 1
-    __shared__ TOut stage[64 * RS];
-    const int lane = threadIdx.x & 63;
-    const int wv = threadIdx.x >> 6;
-    const int ch = by * 4 + wv;
-    const int base = channel_base(ch);
-    const bool deriv = channel_deriv(ch);
-    const int64_t pbase = bx * 64;
-    const int64_t p = pbase + lane;
-    const bool active = p < P;
-    const int64_t pc = active ? p : P - 1;
-    const int64_t NP = N * P;
-    PanelFrame pf;
-    pf.nx = normal[3 * pc];
-    pf.ny = normal[3 * pc + 1];
-    pf.nz = normal[3 * pc + 2];
-    pf.U0n = f.ca * pf.nx + f.sa * pf.ny;
-    const double i2h = 1.0 / (2.0 * f.dtau);
-
-    auto X = [&](int64_t n) { return source_term<TIn>(base, rho, u, pp, n * P + pc, NP, pf, f); };
-
-    // ---- forward sweep: f_n for n = 0..N-1, Thomas row r = n-1 once f_n is known
-    const double X0 = X(0), X1 = X(1), X2 = X(2);
-    const double f0 = deriv ? (-3.0 * X0 + 4.0 * X1 - X2) * i2h : X0;
-    double Xmm = 0.0, Xm = X0, Xc = X1, Xp = X2;
-    double fprev = f0, fN1 = 0.0, dprev = 0.0;
-    TScr *scr_ch = scr + (int64_t)ch * NP;
-    for (int64_t nb = 1; nb < N; nb += PF) {
-        double Xf[PF];
-#pragma unroll
-        for (int i = 0; i < PF; ++i) {
-            const int64_t n2 = nb + i + 2;
-            Xf[i] = (n2 < N) ? X(n2) : 0.0;
-        }
-#pragma unroll
-        for (int i = 0; i < PF; ++i) {
-            const int64_t n = nb + i;
-            if (n < N) {
-                double fn;
-                if (n < N - 1) fn = deriv ? (Xp - Xm) * i2h : Xc;
-                else fn = deriv ? (3.0 * Xc - 4.0 * Xm + Xmm) * i2h : Xc;
-                const int64_t r = n - 1;
-                if (r >= 1) {
-                    double rhs = 6.0 * fprev;
-                    if (r == 1) rhs -= f0;
-                    if (r == N - 2) rhs -= fn;
-                    const double d = (rhs - dprev) * cp[r];
-                    if (active) scr_ch[r * P + p] = (TScr)d;
-                    dprev = d;
-                }
-                if (n == N - 1) fN1 = fn;
-                fprev = fn;
-                Xmm = Xm;
-                Xm = Xc;
-                Xc = Xp;
-                Xp = Xf[i];
-            }
-        }
-    }
-
-    // ---- back substitution in reverse order, coefficients by storage index i:
-    // i = 0: c_{-1}; i = n+1: c_n (n = 0..N-1); i = N+1: c_N; i >= N+2: 0.
-    const double xN2 = dprev;  // x_{N-2} = d'_{N-2}
-    double x = xN2;            // x_{n+1} of the recurrence
-    const int cc = ch & 3;  // channel within the group
-    constexpr int SB = CH < 16 ? CH : 16;  // back-substitution steps loaded ahead
-    for (int64_t b = NS / CH - 1; b >= 0; --b) {
-        const int64_t i0 = b * CH;
-        for (int sb = CH - SB; sb >= 0; sb -= SB) {
-            double dpre[SB];
-#pragma unroll
-            for (int q = 0; q < SB; ++q) {
-                const int64_t n = i0 + sb + q - 1;
-                dpre[q] = (n >= 1 && n <= N - 3 && active) ? (double)scr_ch[n * P + p] : 0.0;
-            }
-#pragma unroll
-            for (int q = SB - 1; q >= 0; --q) {
-                const int64_t i = i0 + sb + q;
-                double v;
-                if (i >= N + 2) v = 0.0;
-                else if (i == N + 1) v = 2.0 * fN1 - xN2;
-                else if (i == N) v = fN1;
-                else if (i >= 2) {
-                    const int64_t n = i - 1;
-                    if (n <= N - 3) x = dpre[q] - cp[n] * x;
-                    v = x;
-                } else if (i == 1) v = f0;
-                else v = 2.0 * f0 - x;
-                stage[lane * RS + (sb + q) * 4 + cc] = Store<TOut>::put(v);
-            }
-        }
-        __syncthreads();
-        // block-wide flush: for each of the 64 panels, CH quads of 4 channels, contiguous in memory
-        for (int t = threadIdx.x; t < 64 * CH; t += 256) {
-            const int r = t / CH, col = t - r * CH;
-            const int64_t prow = pbase + r;
-            if (prow < P) {
-                TOut *dst = coef + (((prow * 2 + by) * NS) + i0 + col) * 4;
-                const TOut *src = stage + r * RS + col * 4;
-                dst[0] = src[0];
-                dst[1] = src[1];
-                dst[2] = src[2];
-                dst[3] = src[3];
-            }
-        }
-        __syncthreads();
-    }
-}
-
 // ------------------------------------------------------- chunked source stage
-// FP32 and BF16 coefficient modes (the plain FP64 form keeps the exact
-// sequential kernel above).  Geometry in fwh_internal.h: a block owns 32 panels
+// Geometry in fwh_internal.h: a block owns 32 panels
 // and 64 coefficient indices; wave w handles base quantity w (Q, L_1, L_2, L_3)
 // with lanes 0-31 on its derivative channel and lanes 32-63 on the channel
 // itself, so the source terms are wave-uniform.  Each thread runs the forward
@@ -547,13 +368,23 @@ __device__ __forceinline__ void src_chunk(const SrcFwdArgs &a, int64_t pbk, int6
     }
 }
 
-template <typename TIn, typename TOut, bool GEN, int ENDS = 3>
-__device__ __forceinline__ void src_chunk_block(const SrcFwdArgs &a, int64_t pbk, int64_t k) {
+// Chunk k of panel block pbk, with the end rules it can reach.  One set of LDS arrays for all forms:
+// separate arrays of the instantiations inlined into one kernel would add up.
+template <typename TIn, typename TOut>
+__device__ __forceinline__ void src_chunk_block(const SrcFwdArgs &a, int64_t pbk, int64_t k, bool interior) {
     __shared__ TIn ring0[kSrcGV];
     __shared__ TIn ring1[kSrcGV];
     __shared__ float tile[(kSrcTC / 4) * kSrcRS];
-    __shared__ double endv[GEN && (ENDS & 2) ? 2 * 256 : 1];  // f_{N-1}, d_{N-2} per thread
-    src_chunk<TIn, TOut, GEN, ENDS>(a, pbk, k * kSrcTC, ring0, ring1, tile, endv);
+    __shared__ double endv[2 * 256];  // f_{N-1}, d_{N-2} per thread
+    const int64_t i0 = k * kSrcTC, R0 = i0 - 1 - kSrcH;
+    if (interior) {
+        src_chunk<TIn, TOut, false>(a, pbk, i0, ring0, ring1, tile, endv);
+    } else {
+        const bool s_in = R0 <= 3, e_in = R0 + kSrcW >= a.N - 1;
+        if (s_in && e_in) src_chunk<TIn, TOut, true, 3>(a, pbk, i0, ring0, ring1, tile, endv);
+        else if (e_in) src_chunk<TIn, TOut, true, 2>(a, pbk, i0, ring0, ring1, tile, endv);
+        else src_chunk<TIn, TOut, true, 1>(a, pbk, i0, ring0, ring1, tile, endv);
+    }
 }
 
 // ------------------------------------------------ chunked source adjoint stage
@@ -799,341 +630,127 @@ __device__ __forceinline__ void src_adj_chunk(const SrcAdjArgs &a, int64_t pbk, 
 // slabs [256][kAdjSlabRS], then the Xbar tile [kSrcTC / 2][kSrcRS]
 constexpr int kAdjWords = 256 * kAdjSlabRS > (kSrcTC / 2) * kSrcRS ? 256 * kAdjSlabRS : (kSrcTC / 2) * kSrcRS;
 template <typename TIn>
-__device__ __forceinline__ void src_adj_interior_block(const SrcAdjArgs &a, int64_t pbk, int64_t k) {
+__device__ __forceinline__ void src_adj_block(const SrcAdjArgs &a, int64_t pbk, int64_t k, bool interior) {
     __shared__ float lds[kAdjWords];
-    src_adj_chunk<TIn, false>(a, pbk, k, lds);
+    if (interior) src_adj_chunk<TIn, false>(a, pbk, k, lds);
+    else src_adj_chunk<TIn, true>(a, pbk, k, lds);
 }
 
-template <typename TIn>
-__device__ __forceinline__ void src_adj_general_block(const SrcAdjArgs &a, int64_t pbk, int64_t k) {
-    __shared__ float lds[kAdjWords];
-    src_adj_chunk<TIn, true>(a, pbk, k, lds);
-}
-
-// 1-D grid of (panel block, interior chunk) pairs, chunks fastest, renumbered per XCD: the chunks of
+// One launch for all chunks: the boundary chunks' blocks first (ngen chunks of every panel block,
+// padded to a multiple of kXcds blocks), then the interior ones, so that the boundary chunks do not run
+// as a launch of their own with most of the chip idle at its end (source adjoint of a 2048-panel,
+// 512-frame surface: 46 us in two launches).
+// Interior: (panel block, chunk) pairs, chunks fastest, renumbered per XCD: the chunks of
 // one panel block run together on one XCD, so the coefficient-adjoint rows that neighbouring chunks
 // both read (the recurrences' overlap) come from that XCD's L2 rather than from HBM twice.
 template <typename TIn>
-__global__ __launch_bounds__(256) void src_adj_interior_kernel(SrcAdjArgs a, int64_t nint) {
-    const int64_t L = xcd_block(blockIdx.x, gridDim.x), pbk = L / nint;
-    src_adj_interior_block<TIn>(a, pbk, 1 + L - pbk * nint);
+__global__ __launch_bounds__(256) void src_adj_kernel(SrcAdjArgs a, int64_t pb, int64_t ngen, int64_t nint,
+                                                      int64_t gen_blocks) {
+    const int64_t h = blockIdx.x;
+    if (h < gen_blocks) {
+        if (h < pb * ngen) src_adj_block<TIn>(a, h % pb, src_general_chunk(h / pb, nint), false);
+    } else {
+        const int64_t L = xcd_block(h - gen_blocks, gridDim.x - gen_blocks), pbk = L / nint;
+        src_adj_block<TIn>(a, pbk, 1 + L - pbk * nint, true);
+    }
 }
-// grid (panel blocks, general chunks)
+// batched: the boundary chunks of all cases, then the interior ones
 template <typename TIn>
-__global__ __launch_bounds__(256) void src_adj_general_kernel(SrcAdjArgs a) {
-    src_adj_general_block<TIn>(a, blockIdx.x, src_general_chunk(blockIdx.y, adj_interior_chunks(a.N)));
+__global__ __launch_bounds__(256) void src_adj_batched(const BatchCase *__restrict__ cases,
+                                                       const int64_t *__restrict__ start,
+                                                       const int64_t *__restrict__ startg, int n, int64_t gen_blocks) {
+    const int64_t g = blockIdx.x;
+    if (g < gen_blocks) {
+        if (g >= startg[n]) return;
+        const int c = find_case(startg, n, g);
+        const int64_t local = g - startg[c], N = cases[c].sadj.N;
+        const int64_t nint = adj_interior_chunks(N), ng = adj_chunks(N) - nint, pbk = local / ng;
+        src_adj_block<TIn>(cases[c].sadj, pbk, src_general_chunk(local - pbk * ng, nint), false);
+    } else {
+        const int64_t h = xcd_block(g - gen_blocks, gridDim.x - gen_blocks);
+        const int c = find_case(start, n, h);
+        const int64_t local = h - start[c];
+        const int64_t nk = adj_interior_chunks(cases[c].sadj.N), pbk = local / nk;
+        src_adj_block<TIn>(cases[c].sadj, pbk, 1 + local - pbk * nk, true);
+    }
 }
-template <typename TIn>
-__global__ __launch_bounds__(256) void src_adj_interior_batched(const BatchCase *__restrict__ cases,
-                                                                const int64_t *__restrict__ start, int n) {
-    const int64_t h = xcd_block(blockIdx.x, gridDim.x);
-    const int c = find_case(start, n, h);
-    const int64_t local = h - start[c];
-    const int64_t nk = adj_interior_chunks(cases[c].sadj.N);
-    const int64_t pbk = local / nk;
-    src_adj_interior_block<TIn>(cases[c].sadj, pbk, 1 + local - pbk * nk);
-}
-template <typename TIn>
-__global__ __launch_bounds__(256) void src_adj_general_batched(const BatchCase *__restrict__ cases,
-                                                               const int64_t *__restrict__ start, int n) {
-    const int c = find_case(start, n, blockIdx.x);
-    const int64_t local = (int64_t)blockIdx.x - start[c];
-    const int64_t N = cases[c].sadj.N;
-    const int64_t nint = adj_interior_chunks(N);
-    const int64_t ng = adj_chunks(N) - nint;
-    const int64_t pbk = local / ng;
-    src_adj_general_block<TIn>(cases[c].sadj, pbk, src_general_chunk(local - pbk * ng, nint));
-}
+
+constexpr int64_t round_xcd(int64_t blocks) { return (blocks + kXcds - 1) / kXcds * kXcds; }
 
 template <typename TIn>
 hipError_t src_adj_chunk_launch_t(const SrcAdjArgs &a, hipStream_t stream) {
-    const unsigned pb = (unsigned)((a.P + kSrcPanels - 1) / kSrcPanels);
-    const int64_t nint = adj_interior_chunks(a.N);
-    const int64_t ngen = adj_chunks(a.N) - nint;
-    if (nint > 0) {
-        src_adj_interior_kernel<TIn><<<dim3((unsigned)(pb * nint)), dim3(256), 0, stream>>>(a, nint);
-        const hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
-    src_adj_general_kernel<TIn><<<dim3(pb, (unsigned)ngen), dim3(256), 0, stream>>>(a);
+    const int64_t pb = (a.P + kSrcPanels - 1) / kSrcPanels;
+    const int64_t nint = adj_interior_chunks(a.N), ngen = adj_chunks(a.N) - nint, gb = round_xcd(pb * ngen);
+    src_adj_kernel<TIn><<<dim3((unsigned)(gb + pb * nint)), dim3(256), 0, stream>>>(a, pb, ngen, nint, gb);
     return hipGetLastError();
 }
 
-// ------------------------------------------------------------------ adjoint
-
-// Transpose of the prefilter for one (panel, channel): coefficient adjoints
-// a_{-1..N} (storage indices 0..N+1) -> adjoints of the channel values f_0..f_{N-1}:
-//   end rows: a_0 += 2 a_{-1}, a_1 -= a_{-1}, a_{N-1} += 2 a_N, a_{N-2} -= a_N;
-//   interior: z = T^{-1} a_{1..N-2} (T = tridiag(1,4,1), symmetric);
-//   fbar_r = 6 z_r (r = 1..N-2), fbar_0 = a_0 - z_1, fbar_{N-1} = a_{N-1} - z_{N-2}.
-// Result written time-major into scr [8][N][P].
-template <typename TR>
-__device__ __forceinline__ void prefilter_adj_body(const PreAdjArgs &a, int64_t bx, int by) {
-    const TR *__restrict__ cbar = static_cast<const TR *>(a.cbar);
-    const int64_t P = a.P, N = a.N, NS = a.NS;
-    const double *__restrict__ cp = a.cp;
-    TR *__restrict__ scr = static_cast<TR *>(a.scr);
-    constexpr int CH = 128 / (int)sizeof(TR);
-    constexpr int PF = 8;
-    __shared__ TR stage[4][64][CH + 1];
-    const int lane = threadIdx.x & 63;
-    const int wv = threadIdx.x >> 6;
-    const int ch = by * 4 + wv;
-    const int64_t pbase = bx * 64;
-    const int64_t p = pbase + lane;
-    const bool active = p < P;
-    const int64_t pc = active ? p : P - 1;
-    const TR *row = cbar + ((int64_t)ch * P + pc) * NS;
-    const TR *cbar_ch = cbar + (int64_t)ch * P * NS;
-    const double am1 = (double)row[0];
-    const double aN = (double)row[N + 1];
-    double a0 = 0.0, aN1 = 0.0, dprev = 0.0;
-    TR *scr_ch = scr + (int64_t)ch * N * P;
-    // forward elimination over rows r = 1..N-2 (storage index r+1), streaming the row through LDS
-    const int64_t nblk = (N + CH - 1) / CH;  // storage indices 0..N cover a_{-1}..a_{N-1}
-    for (int64_t b = 0; b < nblk + 1; ++b) {
-        const int64_t i0 = b * CH;
-        __syncthreads();
-        for (int t = lane; t < 64 * CH; t += 64) {
-            const int r = t / CH, col = t - r * CH;
-            const int64_t prow = pbase + r;
-            stage[wv][r][col] = (prow < P && i0 + col < NS) ? cbar_ch[prow * NS + i0 + col] : (TR)0;
-        }
-        __syncthreads();
-#pragma unroll 4
-        for (int q = 0; q < CH; ++q) {
-            const int64_t i = i0 + q;
-            const int64_t r = i - 1;  // coefficient index
-            double a = (double)stage[wv][lane][q];
-            if (r == 0) a0 = a + 2.0 * am1;
-            if (r == N - 1) aN1 = a + 2.0 * aN;
-            if (r >= 1 && r <= N - 2) {
-                if (r == 1) a -= am1;
-                if (r == N - 2) a -= aN;
-                const double d = (a - dprev) * cp[r];
-                if (active) scr_ch[r * P + p] = (TR)d;
-                dprev = d;
-            }
-        }
-    }
-    // back substitution, fbar written in place
-    double z = dprev;  // z_{N-2}
-    const double zN2 = z;
-    if (active) scr_ch[(N - 2) * P + p] = (TR)(6.0 * zN2);
-    for (int64_t rb = N - 3; rb >= 1; rb -= PF) {
-        double dpre[PF];
-#pragma unroll
-        for (int q = 0; q < PF; ++q) {
-            const int64_t r = rb - q;
-            dpre[q] = (r >= 1 && active) ? (double)scr_ch[r * P + p] : 0.0;
-        }
-#pragma unroll
-        for (int q = 0; q < PF; ++q) {
-            const int64_t r = rb - q;
-            if (r >= 1) {
-                z = dpre[q] - cp[r] * z;
-                if (active) scr_ch[r * P + p] = (TR)(6.0 * z);
-            }
-        }
-    }
-    const double z1 = (N - 2 >= 1) ? z : 0.0;  // after the loop z = z_1
-    if (active) {
-        scr_ch[p] = (TR)(a0 - z1);
-        scr_ch[(N - 1) * P + p] = (TR)(aN1 - zN2);
-    }
-}
-
-// Per (frame n, panel p): source-term adjoints
-//   Qbar = fbar_Q + D^T fbar_Qdot,  Lbar_i = fbar_Li + D^T fbar_Ldot_i
-// (D the derivative matrix: central rows 1..N-2, one-sided rows 0 and N-1), then the
-// chain rule through Q = rho u.n - U0.n and L_i = p' n_i + rho (u_i - U0_i) u.n:
-//   drho = u.n (Qbar + Lbar.w),  du = rho n (Qbar + Lbar.w) + rho u.n Lbar,
-//   dp' = Lbar.n,  with w = u - U0.
-template <typename TR, typename TIn>
-__device__ __forceinline__ void source_adj_chain_body(const ChainArgs &a, int64_t bx, int64_t n) {
-    const TR *__restrict__ scr = static_cast<const TR *>(a.scr);
-    const TIn *__restrict__ rho = static_cast<const TIn *>(a.rho);
-    const TIn *__restrict__ u = static_cast<const TIn *>(a.u);
-    const double *__restrict__ normal = a.normal;
-    const int64_t P = a.P, N = a.N;
-    const Flow f = a.f;
-    TIn *__restrict__ g_rho = static_cast<TIn *>(a.g_rho);
-    TIn *__restrict__ g_u = static_cast<TIn *>(a.g_u);
-    TIn *__restrict__ g_p = static_cast<TIn *>(a.g_p);
-    const int64_t p = bx * 256 + threadIdx.x;
-    if (p >= P) return;
-    const int64_t NP = N * P;
-    const double i2h = 1.0 / (2.0 * f.dtau);
-    auto S = [&](int c, int64_t m) { return (double)scr[(int64_t)c * NP + m * P + p]; };
-    auto DT = [&](int c) {  // (D^T v)_n for channel c
-        double s = 0.0;
-        if (n - 1 >= 1 && n - 1 <= N - 2) s += S(c, n - 1);
-        if (n + 1 >= 1 && n + 1 <= N - 2) s -= S(c, n + 1);
-        if (n <= 2) s += (n == 0 ? -3.0 : (n == 1 ? 4.0 : -1.0)) * S(c, 0);
-        if (n >= N - 3) s += (n == N - 1 ? 3.0 : (n == N - 2 ? -4.0 : 1.0)) * S(c, N - 1);
-        return s * i2h;
-    };
-    const double Qb = S(1, n) + DT(0);
-    double Lb[3];
-    for (int i = 0; i < 3; ++i) Lb[i] = S(5 + i, n) + DT(2 + i);
-    const double nx = normal[3 * p], ny = normal[3 * p + 1], nz = normal[3 * p + 2];
-    const int64_t idx = n * P + p;
-    const double r = (double)rho[idx];
-    const double u1 = (double)u[idx], u2 = (double)u[NP + idx], u3 = (double)u[2 * NP + idx];
-    const double un = u1 * nx + u2 * ny + u3 * nz;
-    const double Lw = Lb[0] * (u1 - f.ca) + Lb[1] * (u2 - f.sa) + Lb[2] * u3;
-    const double q = Qb + Lw;
-    g_rho[idx] = (TIn)(un * q);
-    g_u[idx] = (TIn)(r * nx * q + r * un * Lb[0]);
-    g_u[NP + idx] = (TIn)(r * ny * q + r * un * Lb[1]);
-    g_u[2 * NP + idx] = (TIn)(r * nz * q + r * un * Lb[2]);
-    g_p[idx] = (TIn)(Lb[0] * nx + Lb[1] * ny + Lb[2] * nz);
-}
-
-template <typename TIn, typename TScr, typename TOut>
-__global__ __launch_bounds__(256) void source_fwd_kernel(SrcFwdArgs a) {
-    source_fwd_body<TIn, TScr, TOut>(a, blockIdx.x, blockIdx.y);
-}
-
-// grid (panel blocks, interior chunks): chunk k = 1 + blockIdx.y.  (Chunks of one panel block on one
-// XCD, as the source adjoint runs them, did not cut this stage's HBM reads: a chunk reads the rows it
-// shares with the next one last, the next chunk reads them first.)
+// grid (panel blocks, chunks): the ngen boundary chunks first, then the interior ones k = 1 .. nint, all in
+// one launch (a launch per boundary chunk ran 1024 blocks each on the 32768-panel sphere, 100 us apiece,
+// 0.25 ms of its 1.30 ms).  (Chunks of one panel block on one XCD, as the source adjoint runs them, did
+// not cut this stage's HBM reads: a chunk reads the rows it shares with the next one last, the next
+// chunk reads them first.)
 template <typename TIn, typename TOut>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void src_interior_kernel(SrcFwdArgs a) {
-    src_chunk_block<TIn, TOut, false>(a, blockIdx.x, 1 + (int64_t)blockIdx.y);
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void src_kernel(SrcFwdArgs a, int64_t ngen,
+                                                                                         int64_t nint) {
+    const int64_t g = blockIdx.y;
+    src_chunk_block<TIn, TOut>(a, blockIdx.x, g < ngen ? src_general_chunk(g, nint) : 1 + g - ngen, g >= ngen);
 }
-// one general chunk k for every panel block; ENDS as in src_chunk
-template <typename TIn, typename TOut, int ENDS>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void src_general_kernel(
-    SrcFwdArgs a, int64_t k) {
-    src_chunk_block<TIn, TOut, true, ENDS>(a, blockIdx.x, k);
-}
-// batched: blocks of case c are [start[c], start[c+1]), panel block major
+// batched: the boundary chunks of all cases, then the interior ones; blocks of case c are [start[c],
+// start[c+1]) of each, panel block major
 template <typename TIn, typename TOut>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void src_interior_batched(const BatchCase *__restrict__ cases,
-                                                            const int64_t *__restrict__ start, int n) {
-    const int c = find_case(start, n, blockIdx.x);
-    const int64_t local = (int64_t)blockIdx.x - start[c];
-    const int64_t nk = src_interior_chunks(cases[c].src.N);
-    const int64_t pbk = local / nk;
-    src_chunk_block<TIn, TOut, false>(cases[c].src, pbk, 1 + local - pbk * nk);
-}
-template <typename TIn, typename TOut>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void src_general_batched(const BatchCase *__restrict__ cases,
-                                                           const int64_t *__restrict__ start, int n) {
-    const int c = find_case(start, n, blockIdx.x);
-    const int64_t local = (int64_t)blockIdx.x - start[c];
-    const int64_t nint = src_interior_chunks(cases[c].src.N);
-    const int64_t ng = cases[c].src.NS / kSrcTC - nint;
-    const int64_t pbk = local / ng;
-    src_chunk_block<TIn, TOut, true>(cases[c].src, pbk, src_general_chunk(local - pbk * ng, nint));
-}
-
-template <typename TR>
-__global__ __launch_bounds__(256) void prefilter_adj_kernel(PreAdjArgs a) {
-    prefilter_adj_body<TR>(a, blockIdx.x, blockIdx.y);
-}
-
-template <typename TR, typename TIn>
-__global__ __launch_bounds__(256) void source_adj_chain_kernel(ChainArgs a) {
-    source_adj_chain_body<TR, TIn>(a, blockIdx.x, blockIdx.y);
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void src_batched(
+    const BatchCase *__restrict__ cases, const int64_t *__restrict__ start, const int64_t *__restrict__ startg, int n) {
+    const int64_t gen_blocks = startg[n], g = blockIdx.x;
+    const bool interior = g >= gen_blocks;
+    const int64_t h = interior ? g - gen_blocks : g;
+    const int64_t *st = interior ? start : startg;
+    const int c = find_case(st, n, h);
+    const int64_t local = h - st[c], nint = src_interior_chunks(cases[c].src.N);
+    const int64_t nk = interior ? nint : cases[c].src.NS / kSrcTC - nint, pbk = local / nk, j = local - pbk * nk;
+    src_chunk_block<TIn, TOut>(cases[c].src, pbk, interior ? 1 + j : src_general_chunk(j, nint), interior);
 }
 
 template <typename TIn, typename TOut>
 hipError_t source_chunk_launch_t(const SrcFwdArgs &a, hipStream_t stream) {
-    const unsigned pb = (unsigned)((a.P + kSrcPanels - 1) / kSrcPanels);
-    const int64_t nint = src_interior_chunks(a.N);
-    const int64_t ngen = a.NS / kSrcTC - nint;
-    if (nint > 0) {
-        src_interior_kernel<TIn, TOut><<<dim3(pb, (unsigned)nint), dim3(256), 0, stream>>>(a);
-        const hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
-    // one launch per general chunk, with the end rules it can reach
-    for (int64_t g = 0; g < ngen; ++g) {
-        const int64_t k = src_general_chunk(g, nint), R0 = k * kSrcTC - 1 - kSrcH;
-        const bool s_in = R0 <= 3, e_in = R0 + kSrcW >= a.N - 1;
-        if (s_in && e_in) src_general_kernel<TIn, TOut, 3><<<dim3(pb), dim3(256), 0, stream>>>(a, k);
-        else if (e_in) src_general_kernel<TIn, TOut, 2><<<dim3(pb), dim3(256), 0, stream>>>(a, k);
-        else src_general_kernel<TIn, TOut, 1><<<dim3(pb), dim3(256), 0, stream>>>(a, k);
-        const hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
-    return hipSuccess;
-}
-
-template <typename TIn, typename TScr, typename TOut>
-hipError_t source_launch_t(const SrcFwdArgs &a, hipStream_t stream) {
-    dim3 grid((unsigned)((a.P + 63) / 64), 2);
-    source_fwd_kernel<TIn, TScr, TOut><<<grid, dim3(256), 0, stream>>>(a);
-    return hipGetLastError();
-}
-
-template <typename TR, typename TIn>
-hipError_t source_adj_launch_t(const PreAdjArgs &pa, const ChainArgs &ca, hipStream_t stream) {
-    dim3 grid1((unsigned)((pa.P + 63) / 64), 2);
-    prefilter_adj_kernel<TR><<<grid1, dim3(256), 0, stream>>>(pa);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    dim3 grid2((unsigned)((ca.P + 255) / 256), (unsigned)ca.N);
-    source_adj_chain_kernel<TR, TIn><<<grid2, dim3(256), 0, stream>>>(ca);
+    const int64_t nint = src_interior_chunks(a.N), nk = a.NS / kSrcTC;
+    src_kernel<TIn, TOut><<<dim3((unsigned)((a.P + kSrcPanels - 1) / kSrcPanels), (unsigned)nk), dim3(256), 0, stream>>>(
+        a, nk - nint, nint);
     return hipGetLastError();
 }
 
 }  // namespace
 
 hipError_t launch_source(int in_dtype, int coef_type, const void *rho, const void *u, const void *pp,
-                         const double *normal, int64_t P, int64_t N, int64_t NS, Flow f, const double *cp,
-                         void *scratch, void *coef, hipStream_t stream) {
-    const SrcFwdArgs a{rho, u, pp, normal, P, N, NS, f, cp, scratch, coef};
-    if (in_dtype == 0) {
-        if (coef_type == 0) return source_launch_t<double, double, double>(a, stream);
-        if (coef_type == 1) return source_chunk_launch_t<double, float>(a, stream);
-        return source_chunk_launch_t<double, bf16s>(a, stream);
-    }
-    if (coef_type == 0) return source_launch_t<float, double, double>(a, stream);
-    if (coef_type == 1) return source_chunk_launch_t<float, float>(a, stream);
-    return source_chunk_launch_t<float, bf16s>(a, stream);
+                         const double *normal, int64_t P, int64_t N, int64_t NS, Flow f, const double *cp, void *coef,
+                         hipStream_t stream) {
+    const SrcFwdArgs a{rho, u, pp, normal, P, N, NS, f, cp, nullptr, coef};
+    if (in_dtype == 0)
+        return coef_type == 1 ? source_chunk_launch_t<double, float>(a, stream)
+                              : source_chunk_launch_t<double, bf16s>(a, stream);
+    return coef_type == 1 ? source_chunk_launch_t<float, float>(a, stream)
+                          : source_chunk_launch_t<float, bf16s>(a, stream);
 }
 
-hipError_t launch_source_adjoint(int real_type, int in_dtype, const void *cbar, const void *rho, const void *u,
-                                 const double *normal, int64_t P, int64_t N, int64_t NS, Flow f, const double *cp,
-                                 void *scratch, void *g_rho, void *g_u, void *g_p, hipStream_t stream) {
-    const PreAdjArgs pa{cbar, P, N, NS, cp, scratch};
-    const ChainArgs ca{scratch, rho, u, normal, P, N, f, g_rho, g_u, g_p};
-    if (real_type == 0) {
-        if (in_dtype == 0) return source_adj_launch_t<double, double>(pa, ca, stream);
-        return source_adj_launch_t<double, float>(pa, ca, stream);
-    }
+hipError_t launch_source_adjoint(int in_dtype, const void *cbar, const void *rho, const void *u, const double *normal,
+                                 int64_t P, int64_t N, int64_t NS, Flow f, const double *cp, void *g_rho, void *g_u,
+                                 void *g_p, hipStream_t stream) {
     const SrcAdjArgs sa{static_cast<const float *>(cbar), rho, u, normal, P, N, NS, f, cp, g_rho, g_u, g_p};
     if (in_dtype == 0) return src_adj_chunk_launch_t<double>(sa, stream);
     return src_adj_chunk_launch_t<float>(sa, stream);
 }
 
-// Batched source stages (FP32/BF16 modes: float scratch).
+// Batched source stages.
 hipError_t launch_batch_source(int in_dtype, int coef_type, const BatchCase *cases, const int64_t *start_int,
                                const int64_t *start_gen, int n, int64_t blocks_int, int64_t blocks_gen,
                                hipStream_t stream) {
-    const dim3 b(256);
-    if (blocks_int > 0) {
-        const dim3 g((unsigned)blocks_int);
-        if (in_dtype == 0) {
-            if (coef_type == 1) src_interior_batched<double, float><<<g, b, 0, stream>>>(cases, start_int, n);
-            else src_interior_batched<double, bf16s><<<g, b, 0, stream>>>(cases, start_int, n);
-        } else {
-            if (coef_type == 1) src_interior_batched<float, float><<<g, b, 0, stream>>>(cases, start_int, n);
-            else src_interior_batched<float, bf16s><<<g, b, 0, stream>>>(cases, start_int, n);
-        }
-        const hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
-    const dim3 g((unsigned)blocks_gen);
+    const dim3 g((unsigned)(blocks_int + blocks_gen)), b(256);
     if (in_dtype == 0) {
-        if (coef_type == 1) src_general_batched<double, float><<<g, b, 0, stream>>>(cases, start_gen, n);
-        else src_general_batched<double, bf16s><<<g, b, 0, stream>>>(cases, start_gen, n);
+        if (coef_type == 1) src_batched<double, float><<<g, b, 0, stream>>>(cases, start_int, start_gen, n);
+        else src_batched<double, bf16s><<<g, b, 0, stream>>>(cases, start_int, start_gen, n);
     } else {
-        if (coef_type == 1) src_general_batched<float, float><<<g, b, 0, stream>>>(cases, start_gen, n);
-        else src_general_batched<float, bf16s><<<g, b, 0, stream>>>(cases, start_gen, n);
+        if (coef_type == 1) src_batched<float, float><<<g, b, 0, stream>>>(cases, start_int, start_gen, n);
+        else src_batched<float, bf16s><<<g, b, 0, stream>>>(cases, start_int, start_gen, n);
     }
     return hipGetLastError();
 }
@@ -1141,15 +758,10 @@ hipError_t launch_batch_source(int in_dtype, int coef_type, const BatchCase *cas
 hipError_t launch_batch_source_adjoint(int in_dtype, const BatchCase *cases, const int64_t *start_int,
                                        const int64_t *start_gen, int n, int64_t blocks_int, int64_t blocks_gen,
                                        hipStream_t stream) {
-    const dim3 b(256);
-    if (blocks_int > 0) {
-        if (in_dtype == 0) src_adj_interior_batched<double><<<dim3((unsigned)blocks_int), b, 0, stream>>>(cases, start_int, n);
-        else src_adj_interior_batched<float><<<dim3((unsigned)blocks_int), b, 0, stream>>>(cases, start_int, n);
-        const hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
-    if (in_dtype == 0) src_adj_general_batched<double><<<dim3((unsigned)blocks_gen), b, 0, stream>>>(cases, start_gen, n);
-    else src_adj_general_batched<float><<<dim3((unsigned)blocks_gen), b, 0, stream>>>(cases, start_gen, n);
+    const int64_t gb = round_xcd(blocks_gen);
+    const dim3 g((unsigned)(blocks_int + gb)), b(256);
+    if (in_dtype == 0) src_adj_batched<double><<<g, b, 0, stream>>>(cases, start_int, start_gen, n, gb);
+    else src_adj_batched<float><<<g, b, 0, stream>>>(cases, start_int, start_gen, n, gb);
     return hipGetLastError();
 }
 
