@@ -131,6 +131,15 @@ int forward_gather(const fwh_plan *pl, int in_dtype) {
     return pl->gather_kind;
 }
 
+// Whether a streaming-gather plan runs the few-observer form instead (the same sums): while its time, 3.6 ps
+// per panel-observer-sample (its coefficient loads from L2), stays below the streaming form's chain of
+// 128 panels per split, about 100 us and at least 0.12 us per sample of the window.  Measured (us, streaming
+// / few, FP32, 8 observers): 2048 panels x 512 frames 112 / 28, 2048 x 1900 252 / 98, 8192 x 512
+// 111 / 104, 8192 x 1024 159 / 201, 16384 x 512 127 / 194.
+bool few_observers(const fwh_plan *pl) {
+    return pl->P * pl->O * pl->n_t_max < std::max<int64_t>(24000000, 30000 * pl->n_t_max);
+}
+
 int layout(fwh_plan *pl) {
     const size_t P = (size_t)pl->P, O = (size_t)pl->O, N = (size_t)pl->N, NS = (size_t)pl->NS;
     size_t off = 0;
@@ -547,7 +556,11 @@ int fwh_forward(fwh_plan *pl, int32_t in_dtype, const void *rho, const void *u, 
         const int kind = forward_gather(pl, in_dtype);
         {
             StageScope sc(pl, FWH_STAGE_GATHER, st);
-            if (kind == FWH_GATHER_STREAM)
+            if (kind == FWH_GATHER_STREAM && pl->gather_variant == FWH_GATHER_AUTO && few_observers(pl))
+                e = fwh::launch_gather_few(coef_type, pl->at<fwh::PairRec>(pl->off_rec_op), pl->rbf(),
+                                           pl->at<int32_t>(pl->off_nt), pl->ws + pl->off_coef, pl->P, pl->O, pl->NS,
+                                           pl->n_t_max, pl->splits, pl->at<float>(pl->off_part), st);
+            else if (kind == FWH_GATHER_STREAM)
                 e = fwh::launch_gather_stream(coef_type, pl->at<fwh::PairRec>(pl->off_rec_op), pl->rbf(),
                                               pl->at<int32_t>(pl->off_nt), pl->ws + pl->off_coef, pl->P, pl->O,
                                               pl->NS, pl->n_t_max, pl->splits, pl->at<float>(pl->off_part), st);

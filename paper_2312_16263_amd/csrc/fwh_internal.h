@@ -343,6 +343,11 @@ int gather_stream_blocks_per_cu(int coef_type, int64_t NS, int64_t nt_max);
 hipError_t launch_gather_stream(int coef_type, const PairRec *rec_op, const PairBf *rbf, const int32_t *nt,
                                 const void *coef, int64_t P, int64_t O, int64_t NS, int64_t nt_max, int splits,
                                 float *partial, hipStream_t stream);
+// At most kLdsWaves observers on a small surface (fwh_gather_few.hip): the streaming gather's splits and
+// sums, one wave per observer and row of 61 samples.
+hipError_t launch_gather_few(int coef_type, const PairRec *rec, const PairBf *rbf, const int32_t *nt, const void *coef,
+                             int64_t P, int64_t O, int64_t NS, int64_t nt_max, int splits, float *partial,
+                             hipStream_t stream);
 // out[i] = sum over splits of partial[z][i], in FP64 and fixed order, rounded to float.
 hipError_t launch_reduce_splits(const float *partial, int splits, int64_t total, float *out, hipStream_t stream);
 
