@@ -38,13 +38,14 @@ struct bf16s {
 // chunk at a time, as 16-byte (8-byte for BF16) quads of the interleaved layout.
 constexpr int kSrcRS = 257;  // LDS row: 8 channels x 32 panels + 1
 
-// Per-thread source-term form X = a p' + rho (b.u - g) u.n - d, which covers
-// Q (a = 0, b = 0, g = -1, d = U0.n) and L_i (a = n_i, b = e_i, g = U0_i, d = 0).
+// Per-thread source-term form X = a p' + rho (b u_i - g) u.n - d, which covers
+// Q (a = 0, b = 0, g = -1, d = U0.n) and L_i (a = n_i, b = 1, g = U0_i, d = 0).
 template <typename TIn>
 struct SrcLane {
     const TIn *rho, *u, *pp;
     int64_t NP;
-    double nx, ny, nz, al, b1, b2, b3, gm, dl;
+    double nx, ny, nz, al, b, gm, dl;
+    int uw;               // the base quantity's component of u (0..2; Q: any, times zero)
     double s_der, s_val;  // f = s_der (X+ - X-) + s_val X
     int ch;               // channel index (0..7)
     __device__ __forceinline__ SrcLane(const SrcFwdArgs &a, int64_t pc) {
@@ -60,29 +61,25 @@ struct SrcLane {
         nz = a.normal[3 * pc + 2];
         const double Ux = a.f.ca, Uy = a.f.sa;
         al = w == 1 ? nx : (w == 2 ? ny : (w == 3 ? nz : 0.0));
-        b1 = w == 1 ? 1.0 : 0.0;
-        b2 = w == 2 ? 1.0 : 0.0;
-        b3 = w == 3 ? 1.0 : 0.0;
+        b = w == 0 ? 0.0 : 1.0;
+        uw = __builtin_amdgcn_readfirstlane(w == 0 ? 0 : w - 1);
         gm = w == 0 ? -1.0 : (w == 1 ? Ux : (w == 2 ? Uy : 0.0));
         dl = w == 0 ? Ux * nx + Uy * ny : 0.0;
         s_der = der ? 1.0 / (2.0 * a.f.dtau) : 0.0;
         s_val = der ? 0.0 : 1.0;
     }
-    // the five inputs at time row m (offset m * P from this panel)
+    // the five inputs at a time row, and component uw of u again (read from LDS: fewer instructions than
+    // its selection from the three)
     struct Raw {
-        TIn r, u1, u2, u3, p;
+        TIn r, u1, u2, u3, p, uw;
     };
-    __device__ __forceinline__ Raw load(int64_t off) const {
-        return Raw{rho[off], u[off], u[NP + off], u[2 * NP + off], pp[off]};
-    }
     __device__ __forceinline__ double X(const Raw &v) const {
         const double r = (double)v.r;
         const double u1 = (double)v.u1, u2 = (double)v.u2, u3 = (double)v.u3;
         const double un = u1 * nx + u2 * ny + u3 * nz;
-        const double bu = b1 * u1 + b2 * u2 + b3 * u3 - gm;
+        const double bu = b * (double)v.uw - gm;
         return al * (double)v.p + r * bu * un - dl;
     }
-    __device__ __forceinline__ double X(int64_t off) const { return X(load(off)); }
 };
 
 __device__ __forceinline__ uint16_t bf16_rne(float x) {
@@ -125,10 +122,14 @@ __device__ __forceinline__ void src_flush(const float *tile, TOut *coef, int64_t
 // and the back substitution from the top of that window, reduced right-hand
 // sides in registers, overwritten by the coefficients.  The block's inputs (5
 // variables x 32 panels per source-term row, rows R0 - 3 .. R0 + kSrcW + 2) are
-// loaded once, cooperatively, in groups of kSrcG rows by direct global -> LDS
-// copies into two buffers: group m + 1 is in flight while group m is used, one
-// barrier per group.  The four waves (four base quantities) read their inputs
-// from LDS (both half-waves read the same panel's row: a broadcast).
+// loaded once, cooperatively, in groups of G = kSrcG rows by direct global -> LDS
+// copies into three buffers: groups m + 1 and m + 2 are in flight while group m
+// is used, one barrier per group.  The four waves (four base quantities) read
+// their inputs from LDS (both half-waves read the same panel's row: a broadcast).
+// Bound by vector issue (about 60 % of the cycles) and memory latency behind it
+// (three blocks of 150 registers per CU): 18252 panels x 6535 frames, FP32 data,
+// 1.61 ms (6.3 GB, 3.9 TB/s), 1.77 ms with one group in flight and per-lane copy
+// addresses; 32768 x 2048, FP64 data, 1.23 ms (4.9 GB) against 1.44.
 //
 // GEN = false: interior chunk (every row in [kSrcPivotRows, N - 3]): central
 // differences, constant pivot, no end rows, no branches.  GEN = true: a chunk
@@ -139,16 +140,21 @@ __device__ __forceinline__ void src_flush(const float *tile, TOut *coef, int64_t
 // the end rules block-uniform predicates, so both kinds keep the right-hand
 // sides in registers.  The coefficients leave through a [kSrcTC / 4][kSrcRS]
 // LDS tile in four quarters.
-constexpr int kSrcG = 12;                       // rows per staged group
+// rows per staged group: three buffers of a group, the LDS tile and the end values leave room for three
+// blocks per CU
+template <typename TIn>
+constexpr int kSrcG = sizeof(TIn) == 8 ? 8 : 12;
 constexpr int kSrcNX = kSrcW + 6;               // source-term rows R0 - 3 .. R0 + kSrcW + 2
-constexpr int kSrcNG = (kSrcNX + kSrcG - 1) / kSrcG;
-constexpr int kSrcGV = kSrcG * 5 * kSrcPanels;  // values per group
+template <typename TIn>
+constexpr int kSrcNG = (kSrcNX + kSrcG<TIn> - 1) / kSrcG<TIn>;
+template <typename TIn>
+constexpr int kSrcGV = kSrcG<TIn> * 5 * kSrcPanels;  // values per group
 
 typedef __attribute__((address_space(3))) void *src_lds_ptr_t;
 
 // Direct global -> LDS copies of the staged groups.  Group m goes to
 // dst[var][r][panel]: variables [rho, u1, u2, u3, p'], source-term rows k =
-// m*kSrcG + r (record row R0 - 3 + k, clamped to [0, N-1]), panels pbase ..
+// m*G + r (record row R0 - 3 + k, clamped to [0, N-1]), panels pbase ..
 // pbase + 31.  A piece of 64 dwords (4 bytes per lane) is one (variable, row) in
 // FP64 and two rows of a variable in FP32; the lane's panel (clamped to P - 1),
 // dword half and row within the piece are fixed.  Wave wv issues the pieces wv,
@@ -157,7 +163,8 @@ template <typename TIn>
 struct SrcDma {
     static constexpr int DW = (int)sizeof(TIn) / 4;  // dwords per value
     static constexpr int RPP = 2 / DW;               // rows per piece
-    static constexpr int PPV = kSrcG / RPP;          // pieces per variable
+    static constexpr int G = kSrcG<TIn>;
+    static constexpr int PPV = G / RPP;          // pieces per variable
     static constexpr int NPIECE = 5 * PPV;
     static constexpr int NI = (NPIECE + 3) / 4;      // pieces per wave (at most)
     const unsigned char *vbase[NI];                  // variable base of piece i (uniform)
@@ -179,19 +186,31 @@ struct SrcDma {
     }
 
     // lane_row: row of this lane within a piece (0, or lane >> 5 in FP32);
-    // lane_off: byte offset of the lane's panel and dword half within a row
+    // lane_off: byte offset of the lane's panel and dword half within a row.
+    // CLAMP: rows outside the record are clamped, lane by lane.  Otherwise (interior chunks, all of whose
+    // rows are in the record) a piece is a uniform address and the lane's constant offset, no vector
+    // arithmetic (in FP32 that was a quarter of the kernel's); a piece of two rows of which the second is
+    // past the staged rows reads the first one twice.
+    template <bool CLAMP>
     __device__ __forceinline__ void issue(int m, TIn *dst, int wv, int lane_row, uint32_t lane_off, int64_t R0,
                                           int64_t N) const {
+        const uint32_t piece_off = (uint32_t)lane_row * (uint32_t)rowb + lane_off;
 #pragma unroll
         for (int i = 0; i < NI; ++i) {
             const int pc = wv + 4 * i;
-            const int k0 = m * kSrcG + r[i];
-            const bool go = (NPIECE % 4 == 0 || i + 1 < NI ? true : pc < NPIECE) && k0 < kSrcNX;
+            const int k0 = min(m * G + r[i], kSrcNX - 1);
+            const bool go = NPIECE % 4 == 0 || i + 1 < NI || pc < NPIECE;
             if (go) {
-                int64_t row = R0 - 3 + k0 + lane_row;
-                row = row < 0 ? 0 : (row > N - 1 ? N - 1 : row);
-                __builtin_amdgcn_global_load_lds((const void *)(vbase[i] + row * rowb + lane_off),
-                                                 (src_lds_ptr_t)((unsigned char *)dst + pc * 256), 4, 0, 0);
+                const unsigned char *src;
+                if constexpr (CLAMP) {
+                    int64_t row = R0 - 3 + k0 + lane_row;
+                    row = row < 0 ? 0 : (row > N - 1 ? N - 1 : row);
+                    src = vbase[i] + row * rowb + lane_off;
+                } else {
+                    src = vbase[i] + (R0 - 3 + k0) * rowb + ((m + 1) * G <= kSrcNX || k0 + RPP <= kSrcNX ? piece_off : lane_off);
+                }
+                __builtin_amdgcn_global_load_lds((const void *)src, (src_lds_ptr_t)((unsigned char *)dst + pc * 256), 4,
+                                                 0, 0);
             }
         }
     }
@@ -201,7 +220,7 @@ struct SrcDma {
 // the last (R0 + kSrcW >= N - 1); the rules of an end out of reach are compiled out (they would be
 // false at run time).
 template <typename TIn, typename TOut, bool GEN, int ENDS = 3>
-__device__ __forceinline__ void src_chunk(const SrcFwdArgs &a, int64_t pbk, int64_t i0, TIn *ring0, TIn *ring1,
+__device__ __forceinline__ void src_chunk(const SrcFwdArgs &a, int64_t pbk, int64_t i0, TIn *ring0, TIn *ring1, TIn *ring2,
                                           float *tile, double *endv) {
     constexpr bool kStart = (ENDS & 1) != 0, kEnd = (ENDS & 2) != 0;
     const int64_t P = a.P, N = a.N;
@@ -212,6 +231,8 @@ __device__ __forceinline__ void src_chunk(const SrcFwdArgs &a, int64_t pbk, int6
     const SrcLane<TIn> L(a, pc);
     using Raw = typename SrcLane<TIn>::Raw;
     const double cpi = 2.0 - sqrt(3.0);
+    // interior: the right-hand side's 6 and the pivot are in the scales of f
+    const double s_der = GEN ? L.s_der : 6.0 * cpi * L.s_der, s_val = GEN ? L.s_val : 6.0 * cpi * L.s_val;
     const int64_t R0 = i0 - 1 - kSrcH;
     // Exact Thomas pivots of tridiag(1, 4, 1) (GEN): c'_1 = 1/4, c'_n = 1/(4 - c'_{n-1}), from the
     // plan's table a.cp (a uniform load; equal to cpi to double precision past n = 30, so rows from
@@ -220,7 +241,9 @@ __device__ __forceinline__ void src_chunk(const SrcFwdArgs &a, int64_t pbk, int6
     auto pivot = [&](int rr) { return rr < 64 ? cpt[rr] : cpi; };
     // 32-bit copies for the block-uniform end rules (records are far below 2^31 frames)
     const int R0i = (int)R0, Ni = (int)N;
-    // two buffers of [rho, u1, u2, u3, p'] x kSrcG rows x 32 panels; group m in buffer m & 1
+    // three buffers of [rho, u1, u2, u3, p'] x G rows x 32 panels; group m in buffer m % 3
+    constexpr int G = kSrcG<TIn>, NG = kSrcNG<TIn>, VS = G * kSrcPanels;  // VS: variable stride
+    const int own = half * kSrcPanels + pl, own_uw = own + (1 + L.uw) * VS;
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     int lane_row;
     uint32_t lane_off;
@@ -232,7 +255,8 @@ __device__ __forceinline__ void src_chunk(const SrcFwdArgs &a, int64_t pbk, int6
         lane_off = (uint32_t)(min(pbase + (lane & 31), P - 1) * 4);
     }
     const SrcDma<TIn> dma(a, wv);
-    dma.issue(0, ring0, wv, lane_row, lane_off, R0, N);
+    dma.template issue<GEN>(0, ring0, wv, lane_row, lane_off, R0, N);
+    dma.template issue<GEN>(1, ring1, wv, lane_row, lane_off, R0, N);
     // reduced right-hand sides, then coefficients, of window rows s, in registers
     const int col = L.ch * 32 + pl;
     float dvr[kSrcW];
@@ -242,13 +266,18 @@ __device__ __forceinline__ void src_chunk(const SrcFwdArgs &a, int64_t pbk, int6
     double Xa = 0.0, Xb = 0.0, Xc = 0.0, Xd = 0.0, Xe = 0.0;
     double fprev = 0.0, dprev = 0.0, f0 = 0.0;
 #pragma unroll
-    for (int m = 0; m < kSrcNG; ++m) {
-        // this wave's copies of group m have landed; the barrier makes every wave's visible
-        // and frees the other buffer (group m - 1 has been read), which then receives m + 1
-        __builtin_amdgcn_s_waitcnt(0);
-        __syncthreads();
-        if (m + 1 < kSrcNG) dma.issue(m + 1, ((m + 1) & 1) ? ring1 : ring0, wv, lane_row, lane_off, R0, N);
-        const TIn *buf = (m & 1) ? ring1 : ring0;
+    for (int m = 0; m < NG; ++m) {
+        // this wave's copies of group m have landed (those of group m + 1 may be in flight); the barrier
+        // makes every wave's visible and frees the buffer of group m - 1, which receives group m + 2
+        constexpr int kAhead = SrcDma<TIn>::NPIECE / 4;  // copies of a group, of the wave with the fewest
+        if (m + 1 < NG) __builtin_amdgcn_s_waitcnt((kAhead & 15) | 0x70 | (kAhead >> 4) << 14);
+        else __builtin_amdgcn_s_waitcnt(0x70);
+        // (no __syncthreads: it waits for every copy in flight)
+        asm volatile("s_barrier" ::: "memory");
+        if (m + 2 < NG)
+            dma.template issue<GEN>(m + 2, (m + 2) % 3 == 0 ? ring0 : ((m + 2) % 3 == 1 ? ring1 : ring2), wv, lane_row,
+                                    lane_off, R0, N);
+        const TIn *buf = m % 3 == 0 ? ring0 : (m % 3 == 1 ? ring1 : ring2);
         // Rows go in pairs: lanes 0-31 compute X of row k, lanes 32-63 (the same panel and base
         // quantity) X of row k + 1, and one swap of the halves (v_permlane32_swap, per dword) gives
         // every lane both, so each source term is computed once instead of once per half.
@@ -263,13 +292,13 @@ __device__ __forceinline__ void src_chunk(const SrcFwdArgs &a, int64_t pbk, int6
                 const int n = R0i - 1 + it;
                 double fn;
                 if constexpr (!GEN) {
-                    fn = L.s_der * (Xd - Xb) + L.s_val * Xc;
+                    fn = s_der * (Xd - Xb) + s_val * Xc;
                 } else {
                     fn = 0.0;
                     if ((unsigned)n < (unsigned)Ni) {
                         const double dx = (kStart && n == 0) ? -3.0 * Xc + 4.0 * Xd - Xe
                                           : ((kEnd && n == Ni - 1) ? 3.0 * Xc - 4.0 * Xb + Xa : Xd - Xb);
-                        fn = L.s_der * dx + L.s_val * Xc;
+                        fn = s_der * dx + s_val * Xc;
                     }
                     if (kStart && n == 0) f0 = fn;
                     // f_{N-1} and (below) d_{N-2} wait in LDS for the end coefficients: held in
@@ -279,7 +308,7 @@ __device__ __forceinline__ void src_chunk(const SrcFwdArgs &a, int64_t pbk, int6
                 if (it >= 2) {
                     float dvs;
                     if constexpr (!GEN) {
-                        const double d = (6.0 * fprev - dprev) * cpi;
+                        const double d = fma(-cpi, dprev, fprev);
                         dprev = d;
                         dvs = (float)d;
                     } else {
@@ -305,12 +334,13 @@ __device__ __forceinline__ void src_chunk(const SrcFwdArgs &a, int64_t pbk, int6
             }
         };
 #pragma unroll
-        for (int r = 0; r < kSrcG; r += 2) {
-            const int k = m * kSrcG + r;
+        for (int r = 0; r < G; r += 2) {
+            const int k = m * G + r;
             if (k < kSrcNX) {
-                const TIn *rw = buf + (r + half) * kSrcPanels + pl;
-                constexpr int VS = kSrcG * kSrcPanels;  // variable stride
-                const Raw v{rw[0], rw[VS], rw[2 * VS], rw[3 * VS], rw[4 * VS]};
+                // (one integer offset from the buffer: through a longer chain of pointers the compiler no
+                // longer sees that the copies in flight go to other buffers, and waits for them here)
+                const int at = own + r * kSrcPanels, at_uw = own_uw + r * kSrcPanels;
+                const Raw v{buf[at], buf[at + VS], buf[at + 2 * VS], buf[at + 3 * VS], buf[at + 4 * VS], buf[at_uw]};
                 double Xm = L.X(v);
                 if constexpr (GEN) {
                     const int mrow = R0i - 3 + k + half;
@@ -372,18 +402,17 @@ __device__ __forceinline__ void src_chunk(const SrcFwdArgs &a, int64_t pbk, int6
 // separate arrays of the instantiations inlined into one kernel would add up.
 template <typename TIn, typename TOut>
 __device__ __forceinline__ void src_chunk_block(const SrcFwdArgs &a, int64_t pbk, int64_t k, bool interior) {
-    __shared__ TIn ring0[kSrcGV];
-    __shared__ TIn ring1[kSrcGV];
+    __shared__ TIn ring0[kSrcGV<TIn>], ring1[kSrcGV<TIn>], ring2[kSrcGV<TIn>];
     __shared__ float tile[(kSrcTC / 4) * kSrcRS];
     __shared__ double endv[2 * 256];  // f_{N-1}, d_{N-2} per thread
     const int64_t i0 = k * kSrcTC, R0 = i0 - 1 - kSrcH;
     if (interior) {
-        src_chunk<TIn, TOut, false>(a, pbk, i0, ring0, ring1, tile, endv);
+        src_chunk<TIn, TOut, false>(a, pbk, i0, ring0, ring1, ring2, tile, endv);
     } else {
         const bool s_in = R0 <= 3, e_in = R0 + kSrcW >= a.N - 1;
-        if (s_in && e_in) src_chunk<TIn, TOut, true, 3>(a, pbk, i0, ring0, ring1, tile, endv);
-        else if (e_in) src_chunk<TIn, TOut, true, 2>(a, pbk, i0, ring0, ring1, tile, endv);
-        else src_chunk<TIn, TOut, true, 1>(a, pbk, i0, ring0, ring1, tile, endv);
+        if (s_in && e_in) src_chunk<TIn, TOut, true, 3>(a, pbk, i0, ring0, ring1, ring2, tile, endv);
+        else if (e_in) src_chunk<TIn, TOut, true, 2>(a, pbk, i0, ring0, ring1, ring2, tile, endv);
+        else src_chunk<TIn, TOut, true, 1>(a, pbk, i0, ring0, ring1, ring2, tile, endv);
     }
 }
 
