@@ -256,7 +256,8 @@ __device__ __forceinline__ void gather_lds_body(const GatherArgs &a, int64_t t, 
     const PairRec *const rec_t = rec + tbase * P;
     const PairBf *const rbf_t = a.rbf + tbase * P;
     // issue the loads of the stage starting at panel ps into the stage buffer `base`
-    auto fill = [&](int64_t ps, unsigned char *base) {
+    auto fill = [&](auto nobs_c, int64_t ps, unsigned char *base) {
+        constexpr bool kFullRegs = decltype(nobs_c)::value == OPW;
         const int np = (int)(pe - ps < PT ? pe - ps : PT);
         for (int q = 0; q < np; ++q) {
             const int64_t p = ps + q;
@@ -279,8 +280,10 @@ __device__ __forceinline__ void gather_lds_body(const GatherArgs &a, int64_t t, 
         unsigned char *rbase = base + (size_t)PT * win_bytes;
         const int runits = np * TILE * 4;
         for (int ci = wv; ci * 64 < runits; ci += kLdsWaves) {
+            if (kTiles > 1 && ci % kTiles * kYTile > ot_last) continue;  // a tile without observers: not read
             int l = lane;
-            asm volatile("" : "+v"(l));  // not hoisted out of the panel loop: its registers are all in use
+            // not hoisted out of the panel loop where its registers are all in use
+            if constexpr (kFullRegs) asm volatile("" : "+v"(l));
             const int q = ci / kTiles, j = min(ci % kTiles * kYTile + (l >> 2), (int)ot_last), uu = l & 3;
             const int h = j & ~(kYTile - 1), c = min((int)(O - tbase) - h, kYTile), js = j & (kYTile - 1);
             const int at = uu < 2 ? 2 * js + uu : (uu == 2 ? kRecW / 4 * c + js : (kRecN0w * c) / 4 + (js >> 2));
@@ -293,7 +296,7 @@ __device__ __forceinline__ void gather_lds_body(const GatherArgs &a, int64_t t, 
             const int bunits = np * TILE * 2;
             for (int ci = wv; ci * 64 < bunits; ci += kLdsWaves) {
                 int u = ci * 64 + lane;
-                asm volatile("" : "+v"(u));
+                if constexpr (kFullRegs) asm volatile("" : "+v"(u));
                 u = u < bunits ? u : bunits - 1;
                 const int q = u / (TILE * 2), j = min((u - q * (TILE * 2)) >> 1, (int)ot_last);
                 const int h = j & ~(kYTile - 1), c = min((int)(O - tbase) - h, kYTile);
@@ -340,27 +343,28 @@ __device__ __forceinline__ void gather_lds_body(const GatherArgs &a, int64_t t, 
     nobs = __builtin_amdgcn_readfirstlane(nobs);
     int nsub = (int)((nt_wave - k0 + kLdsLanesOut - 1) / kLdsLanesOut);
     nsub = __builtin_amdgcn_readfirstlane(nsub < 0 ? 0 : (nsub > SUBW ? SUBW : nsub));
+    const int rec0 = PT * (int)win_bytes;  // the stage buffer's records
     // one panel of the stage for this wave's first NOBS observers, NSUB sub-rows.  The window
     // elements are addressed by one byte offset from the stage buffer `sb` (qb: the byte offset of
     // the lane's element in panel slot q's first channel group at n0 = lo; the pair record carries
     // n0 - lo in bytes; the second group is NW elements later): a longer chain of pointer
     // arithmetic hides from the compiler which of the two buffers a read touches, and it then makes
     // the read wait for the copies into the other one.
-    auto panel_work = [&](auto nobs_c, auto nsub_c, const float4 *lrec, const unsigned char *sb, int qb, int q) {
+    auto panel_work = [&](auto nobs_c, auto nsub_c, const unsigned char *sb, int qb, int q) {
         constexpr int NOBS = decltype(nobs_c)::value;
         constexpr int NSUB = decltype(nsub_c)::value;
 #pragma unroll
         for (int j = 0; j < NOBS; ++j) {
             const int slot = q * TILE + slot_of(j);
-            const float4 *R = lrec + slot * 4;
+            const float4 *R = reinterpret_cast<const float4 *>(sb + (rec0 + slot * 64));
             const float4 W = R[2];
-            const int b0 = qb + reinterpret_cast<const int *>(R + 3)[slot_of(j) & 3];
+            const int b0 = qb + *reinterpret_cast<const int *>(sb + (rec0 + slot * 64 + 48 + 4 * (slot_of(j) & 3)));
             const QT *P0 = reinterpret_cast<const QT *>(sb + b0);
             const QT *P1 = reinterpret_cast<const QT *>(sb + (b0 + NW * EB));
             float4 Ka, Kb;
             uint4 Kh, Kl;
             if constexpr (kBf) {
-                const uint4 *B = reinterpret_cast<const uint4 *>(lrec + PT * TILE * 4) + slot * 2;
+                const uint4 *B = reinterpret_cast<const uint4 *>(sb + (rec0 + PT * TILE * 64 + slot * 32));
                 Kh = B[0];
                 Kl = B[1];
             } else {
@@ -411,17 +415,16 @@ __device__ __forceinline__ void gather_lds_body(const GatherArgs &a, int64_t t, 
         constexpr int NSUB = decltype(nsub_c)::value;
         int cnt = 0;
         bool flushed = false;  // some chunk sum is already in the outputs
-        if (pb < pe) fill(pb, stA);
+        if (pb < pe) fill(nobs_c, pb, stA);
         // one stage from buffer `cur` while the next one is copied into `nxt`
         auto stage = [&](int64_t ps, const unsigned char *cur, unsigned char *nxt) __attribute__((always_inline)) {
             const int np = (int)(pe - ps < PT ? pe - ps : PT);
             __builtin_amdgcn_s_waitcnt(0);  // this wave's loads of stage ps have landed
             __syncthreads();                // ... and every wave's; the other buffer is free
-            if (ps + PT < pe) fill(ps + PT, nxt);
+            if (ps + PT < pe) fill(nobs_c, ps + PT, nxt);
             const unsigned char *base = cur;
-            const float4 *lrec = reinterpret_cast<const float4 *>(base + (size_t)PT * win_bytes);
             for (int q = 0; q < np; ++q) {
-                panel_work(nobs_c, nsub_c, lrec, base, (int)(q * win_bytes) + lane * EB, q);
+                panel_work(nobs_c, nsub_c, base, (int)(q * win_bytes) + lane * EB, q);
                 if (++cnt == kLdsChunk) {
 #pragma unroll
                     for (int j = 0; j < NOBS; ++j)
