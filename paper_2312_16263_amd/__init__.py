@@ -480,7 +480,8 @@ def autotune(batch: "Batch", candidates=None, bpc_candidates=None, reps=2, cache
             sub = Batch([batch.plans[i] for i in idx], [batch.inputs[i] for i in idx],
                         blocks_per_cu=batch.blocks_per_cu)
             table = []
-            for rows, iu in cands:
+            # a class too small for the matrix-core gather by itself runs the LDS-staged one: 4 rows only
+            for rows, iu in cands if sub.gather == "mfma" else sorted({(4, iu) for _, iu in cands}):
                 for j in range(len(idx)):
                     sub.tune_case(j, iu, rows, bind=False)
                 sub.bind()

@@ -122,3 +122,25 @@ def test_batched_matrix_core_gather_equals_single(mode):
     for c, plan, d, p in zip(cases, plans, inputs, batch.p_out):
         p_ref, _, nt = oracle_forward(c, *c.data())
         assert rel_l2(p.cpu().numpy(), p_ref, valid_mask(nt, p.shape[1])) <= TOL[mode]
+
+
+def test_autotune_of_a_batch_with_a_small_class():
+    """The batch is large enough for the matrix-core gather, its small class by itself is not."""
+    import torch
+    import paper_2312_16263_amd as fwh
+    surf = surfaces.sphere(1.0, 32, 64)
+    big = configs.Case("big", surf, surfaces.observer_circle(360, 10.0, step_deg=1.0), 0.4, 8.0, 1 / 64, 1700,
+                       kind="dipole", omega=2.0, data_dtype=np.float32)
+    cases = [big, _case(16, 306)]
+    plans = [make_plan(c, "f32") for c in cases]
+    batch = fwh.Batch(plans, [tuple(to_device(c.data(), torch.float32)) for c in cases])
+    assert batch.gather == "mfma"
+    batch.forward()
+    torch.cuda.synchronize()
+    before = [p.clone() for p in batch.p_out]
+    res = fwh.autotune(batch, candidates=[(4, 1e6), (3, 1e6), (2, 1e7)], bpc_candidates=(2,), reps=1)
+    assert len(res["classes"]) == 2
+    batch.forward()
+    torch.cuda.synchronize()
+    for a, b in zip(batch.p_out, before):  # other panel ranges: FP32 rounding of the partial sums
+        assert rel_l2(a.double().cpu().numpy(), b.double().cpu().numpy()) <= 1e-6
