@@ -57,14 +57,14 @@ def measured_traffic(kernel, path=TRAFFIC_PROFILE):
     return total if found else None
 
 
-GATHER_KERNELS = {"lds": "gather_lds_kernel", "stream": "gather_stream_kernel", "mfma": "gather_mfma_kernel",
+GATHER_KERNELS = {"lds": "gather_lds_kernel", "stream": "gather_stream_kernel", "mfma": "gather_y_kernel",
                   "direct": "gather_tuned_kernel"}
 
 
 def gather_kernel(plan, mode):
     """Name of the forward gather kernel the plan runs, as the traffic summaries list it."""
     kind = plan.info()[0]
-    name = GATHER_KERNELS.get(kind, "gather_f64_kernel")
+    name = GATHER_KERNELS.get(kind, "gather64_kernel")
     if kind in ("lds", "stream", "mfma"):
         name += "<float>" if mode == "f32" else "<unsigned short>"
     return name
@@ -604,7 +604,7 @@ def main():
     # source stage: HBM-bound streaming (inputs read once, coefficients written once)
     NS = ((c.n_tau + 12 + 63) // 64) * 64
     src_bytes = 5 * 8 * c.n_panels * c.n_tau + 8 * 4 * c.n_panels * NS
-    src = {"bound": "hbm", "kernel": "src_interior_kernel + src_general_kernel", "achieved": src_bytes / (avg["source"] * 1e-3) / 1e9,
+    src = {"bound": "hbm", "kernel": "src_kernel", "achieved": src_bytes / (avg["source"] * 1e-3) / 1e9,
            "peak": HBM_PEAK / 1e9, "unit": "GB/s", "algorithmic_bytes": src_bytes, "avg_launch_ms": avg["source"]}
     src["frac"] = src["achieved"] * 1e9 / HBM_PEAK
 

@@ -118,19 +118,22 @@ int fwh_setup(fwh_plan *plan, void *workspace, size_t workspace_bytes, void *str
 
 /* Launch choices of the FP32/BF16 forward gather, for tests and measurements
  * (the defaults pick by themselves).  gather: FWH_GATHER_AUTO (the first of
- * STREAM, LDS, MFMA, DIRECT that applies), FWH_GATHER_STREAM (whole coefficient
+ * STREAM, MFMA, LDS, DIRECT that applies; MFMA up to a spread of 450 samples over
+ * 16 observers; in FWH_MODE_BF16 calls with FP64 data run LDS in its place; up to
+ * 8 observers on a small surface run a form of STREAM with the same sums),
+ * FWH_GATHER_STREAM (whole coefficient
  * rows of each panel staged once, two waves per observer: at most 8 observers
  * and 32 x 61 samples per observer; for cases bound by HBM), FWH_GATHER_LDS
  * (coefficient windows of a 32-observer tile staged in LDS; needs one panel's
  * window over a tile to fit), FWH_GATHER_MFMA (channel combine on the matrix
- * cores for 32 observers x 16 samples at a time, then the taps; needs a tile's
- * delay-index spread below about 260 samples) or FWH_GATHER_DIRECT (direct
+ * cores for 16 observers x 16 samples at a time, then the taps; asked for by name
+ * it needs a delay-index spread of at most 265 samples over 32 observers) or FWH_GATHER_DIRECT (direct
  * loads); STREAM, LDS and MFMA make fwh_setup fail with FWH_EINVAL when they do
  * not apply.
  * splits: number of panel ranges summed separately and then added in fixed
  * order (0: chosen by fwh_setup to fill whole rounds of resident workgroups;
  * else 1 .. min(256, ceil(P/128)), FWH_ESIZE beyond).  Every choice gives the
- * same sums up to FP32 rounding order.  Host only; takes effect at the next
+ * same sums up to FP32 rounding order (LDS and MFMA the same bits in FP32 storage).  Host only; takes effect at the next
  * fwh_setup, which must follow (until it does, forward and adjoint calls fail
  * with FWH_ESTATE).  FWH_EINVAL for an unknown variant, or for any choice but
  * (AUTO, 0) in FWH_MODE_F64. */
@@ -213,13 +216,15 @@ int fwh_batch_tune(fwh_batch *batch, double item_units, int32_t blocks_per_cu);
 /* Host only: tiles of one case for the next fwh_batch_bind: target work per
  * forward item (<= 0 keeps the batch's) and rows of 61 samples per block of
  * the matrix-core gather (2..4; 4 only when the batch uses the LDS-staged
- * gather).  Shorter blocks waste fewer rows past short windows and cost more
+ * gather, fwh_batch_gather).  Shorter blocks waste fewer rows past short windows and cost more
  * window overlap; the autotuner of the Python binding picks both per class of
  * case sizes. */
 int fwh_batch_tune_case(fwh_batch *batch, int32_t case_index, double item_units, int32_t rows);
-/* The forward gather the batch runs for all its cases: FWH_GATHER_LDS when
- * every case's windows fit it, unless every plan was tuned to FWH_GATHER_MFMA
- * (fwh_plan_tune); FWH_GATHER_MFMA when only it fits them all. */
+/* The forward gather the batch runs for all its cases: FWH_GATHER_MFMA when every
+ * plan would take it by itself, the batch holds at least 1e9
+ * panel-observer-samples and its data are FP32 or its storage is; or when every
+ * plan was tuned to it (fwh_plan_tune), or only it fits them all; else
+ * FWH_GATHER_LDS. */
 int fwh_batch_gather(const fwh_batch *batch, int32_t *gather);
 /* Build the work list and upload descriptors and list into the workspace
  * (>= workspace_bytes, 256-byte aligned) on `stream`; synchronises `stream`. */
