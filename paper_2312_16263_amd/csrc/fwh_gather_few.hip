@@ -7,7 +7,7 @@
 // samples of one split, so the same splits run on 7 x 8 times as many waves, and loads its
 // coefficients itself, kFewAhead panels ahead, from L2 (every observer's windows again: the reason not
 // to use it where the coefficients outgrow the caches).  The splits, and the order of every sum, are the streaming
-// gather's: the two give the same results bit for bit.
+// gather's: the two give the same results bit for bit.  28 us for that surface.
 #include <type_traits>
 
 #include "fwh_internal.h"
@@ -27,7 +27,7 @@ __device__ __forceinline__ float next_lane(float x) {
 }
 
 // One panel of one row, FP32: g = sum_c K_c coef_c, then the four taps into one accumulator.  rec: dword
-// lane % 16 of the pair's record in every row of 16 lanes (K_0 .. K_7, w_0 .. w_3, n0), read as the
+// lane % 16 of the pair's record in every row of 16 lanes (K_0 .. K_7, w_0 .. w_3, n0w, n0), read as the
 // broadcast DPP source of each FMA.  A DPP read needs two wait states after a VALU write of its source
 // (s_nop: rec may come from a register copy, g and its shifts are written here).
 __device__ __forceinline__ void few_panel(float &acc, float rec, uintx4 a, uintx4 b) {
