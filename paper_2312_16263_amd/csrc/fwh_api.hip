@@ -84,6 +84,9 @@ struct fwh_plan {
     template <typename T>
     T *at(size_t off) const { return reinterpret_cast<T *>(ws + off); }
     void *scratch() const { return off_scr == SIZE_MAX ? nullptr : ws + off_scr; }
+    // FP64 form: two words in place of the delay extremes, which fwh_setup has read: the widest tile window
+    // (setup) and the source stages' mark of values that are not finite
+    int *spoiled() const { return at<int>(off_dmm) + 1; }
     fwh::PairBf *rbf() const { return mode == FWH_MODE_BF16 ? at<fwh::PairBf>(off_rbf) : nullptr; }
 };
 
@@ -342,7 +345,7 @@ int fwh_setup(fwh_plan *pl, void *workspace, size_t workspace_bytes, void *strea
         // widest window over a tile of observers -> the gather's LDS tile (the delay extremes have been read)
         int *width = pl->at<int>(pl->off_dmm);
         int w = 0;
-        if ((e = hipMemsetAsync(width, 0, sizeof(int), st)) ||
+        if ((e = hipMemsetAsync(width, 0, 2 * sizeof(int), st)) ||
             (e = fwh::launch_spread64(pl->at<int32_t>(pl->off_N0), P, O, width, st)) ||
             (e = hipMemcpyAsync(&w, width, sizeof(int), hipMemcpyDeviceToHost, st)) || (e = hipStreamSynchronize(st)))
             return hip_fail("fwh_setup: read-back of the tile windows", e);
@@ -538,7 +541,7 @@ int fwh_forward(fwh_plan *pl, int32_t in_dtype, const void *rho, const void *u, 
         StageScope sc(pl, FWH_STAGE_SOURCE, st);
         e = coef_type == 0
                 ? fwh::launch_source64(in_dtype == FWH_F64 ? 0 : 1, rho, u, pp, pl->at<double>(pl->off_n), pl->P, pl->N,
-                                       pl->NS, pl->flow, pl->at<double>(pl->off_cp), pl->scratch(),
+                                       pl->NS, pl->flow, pl->at<double>(pl->off_cp), pl->scratch(), pl->spoiled(),
                                        pl->ws + pl->off_coef, st)
                 : fwh::launch_source(in_dtype == FWH_F64 ? 0 : 1, coef_type, rho, u, pp, pl->at<double>(pl->off_n),
                                      pl->P, pl->N, pl->NS, pl->flow, pl->at<double>(pl->off_cp),
@@ -551,7 +554,7 @@ int fwh_forward(fwh_plan *pl, int32_t in_dtype, const void *rho, const void *u, 
         e = fwh::launch_gather64(pl->at<double>(pl->off_K64), pl->at<double>(pl->off_W64),
                                  pl->at<int32_t>(pl->off_N0), pl->at<int32_t>(pl->off_nt),
                                  pl->at<double>(pl->off_coef), pl->P, pl->O, pl->NS, pl->n_t_max, pl->w16, pl->splits,
-                                 pl->at<double>(pl->off_scr), static_cast<double *>(p_out), st);
+                                 pl->at<double>(pl->off_scr), pl->spoiled(), static_cast<double *>(p_out), st);
     } else {
         const int kind = forward_gather(pl, in_dtype);
         {
@@ -631,7 +634,8 @@ int fwh_adjoint(fwh_plan *pl, int32_t in_dtype, const void *rho, const void *u, 
         StageScope sc(pl, FWH_STAGE_SOURCE_ADJ, st);
         e = f64 ? fwh::launch_source_adjoint64(in_dtype == FWH_F64 ? 0 : 1, pl->ws + pl->off_coef, rho, u,
                                                pl->at<double>(pl->off_n), pl->P, pl->N, pl->NS, pl->flow,
-                                               pl->at<double>(pl->off_cp), pl->scratch(), g_rho, g_u, g_p, st)
+                                               pl->at<double>(pl->off_cp), pl->scratch(), pl->spoiled(), g_rho, g_u,
+                                               g_p, st)
                 : fwh::launch_source_adjoint(in_dtype == FWH_F64 ? 0 : 1, pl->ws + pl->off_coef, rho, u,
                                              pl->at<double>(pl->off_n), pl->P, pl->N, pl->NS, pl->flow,
                                              pl->at<double>(pl->off_cp), g_rho, g_u, g_p, st);

@@ -5,7 +5,10 @@
 // recurrence started kF64H rows outside its chunk with zero is off by (2 - sqrt 3)^kF64H = 7e-18 of
 // the local values at the chunk's edge, below FP64 rounding; a chunk within kF64H rows of a record
 // end starts at the end and is exact.  (One thread per whole record left a 2048-panel, 512-frame
-// surface with 256 waves and a serial chain of 512 rows: 420 us forward.)
+// surface with 256 waves and a serial chain of 512 rows: 420 us forward.)  A value that is not finite stays
+// in a recurrence to its end, and so in every coefficient of its (panel, channel): a sweep whose
+// last row is not finite sets *spoiled, and the back substitutions, only when it is set, look at the last row
+// of every chunk.  The last launch of the call clears it again.
 //
 // Gathers: the forward one as in fwh_gather_mfma.hip (channel combine by v_mfma_f64_16x16x4f64 for a
 // tile of 16 observers, taps on the vector ALU after a pass through LDS); the transposed one with the
@@ -61,7 +64,7 @@ struct SrcTerm {
 // Block = the 4 channels of one group (a wave each) for 64 panels, rows [r0, r0 + T) of the system rows
 // 1 .. N-2: reduced right-hand sides d_r -> scr[channel][r][p] (time-major).
 template <typename TIn>
-__global__ __launch_bounds__(256) void src64_sweep_kernel(SrcFwdArgs a, int T) {
+__global__ __launch_bounds__(256) void src64_sweep_kernel(SrcFwdArgs a, int T, int *spoiled) {
     const int64_t P = a.P, N = a.N;
     const int lane = threadIdx.x & 63, ch = (int)blockIdx.y * 4 + (int)(threadIdx.x >> 6);
     const bool deriv = channel_deriv(ch);
@@ -95,12 +98,21 @@ __global__ __launch_bounds__(256) void src64_sweep_kernel(SrcFwdArgs a, int T) {
             }
         }
     }
+    if (!__builtin_isfinite(dprev)) *spoiled = 1;
+}
+
+// Whether the forward sweep of some chunk of T rows met a value that is not finite (scr: the channel's
+// reduced right-hand sides of one panel, [N][P])
+__device__ __forceinline__ bool record_spoiled(const double *scr, int64_t P, int64_t N, int T) {
+    bool bad = false;
+    for (int64_t r = T; r < N - 2; r += T) bad |= !__builtin_isfinite(scr[r * P]);
+    return bad | !__builtin_isfinite(scr[(N - 2) * P]);
 }
 
 // Back substitution of the storage indices [i0, i0 + T) (index i: coefficient c_{i-1}; past N + 1:
 // zero), coefficients out panel-major with the 4 channels of a group interleaved, through LDS.
 template <typename TIn>
-__global__ __launch_bounds__(256) void src64_back_kernel(SrcFwdArgs a, int T) {
+__global__ __launch_bounds__(256) void src64_back_kernel(SrcFwdArgs a, int T, const int *__restrict__ spoiled) {
     constexpr int CH = 16, RS = CH * 4 + 1;
     __shared__ double stage[64 * RS];
     const int64_t P = a.P, N = a.N, NS = a.NS;
@@ -111,6 +123,7 @@ __global__ __launch_bounds__(256) void src64_back_kernel(SrcFwdArgs a, int T) {
     const double *__restrict__ cp = a.cp;
     const double *scr = static_cast<const double *>(a.scr) + (int64_t)ch * N * P + pc;
     double *coef = static_cast<double *>(a.coef);
+    const double x_above = *spoiled && record_spoiled(scr, P, N, T) ? __builtin_nan("") : 0.0;
     double f0 = 0.0, fN1 = 0.0, xN2 = 0.0;
     if (i0 == 0 || i1 > N) {
         const SrcTerm<TIn> X(a, pc, channel_base(ch));
@@ -118,11 +131,11 @@ __global__ __launch_bounds__(256) void src64_back_kernel(SrcFwdArgs a, int T) {
         if (i0 == 0) f0 = X.first(deriv, i2h);
         if (i1 > N) {
             fN1 = X.last(N, deriv, i2h);
-            xN2 = scr[(N - 2) * P];
+            xN2 = scr[(N - 2) * P] + x_above;
         }
     }
     // x_r = d_r - cp_r x_{r+1} (x_{N-1} = 0) from kF64H rows above the chunk
-    double x = 0.0;
+    double x = x_above;
     constexpr int PF = 8;
     const int64_t above = i1 - 1;  // first row past the chunk's
     for (int64_t rb = min<int64_t>(N - 2, above + kF64H - 1); rb >= above; rb -= PF) {
@@ -172,7 +185,7 @@ __global__ __launch_bounds__(256) void src64_back_kernel(SrcFwdArgs a, int T) {
 //   fbar_r = 6 z_r (r = 1 .. N-2), fbar_0 = a_0 + 2 a_{-1} - z_1, fbar_{N-1} = a_{N-1} + 2 a_N - z_{N-2}.
 // Forward sweep of rows [r0, r0 + T) into scr [8][N][P]; rows 0 and N-1 of scr take the end terms
 // a_0 + 2 a_{-1} and a_{N-1} + 2 a_N.
-__global__ __launch_bounds__(256) void adj64_sweep_kernel(PreAdjArgs a, int T) {
+__global__ __launch_bounds__(256) void adj64_sweep_kernel(PreAdjArgs a, int T, int *spoiled) {
     constexpr int CH = 16;
     __shared__ double stage[4][64][CH + 1];
     const int64_t P = a.P, N = a.N, NS = a.NS;
@@ -210,18 +223,20 @@ __global__ __launch_bounds__(256) void adj64_sweep_kernel(PreAdjArgs a, int T) {
             }
         }
     }
+    if (!__builtin_isfinite(dprev)) *spoiled = 1;
 }
 
 // Back substitution of rows [r0, r0 + T): fbar time-major into out [8][N][P].
 __global__ __launch_bounds__(256) void adj64_back_kernel(const double *__restrict__ scr_all, const double *__restrict__ cp,
-                                                         int64_t P, int64_t N, int T, double *__restrict__ out_all) {
+                                                         int64_t P, int64_t N, int T, const int *__restrict__ spoiled,
+                                                         double *__restrict__ out_all) {
     const int64_t p = (int64_t)blockIdx.x * 64 + (threadIdx.x & 63);
     if (p >= P) return;
     const int64_t ch = (int64_t)blockIdx.y * 4 + (threadIdx.x >> 6);
     const double *scr = scr_all + ch * N * P + p;
     double *out = out_all + ch * N * P + p;
     const int64_t r0 = 1 + (int64_t)blockIdx.z * T, r1 = min<int64_t>(N - 2, r0 + T - 1);
-    double z = 0.0;
+    double z = *spoiled && record_spoiled(scr, P, N, T) ? __builtin_nan("") : 0.0;
     constexpr int PF = 8;
     for (int64_t rb = min<int64_t>(N - 2, r1 + kF64H); rb >= r0; rb -= PF) {
         double d[PF];
@@ -247,8 +262,9 @@ __global__ __launch_bounds__(256) void adj64_back_kernel(const double *__restric
 //   drho = u.n (Qbar + Lbar.w),  du = rho n (Qbar + Lbar.w) + rho u.n Lbar,
 //   dp' = Lbar.n,  with w = u - U0.
 template <typename TIn>
-__global__ __launch_bounds__(256) void source_adj_chain_kernel(ChainArgs a) {
+__global__ __launch_bounds__(256) void source_adj_chain_kernel(ChainArgs a, int *spoiled) {
     const int64_t bx = blockIdx.x, n = blockIdx.y;
+    if (bx == 0 && n == 0 && threadIdx.x == 0) *spoiled = 0;
     const double *__restrict__ scr = static_cast<const double *>(a.scr);
     const TIn *__restrict__ rho = static_cast<const TIn *>(a.rho);
     const TIn *__restrict__ u = static_cast<const TIn *>(a.u);
@@ -352,6 +368,7 @@ struct Gather64Args {
     int64_t P, O, NS, nt_max, p_chunk;
     int YR, splits;
     double *partial;  // [splits][O][nt_max]; the output itself when splits == 1
+    int *spoiled;     // the source stage's mark, cleared here
 };
 
 // 64 coefficient indices of both channel groups; lane l = 16 r + i: index 16 r + 4 (i & 3) + (i >> 2),
@@ -532,6 +549,7 @@ __device__ __forceinline__ void gather64_panels(const Gather64Args &a, int64_t t
 __global__ __launch_bounds__(kY64Waves * 64) __attribute__((amdgpu_waves_per_eu(3))) void gather64_kernel(
     Gather64Args a, int64_t tiles, int64_t kblocks) {
     extern __shared__ __align__(16) double ysm64[];
+    if (blockIdx.x == 0 && threadIdx.x == 0) *a.spoiled = 0;
     const int64_t L = xcd_block(blockIdx.x, gridDim.x);
     const int64_t t = L % tiles, rest = L / tiles;
     const int64_t k0 = rest % kblocks * kLdsK, z = rest / kblocks, tbase = t * kYTile;
@@ -574,6 +592,7 @@ __global__ __launch_bounds__(256) void reduce64_kernel(const double *__restrict_
 
 // Windows too wide for the LDS tile: one thread per (observer, sample), loop over panels.
 __global__ __launch_bounds__(256) void gather64_wide_kernel(Gather64Args a, int64_t kblocks) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) *a.spoiled = 0;
     const int64_t o = blockIdx.x / kblocks;
     const int64_t k = (blockIdx.x - o * kblocks) * blockDim.x + threadIdx.x;
     if (k >= a.nt_max) return;
@@ -719,48 +738,49 @@ hipError_t launch_spread64(const int32_t *N0, int64_t P, int64_t O, int *width, 
 }
 
 hipError_t launch_source64(int in_dtype, const void *rho, const void *u, const void *pp, const double *normal, int64_t P,
-                           int64_t N, int64_t NS, Flow f, const double *cp, void *scratch, void *coef,
+                           int64_t N, int64_t NS, Flow f, const double *cp, void *scratch, int *spoiled, void *coef,
                            hipStream_t stream) {
     const SrcFwdArgs a{rho, u, pp, normal, P, N, NS, f, cp, scratch, coef};
     const int T = chunk_frames(P, N);
     const unsigned pb = (unsigned)((P + 63) / 64);
     const dim3 g1(pb, 2, (unsigned)((N - 2 + T - 1) / T)), g2(pb, 2, (unsigned)((NS + T - 1) / T)), b(256);
-    if (in_dtype == 0) src64_sweep_kernel<double><<<g1, b, 0, stream>>>(a, T);
-    else src64_sweep_kernel<float><<<g1, b, 0, stream>>>(a, T);
+    if (in_dtype == 0) src64_sweep_kernel<double><<<g1, b, 0, stream>>>(a, T, spoiled);
+    else src64_sweep_kernel<float><<<g1, b, 0, stream>>>(a, T, spoiled);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    if (in_dtype == 0) src64_back_kernel<double><<<g2, b, 0, stream>>>(a, T);
-    else src64_back_kernel<float><<<g2, b, 0, stream>>>(a, T);
+    if (in_dtype == 0) src64_back_kernel<double><<<g2, b, 0, stream>>>(a, T, spoiled);
+    else src64_back_kernel<float><<<g2, b, 0, stream>>>(a, T, spoiled);
     return hipGetLastError();
 }
 
 hipError_t launch_source_adjoint64(int in_dtype, void *cbar, const void *rho, const void *u, const double *normal,
-                                   int64_t P, int64_t N, int64_t NS, Flow f, const double *cp, void *scratch, void *g_rho,
-                                   void *g_u, void *g_p, hipStream_t stream) {
+                                   int64_t P, int64_t N, int64_t NS, Flow f, const double *cp, void *scratch, int *spoiled,
+                                   void *g_rho, void *g_u, void *g_p, hipStream_t stream) {
     const PreAdjArgs pa{cbar, P, N, NS, cp, scratch};
     const int T = chunk_frames(P, N);
     const dim3 g((unsigned)((P + 63) / 64), 2, (unsigned)((N - 2 + T - 1) / T)), b(256);
-    adj64_sweep_kernel<<<g, b, 0, stream>>>(pa, T);
+    adj64_sweep_kernel<<<g, b, 0, stream>>>(pa, T, spoiled);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     // fbar [8][N][P] takes the place of the coefficient adjoints (NS >= N), which the sweep has read
-    adj64_back_kernel<<<g, b, 0, stream>>>(static_cast<const double *>(scratch), cp, P, N, T, static_cast<double *>(cbar));
+    adj64_back_kernel<<<g, b, 0, stream>>>(static_cast<const double *>(scratch), cp, P, N, T, spoiled,
+                                          static_cast<double *>(cbar));
     if ((e = hipGetLastError()) != hipSuccess) return e;
     const ChainArgs ca{cbar, rho, u, normal, P, N, f, g_rho, g_u, g_p};
     const dim3 gc((unsigned)((P + 255) / 256), (unsigned)N);
-    if (in_dtype == 0) source_adj_chain_kernel<double><<<gc, b, 0, stream>>>(ca);
-    else source_adj_chain_kernel<float><<<gc, b, 0, stream>>>(ca);
+    if (in_dtype == 0) source_adj_chain_kernel<double><<<gc, b, 0, stream>>>(ca, spoiled);
+    else source_adj_chain_kernel<float><<<gc, b, 0, stream>>>(ca, spoiled);
     return hipGetLastError();
 }
 
 hipError_t launch_gather64(const double *K64, const double *W64, const int32_t *N0, const int32_t *nt,
                            const double *coef, int64_t P, int64_t O, int64_t NS, int64_t nt_max, int w16, int splits,
-                           double *partial, double *out, hipStream_t stream) {
+                           double *partial, int *spoiled, double *out, hipStream_t stream) {
     const bool tiled = gather64_tiled(w16);
     if (!tiled) splits = 1;
     const int64_t p_chunk = (P + splits - 1) / splits;
     const Gather64Args a{K64, W64, N0, nt, coef, P, O, NS, nt_max, p_chunk, gather64_y_row(w16), splits,
-                         splits == 1 ? out : partial};
+                         splits == 1 ? out : partial, spoiled};
     if (!tiled) {
         const int64_t kb = (nt_max + 255) / 256;
         gather64_wide_kernel<<<dim3((unsigned)(kb * O)), dim3(256), 0, stream>>>(a, kb);

@@ -265,14 +265,15 @@ hipError_t launch_source(int in_dtype, int coef_type, const void *rho, const voi
                          const double *normal, int64_t P, int64_t N, int64_t NS, Flow f, const double *cp, void *coef,
                          hipStream_t stream);
 
-// Plain FP64 form (fwh_f64.hip).  scratch: [8][N][P] doubles.
+// Plain FP64 form (fwh_f64.hip).  scratch: [8][N][P] doubles.  spoiled: a device word, zero between calls, in
+// which the sweeps of a source stage (or its adjoint) mark that a value is not finite.
 hipError_t launch_source64(int in_dtype, const void *rho, const void *u, const void *pp, const double *normal, int64_t P,
-                           int64_t N, int64_t NS, Flow f, const double *cp, void *scratch, void *coef,
+                           int64_t N, int64_t NS, Flow f, const double *cp, void *scratch, int *spoiled, void *coef,
                            hipStream_t stream);
 // coefficient adjoints cbar [8][P][NS] (overwritten) -> gradients (time-major, in_dtype)
 hipError_t launch_source_adjoint64(int in_dtype, void *cbar, const void *rho, const void *u, const double *normal,
-                                   int64_t P, int64_t N, int64_t NS, Flow f, const double *cp, void *scratch, void *g_rho,
-                                   void *g_u, void *g_p, hipStream_t stream);
+                                   int64_t P, int64_t N, int64_t NS, Flow f, const double *cp, void *scratch, int *spoiled,
+                                   void *g_rho, void *g_u, void *g_p, hipStream_t stream);
 // *width (zeroed by the caller) = widest spread of n0 over a tile of kYTile observers
 hipError_t launch_spread64(const int32_t *N0, int64_t P, int64_t O, int *width, hipStream_t stream);
 // resident blocks per CU of the tiled gather; 0: windows too wide for it (one launch over all panels)
@@ -280,7 +281,7 @@ int gather64_blocks_per_cu(int w16);
 // splits > 1: panel ranges summed separately into partial [splits][O][nt_max] doubles, then added
 hipError_t launch_gather64(const double *K64, const double *W64, const int32_t *N0, const int32_t *nt,
                            const double *coef, int64_t P, int64_t O, int64_t NS, int64_t nt_max, int w16, int splits,
-                           double *partial, double *out, hipStream_t stream);
+                           double *partial, int *spoiled, double *out, hipStream_t stream);
 // pad (pad_bytes): room for a zero-padded copy of gbar, O x adj_pad_row(N, NS) doubles (else a slower form)
 hipError_t launch_adj_gather64(const double *K64, const double *W64, const int32_t *N0, const int32_t *nt,
                                const double *gbar, int64_t P, int64_t O, int64_t N, int64_t NS, int64_t nt_max,
