@@ -227,7 +227,9 @@ __global__ __launch_bounds__(256) void gm_prefilter_kernel(double *coef, int64_t
 // The same for records whose rows a block can hold in LDS (N <= kPsMaxN): every coefficient is read and
 // written once.  A block takes `nr` rows; thread (row, segment of kPsT frames) runs the two recurrences
 // over its segment from kPsH frames outside it, started with zero ((2 - sqrt 3)^30 = 7e-18 of the local
-// values is left of that at the segment) or at the record's end, where they are exact.  One position of
+// values is left of that at the segment) or at the record's end, where they are exact.  A value that is not
+// finite stays in a recurrence to its end, so in every coefficient of the row: a segment that ends its
+// forward recurrence on one marks its row.  One position of
 // padding per segment keeps the threads' reads, kPsT positions apart, on different banks.  Memory bound
 // otherwise: 155648 rows of 1024 frames, 0.85 ms, against 1.54 ms by chunks (each read and written twice).
 constexpr int kPsT = 32, kPsH = 30, kPsMaxN = 256 * kPsT + 2;
@@ -238,12 +240,14 @@ __global__ __launch_bounds__(256) void gm_prefilter_rows_kernel(double *coef, in
                                                               const double *__restrict__ inv_beta) {
     extern __shared__ double lds[];
     __shared__ double ib[kGmPivots];
+    __shared__ int spoiled[256];  // by row
     const int tid = threadIdx.x, NS = N + 2, RS = ps_at(NS) + 1, nseg = ps_segments(N);
     const int64_t r0 = (int64_t)blockIdx.x * nr;
     const int nrow = (int)min<int64_t>(nr, rows - r0);
     double *const base = coef + r0 * NS;
     const int total = nrow * NS;
     if (tid < kGmPivots) ib[tid] = inv_beta[tid];
+    spoiled[tid] = 0;
     for (int i0 = tid; i0 < total; i0 += 256 * 8) {
         double v[8];
 #pragma unroll
@@ -277,6 +281,7 @@ __global__ __launch_bounds__(256) void gm_prefilter_rows_kernel(double *coef, in
         if (n0 + i <= n1) forward(n0 + i);
         x[i] = d;
     }
+    if (active && !__builtin_isfinite(d)) spoiled[row] = 1;
     __syncthreads();
     if (active) {
 #pragma unroll
@@ -284,7 +289,7 @@ __global__ __launch_bounds__(256) void gm_prefilter_rows_kernel(double *coef, in
             if (n0 + i <= n1) f[ps_at(n0 + i + 1)] = x[i];
     }
     __syncthreads();
-    double c = 0.0;
+    double c = active && spoiled[row] ? __builtin_nan("") : 0.0;
     for (int n = min(N - 2, n1 + kPsH); n > n1; --n) c = f[ps_at(n + 1)] - c * pivot(n);
 #pragma unroll
     for (int i = kPsT - 1; i >= 0; --i) {

@@ -6,8 +6,10 @@ whole one gives, here the oracle: not the undefined values near the frame alone.
 import numpy as np
 import pytest
 
+import oracle
 from gpu_common import make_plan, oracle_adjoint, oracle_forward, to_device, valid_mask
-from workloads import configs, surfaces
+from test_gpu_gm import _run_gpu
+from workloads import configs, motion, surfaces
 
 pytestmark = pytest.mark.gpu
 
@@ -60,3 +62,22 @@ def test_fp64_adjoint(sample, value):
         assert not torch.isfinite(a).any()
     for a, b in zip(plan.adjoint(*d, 2 * p), good):
         assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("N,frame,panel", [(131, 0, 0), (131, 70, 14), (131, 130, 3), (34, 20, 7), (700, 400, 9)])
+@pytest.mark.parametrize("value", [np.nan, np.inf])
+def test_general_motion(N, frame, panel, value):
+    body = surfaces.sphere(1.0, 3, 5)
+    dtau = max(1 / 64, 2.0 / N)
+    ms = motion.moving_surface(body, "orbit", N, dtau, 0.1, spin=0.5)
+    rho, u, pp = motion.quiescent_monopole_series(ms, 0.3, 0.01, 6.0, dtau, 0.1, source=(0.05, 0.02, 0.0))
+    rho = rho.copy()
+    rho[frame, panel] = value
+    x = np.array([[9.0, 2.0, 1.0], [-7.0, 5.0, -2.0]])
+    print(f"[nonfinite] general motion N={N} frame={frame} panel={panel} {value}", flush=True)
+    ref, _, nt = oracle.gm_forward(ms, x, 0.3, dtau, 0.1, rho, u, pp)
+    plan, p = _run_gpu(ms, x, 0.3, dtau, 0.1, rho, u, pp)
+    valid = valid_mask(nt, p.shape[1]) > 0
+    assert valid.any() and not np.isfinite(ref[valid]).any()
+    assert not np.isfinite(p[valid]).any()
+    assert np.all(p[~valid] == 0.0)
