@@ -226,6 +226,10 @@ int fwh_batch_tune_case(fwh_batch *batch, int32_t case_index, double item_units,
  * plan was tuned to it (fwh_plan_tune), or only it fits them all; else
  * FWH_GATHER_LDS. */
 int fwh_batch_gather(const fwh_batch *batch, int32_t *gather);
+/* Host only: name that gather instead (FWH_GATHER_LDS or FWH_GATHER_MFMA), for the
+ * next fwh_batch_bind; the rows of every case go back to 4.  FWH_EINVAL when the
+ * windows of some case do not fit it. */
+int fwh_batch_use_gather(fwh_batch *batch, int32_t gather);
 /* Build the work list and upload descriptors and list into the workspace
  * (>= workspace_bytes, 256-byte aligned) on `stream`; synchronises `stream`. */
 int fwh_batch_bind(fwh_batch *batch, void *workspace, size_t workspace_bytes, void *stream);

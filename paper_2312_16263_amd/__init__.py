@@ -30,7 +30,7 @@ ERROR_NAMES = {FWH_EINVAL: "FWH_EINVAL", FWH_EDOMAIN: "FWH_EDOMAIN", FWH_EWINDOW
 
 # names declared in include/fwh.h
 EXPORTED = ["fwh_plan_create", "fwh_plan_tune", "fwh_plan_info", "fwh_setup", "fwh_obs_window", "fwh_forward", "fwh_adjoint", "fwh_post", "fwh_profile_enable",
-            "fwh_profile_read", "fwh_batch_create", "fwh_batch_tune", "fwh_batch_tune_case", "fwh_batch_gather", "fwh_batch_bind", "fwh_batch_forward",
+            "fwh_profile_read", "fwh_batch_create", "fwh_batch_tune", "fwh_batch_tune_case", "fwh_batch_gather", "fwh_batch_use_gather", "fwh_batch_bind", "fwh_batch_forward",
             "fwh_batch_adjoint", "fwh_batch_info", "fwh_batch_destroy", "fwh_destroy", "fwh_gm_plan_create",
             "fwh_gm_window", "fwh_gm_obs_window", "fwh_gm_forward", "fwh_gm_profile_enable",
             "fwh_gm_profile_read", "fwh_gm_destroy", "fwh_forward_noalloc", "fwh_last_error",
@@ -109,6 +109,8 @@ def lib():
         L.fwh_batch_tune_case.restype = ctypes.c_int
         L.fwh_batch_gather.argtypes = [vp, ctypes.POINTER(i32)]
         L.fwh_batch_gather.restype = ctypes.c_int
+        L.fwh_batch_use_gather.argtypes = [vp, i32]
+        L.fwh_batch_use_gather.restype = ctypes.c_int
         L.fwh_batch_bind.argtypes = [vp, vp, sz, vp]
         L.fwh_batch_bind.restype = ctypes.c_int
         L.fwh_batch_forward.argtypes = [vp, vp]
@@ -322,9 +324,10 @@ class Batch:
     adjoint of every case are each a fixed sequence of batched launches (the
     gathers persistent over longest-first work lists), so `capture()` records a
     whole step (forward, dJ/dp' = 2 p', adjoint) in one HIP graph.  `inputs`
-    holds (rho, u, p) device tensors per plan, one dtype."""
+    holds (rho, u, p) device tensors per plan, one dtype.  `gather`: 'mfma' or
+    'lds' names the forward gather of every case (None: chosen)."""
 
-    def __init__(self, plans, inputs, item_units=None, blocks_per_cu=2):
+    def __init__(self, plans, inputs, item_units=None, blocks_per_cu=2, gather=None):
         import torch
         L = lib()
         self.plans = list(plans)
@@ -350,6 +353,8 @@ class Batch:
         _check(L.fwh_batch_create(arr, len(self.plans), self.in_dtype, ctypes.byref(h), ctypes.byref(nb)))
         self._h = h
         self._free = lib().fwh_batch_destroy  # kept: at interpreter exit the module globals may be gone
+        if gather is not None:
+            _check(L.fwh_batch_use_gather(h, {"mfma": GATHER_MFMA, "lds": GATHER_LDS}[gather]))
         self.workspace = torch.empty(int(nb.value), dtype=torch.uint8, device=self.plans[0].device)
         self.blocks_per_cu = blocks_per_cu
         self.tune(item_units, blocks_per_cu)
@@ -477,11 +482,11 @@ def autotune(batch: "Batch", candidates=None, bpc_candidates=None, reps=2, cache
             rows, iu = cache[key]["choice"]
             table = cache[key]["table"]
         else:
+            # on the gather of the whole batch, which the class by itself might not choose
             sub = Batch([batch.plans[i] for i in idx], [batch.inputs[i] for i in idx],
-                        blocks_per_cu=batch.blocks_per_cu)
+                        blocks_per_cu=batch.blocks_per_cu, gather=batch.gather)
             table = []
-            # a class too small for the matrix-core gather by itself runs the LDS-staged one: 4 rows only
-            for rows, iu in cands if sub.gather == "mfma" else sorted({(4, iu) for _, iu in cands}):
+            for rows, iu in cands:
                 for j in range(len(idx)):
                     sub.tune_case(j, iu, rows, bind=False)
                 sub.bind()

@@ -832,6 +832,22 @@ int fwh_batch_gather(const fwh_batch *b, int32_t *gather) {
     return FWH_OK;
 }
 
+int fwh_batch_use_gather(fwh_batch *b, int32_t gather) {
+    g_last_error.clear();
+    if (!b) return fail(FWH_EINVAL, "fwh_batch_use_gather: null batch");
+    if (gather != FWH_GATHER_LDS && gather != FWH_GATHER_MFMA)
+        return fail(FWH_EINVAL, "fwh_batch_use_gather: a batch runs FWH_GATHER_LDS or FWH_GATHER_MFMA (got %d)", (int)gather);
+    for (int c = 0; c < b->n; ++c) {
+        const fwh_plan *pl = b->cases[(size_t)c].plan;
+        if ((gather == FWH_GATHER_MFMA ? pl->mfma_bpc : pl->lds_pt) <= 0)
+            return fail(FWH_EINVAL, "fwh_batch_use_gather: the delay windows of case %d are too wide for it", c);
+    }
+    b->kind = gather;
+    b->case_rows.assign((size_t)b->n, fwh::kLdsSub);
+    b->bound = false;
+    return FWH_OK;
+}
+
 int fwh_batch_bind(fwh_batch *b, void *workspace, size_t workspace_bytes, void *stream_) {
     g_last_error.clear();
     if (!b) return fail(FWH_EINVAL, "fwh_batch_bind: null batch");
