@@ -144,8 +144,11 @@ int fwh_setup(fwh_plan *plan, void *workspace, size_t workspace_bytes, void *str
 #define FWH_GATHER_STREAM  4
 int fwh_plan_tune(fwh_plan *plan, int32_t gather, int32_t splits);
 /* The gather kernel and panel-split count fwh_setup chose (FWH_GATHER_STREAM,
- * _LDS, _MFMA or _DIRECT; FWH_GATHER_AUTO and 1 in FWH_MODE_F64).  FWH_ESTATE before
- * fwh_setup.  Either pointer may be NULL. */
+ * _LDS, _MFMA or _DIRECT; FWH_GATHER_AUTO in FWH_MODE_F64).  FWH_ESTATE before
+ * fwh_setup.  Either pointer may be NULL.  Two kinds of calls run another kernel than
+ * the one named, over the same panel ranges: those of an _MFMA plan in FWH_MODE_BF16
+ * with FP64 data run _LDS (unless the plan was tuned to _MFMA), and those of a _STREAM
+ * plan on a small surface its form for few observers. */
 int fwh_plan_info(const fwh_plan *plan, int32_t *gather, int32_t *splits);
 
 /* Observer window of a set-up plan (host values): t_start [O], n_t [O]

@@ -224,7 +224,7 @@ class Plan:
         self.window = Window(ts, nt, int(ntm.value))
 
     def info(self):
-        """(gather kernel, panel splits) chosen at setup: ('mfma' | 'lds' | 'direct' | 'f64', splits)."""
+        """(gather kernel, panel splits) chosen at setup: ('mfma' | 'lds' | 'stream' | 'direct' | 'f64', splits)."""
         g, s = ctypes.c_int32(), ctypes.c_int32()
         _check(lib().fwh_plan_info(self._h, ctypes.byref(g), ctypes.byref(s)))
         names = {GATHER_LDS: "lds", GATHER_DIRECT: "direct", GATHER_MFMA: "mfma", GATHER_STREAM: "stream"}

@@ -467,8 +467,9 @@ int fwh_setup(fwh_plan *pl, void *workspace, size_t workspace_bytes, void *strea
                         : as_lds ? fwh::gather_lds_blocks_per_cu(ctype_s, pl->lds_nw, pl->lds_pt)
                         : pl->gather_kind == FWH_GATHER_MFMA ? pl->mfma_bpc
                                                              : 2);
-    // (FP64: at least 16 panels per split, the partial signals within the source stage's scratch)
-    const int64_t smax = f64 ? std::max<int64_t>(1, std::min({(int64_t)fwh::kMaxPanelSplits, P / 16,
+    // (FP64: at least 16 panels per split, the partial signals within the source stage's scratch; the form for
+    // wide windows has no splits)
+    const int64_t smax = f64 && pl->mfma_bpc == 0 ? 1 : f64 ? std::max<int64_t>(1, std::min({(int64_t)fwh::kMaxPanelSplits, P / 16,
                                                               8 * N * P / (O * pl->n_t_max)}))
                              : split_cap(P);
     auto rounds = [&](int64_t c) { return (double)((blocks * c + resident - 1) / resident) / (double)c; };
@@ -497,7 +498,7 @@ int fwh_plan_tune(fwh_plan *pl, int32_t gather, int32_t splits) {
         gather != FWH_GATHER_MFMA && gather != FWH_GATHER_STREAM)
         return fail(FWH_EINVAL, "fwh_plan_tune: unknown gather variant %d", (int)gather);
     if (pl->mode == FWH_MODE_F64 && (gather != FWH_GATHER_AUTO || splits != 0))
-        return fail(FWH_EINVAL, "fwh_plan_tune: the plain FP64 form has one gather and no panel splits");
+        return fail(FWH_EINVAL, "fwh_plan_tune: the plain FP64 form chooses its gather and panel splits by itself");
     if (splits < 0 || splits > pl->max_splits)
         return fail(FWH_ESIZE, "fwh_plan_tune: splits must be in 0 .. %d for %lld panels (got %d)", pl->max_splits,
                     (long long)pl->P, (int)splits);
@@ -513,7 +514,7 @@ int fwh_plan_info(const fwh_plan *pl, int32_t *gather, int32_t *splits) {
     if (!pl->ready) return fail(FWH_ESTATE, "fwh_plan_info: plan is not set up");
     if (gather)
         *gather = pl->mode == FWH_MODE_F64 ? FWH_GATHER_AUTO : pl->gather_kind;
-    if (splits) *splits = pl->mode == FWH_MODE_F64 ? 1 : pl->splits;
+    if (splits) *splits = pl->splits;
     return FWH_OK;
 }
 
