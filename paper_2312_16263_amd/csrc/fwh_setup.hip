@@ -146,7 +146,9 @@ __global__ __launch_bounds__(256) void tables_f64_kernel(const double *__restric
 }
 
 // FP32/BF16 forms: block = two observer tiles (kObsTile = 2 kYTile observers) x kTabPanels panels; thread
-// (observer slot j, panel q) computes the pair's tables, the block reduces n0 over the observers
+// (observer slot j, panel q) computes the pair's tables.  Their FP64 arithmetic is what bounds it, so
+// the pairs of the slots that exist are packed into the first waves: 1 and 8 observers x 32768 panels 14 us,
+// 22 with 32 lanes to a panel whatever the number of slots.  The block reduces n0 over the observers
 // per panel: tw[t][p] = (lo, hi) = (min n0, max n0), and wblk[block] = the widest window of the
 // block's panels over the 32 observers, and over its 16-observer tiles in the high 16 bits (blocks
 // t * bpt .. t * bpt + bpt - 1 belong to 32-observer tile t, bpt = ceil(P / kTabPanels)).  The pair
@@ -162,7 +164,8 @@ __global__ __launch_bounds__(256) void tables_tile_kernel(const double *__restri
                                                           PairBf *__restrict__ rbf, int2 *__restrict__ tw,
                                                           int32_t *__restrict__ wblk) {
     const int64_t t = blockIdx.x / bpt;
-    const int j = threadIdx.x % kObsTile, q = threadIdx.x / kObsTile;
+    const int64_t nobs = O - t * kObsTile < kObsTile ? O - t * kObsTile : kObsTile;
+    const int q = (int)(threadIdx.x / (unsigned)nobs), j = (int)threadIdx.x - q * (int)nobs;
     const int64_t p0 = (blockIdx.x - t * bpt) * kTabPanels;
     const int64_t o = t * kObsTile + j, p = p0 + q;
     const int h = j / kYTile, s = j % kYTile;  // 16-observer tile 2 t + h, slot s
@@ -170,14 +173,13 @@ __global__ __launch_bounds__(256) void tables_tile_kernel(const double *__restri
     __shared__ int slo[kTabPanels], slo16[2][kTabPanels], sw16[2][kTabPanels];
     __shared__ int sw[kTabPanels];
     __shared__ uint32_t out[2][kTabPanels * kYTile * 16];
-    const int64_t nobs = O - t * kObsTile < kObsTile ? O - t * kObsTile : kObsTile;
     const int np = (int)(P - p0 < kTabPanels ? P - p0 : kTabPanels);
     const int c0 = (int)(nobs < kYTile ? nobs : kYTile), c1 = (int)nobs - c0;
     const int c = h == 0 ? c0 : c1;
-    const bool valid = o < O && p < P;
+    const bool valid = q < kTabPanels && p < P;
     PairTab pt;
     if (valid) pt = pair_tables(y, dS, x_obs, t_start, nt, N, f, o, p);
-    sn0[q][j] = valid ? pt.n0 : 0;
+    if (valid) sn0[q][j] = pt.n0;
     __syncthreads();
     if (threadIdx.x < kTabPanels) {
         const int qq = threadIdx.x;
