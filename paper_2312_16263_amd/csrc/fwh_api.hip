@@ -84,9 +84,9 @@ struct fwh_plan {
     template <typename T>
     T *at(size_t off) const { return reinterpret_cast<T *>(ws + off); }
     void *scratch() const { return off_scr == SIZE_MAX ? nullptr : ws + off_scr; }
-    // FP64 form: two words in place of the delay extremes, which fwh_setup has read: the widest tile window
-    // (setup) and the source stages' mark of values that are not finite
-    int *spoiled() const { return at<int>(off_dmm) + 1; }
+    // FP64 form: the source stages' mark of values that are not finite, in place of the delay extremes (which
+    // fwh_setup has read)
+    int *spoiled() const { return at<int>(off_dmm); }
     fwh::PairBf *rbf() const { return mode == FWH_MODE_BF16 ? at<fwh::PairBf>(off_rbf) : nullptr; }
 };
 
@@ -299,14 +299,21 @@ int fwh_setup(fwh_plan *pl, void *workspace, size_t workspace_bytes, void *strea
         (e = hipMemcpyAsync(pl->at<double>(pl->off_x), pl->x_obs.data(), O * 3 * sizeof(double), hipMemcpyHostToDevice, st)) ||
         (e = hipMemcpyAsync(pl->at<double>(pl->off_cp), pl->cp.data(), N * sizeof(double), hipMemcpyHostToDevice, st)))
         return hip_fail("fwh_setup: copy of the geometry", e);
+    const bool f64 = pl->mode == FWH_MODE_F64;
+    // FP64 form: the widest delay window over a tile of observers (the gather's LDS tile) comes back with the
+    // delay extremes, in the word after their region (the start times, written further down)
+    int *const width = f64 ? pl->at<int>(pl->off_ts) : nullptr;
     StageScope scope_a(pl, FWH_STAGE_SETUP, st);
     if ((e = fwh::launch_delay(pl->at<double>(pl->off_y), pl->at<double>(pl->off_x), P, O, pl->flow,
-                               pl->at<double>(pl->off_D), st)))
+                               pl->at<double>(pl->off_D), width, st)))
         return hip_fail("fwh_setup: delay kernel", e);
     if ((e = fwh::launch_minmax(pl->at<double>(pl->off_D), P, O, pl->at<double>(pl->off_dmm), st)))
         return hip_fail("fwh_setup: min/max kernel", e);
-    std::vector<double> dmm((size_t)(2 * O));
-    if ((e = hipMemcpyAsync(dmm.data(), pl->at<double>(pl->off_dmm), 2 * O * sizeof(double), hipMemcpyDeviceToHost, st)))
+    if (f64 && (e = fwh::launch_spread(pl->at<double>(pl->off_D), pl->at<double>(pl->off_dmm), P, O, N, pl->flow, width, st)))
+        return hip_fail("fwh_setup: window kernel", e);
+    const size_t back = f64 ? pl->off_ts - pl->off_dmm + sizeof(int) : 2 * (size_t)O * sizeof(double);
+    std::vector<double> dmm((back + sizeof(double) - 1) / sizeof(double));
+    if ((e = hipMemcpyAsync(dmm.data(), pl->at<double>(pl->off_dmm), back, hipMemcpyDeviceToHost, st)))
         return hip_fail("fwh_setup: read-back of the delay extremes", e);
     if ((e = hipStreamSynchronize(st))) return hip_fail("fwh_setup: stream synchronize", e);
     // observer window, Eqs. (t_start), (t_end) per observer with a general tau0
@@ -315,15 +322,15 @@ int fwh_setup(fwh_plan *pl, void *workspace, size_t workspace_bytes, void *strea
     pl->n_t32.assign((size_t)O, 0);
     pl->n_t_max = 0;
     for (int64_t o = 0; o < O; ++o) {
-        const double ts = pl->tau0 + dmm[2 * o];
-        const double te = pl->tau0 + (double)(N - 1) * pl->dtau + dmm[2 * o + 1];
+        double ts, te;
+        const double samples = fwh::obs_window(dmm[2 * o], dmm[2 * o + 1], pl->tau0, pl->dtau, N, ts, te);
         pl->t_start[o] = ts;
         if (!(te >= ts))
             return fail(FWH_EWINDOW,
                         "fwh_setup: observer %lld has an empty window (t_end %.17g < t_start %.17g): the record is "
                         "shorter than the delay spread over the surface",
                         (long long)o, te, ts);
-        const int64_t nt = (int64_t)std::floor((te - ts) / pl->dtau + 1e-9) + 1;
+        const int64_t nt = (int64_t)samples;
         pl->n_t[o] = nt;
         pl->n_t32[o] = (int32_t)nt;
         if (nt > pl->n_t_max) pl->n_t_max = nt;
@@ -331,24 +338,19 @@ int fwh_setup(fwh_plan *pl, void *workspace, size_t workspace_bytes, void *strea
     if ((e = hipMemcpyAsync(pl->at<double>(pl->off_ts), pl->t_start.data(), O * sizeof(double), hipMemcpyHostToDevice, st)) ||
         (e = hipMemcpyAsync(pl->at<int32_t>(pl->off_nt), pl->n_t32.data(), O * sizeof(int32_t), hipMemcpyHostToDevice, st)))
         return hip_fail("fwh_setup: copy of the window", e);
-    const bool f64 = pl->mode == FWH_MODE_F64;
     StageScope scope_b(pl, FWH_STAGE_SETUP, st);
     if ((e = fwh::launch_tables(f64 ? 0 : 1, pl->at<double>(pl->off_y), pl->at<double>(pl->off_dS),
                                 pl->at<double>(pl->off_x), pl->at<double>(pl->off_ts), pl->at<int32_t>(pl->off_nt), P,
                                 O, N, pl->flow, f64 ? pl->at<double>(pl->off_K64) : nullptr,
                                 f64 ? pl->at<double>(pl->off_W64) : nullptr, f64 ? pl->at<int32_t>(pl->off_N0) : nullptr,
+                                f64 ? pl->spoiled() : nullptr,
                                 f64 ? nullptr : pl->at<fwh::PairRec>(pl->off_rec_op), pl->rbf(),
                                 f64 ? nullptr : pl->at<int2>(pl->off_tw), f64 ? nullptr : pl->at<int32_t>(pl->off_wblk),
                                 st)))
         return hip_fail("fwh_setup: table kernel", e);
     if (f64) {
-        // widest window over a tile of observers -> the gather's LDS tile (the delay extremes have been read)
-        int *width = pl->at<int>(pl->off_dmm);
         int w = 0;
-        if ((e = hipMemsetAsync(width, 0, 2 * sizeof(int), st)) ||
-            (e = fwh::launch_spread64(pl->at<int32_t>(pl->off_N0), P, O, width, st)) ||
-            (e = hipMemcpyAsync(&w, width, sizeof(int), hipMemcpyDeviceToHost, st)) || (e = hipStreamSynchronize(st)))
-            return hip_fail("fwh_setup: read-back of the tile windows", e);
+        std::memcpy(&w, dmm.data() + (pl->off_ts - pl->off_dmm) / sizeof(double), sizeof w);
         pl->w16 = w;
         pl->mfma_bpc = fwh::gather64_blocks_per_cu(w);
     }

@@ -343,24 +343,6 @@ __device__ __forceinline__ void unroll(F &&f) {
 // W64[4 pair + j], N0[pair].
 __device__ __forceinline__ int64_t pair64(int64_t t, int64_t p, int64_t P, int c) { return t * kYTile * P + p * c; }
 
-// Widest spread of n0 over the observers of a 16-observer tile (any panel) -> *width (zeroed before).
-__global__ __launch_bounds__(256) void spread64_kernel(const int32_t *__restrict__ N0, int64_t P, int64_t O,
-                                                       int *__restrict__ width) {
-    const int64_t p = (int64_t)blockIdx.x * 256 + threadIdx.x, t = blockIdx.y;
-    const int c = rec_tile_obs(t, O);
-    int lo = INT_MAX, hi = INT_MIN;
-    if (p < P)
-        for (int s = 0; s < c; ++s) {
-            const int v = N0[pair64(t, p, P, c) + s];
-            lo = min(lo, v);
-            hi = max(hi, v);
-        }
-    int w = p < P ? hi - lo : 0;
-#pragma unroll
-    for (int m = 32; m > 0; m >>= 1) w = max(w, __shfl_xor(w, m));
-    if ((threadIdx.x & 63) == 0 && w > 0) atomicMax(width, w);
-}
-
 struct Gather64Args {
     const double *K64, *W64;
     const int32_t *N0, *nt;
@@ -729,12 +711,6 @@ int gather64_blocks_per_cu(int w16) {
         &n, reinterpret_cast<const void *>(&gather64_kernel), kY64Waves * 64,
         (size_t)kYTile * gather64_y_row(w16) * sizeof(double));
     return e == hipSuccess && n > 0 ? n : 1;
-}
-
-hipError_t launch_spread64(const int32_t *N0, int64_t P, int64_t O, int *width, hipStream_t stream) {
-    spread64_kernel<<<dim3((unsigned)((P + 255) / 256), (unsigned)((O + kYTile - 1) / kYTile)), dim3(256), 0, stream>>>(
-        N0, P, O, width);
-    return hipGetLastError();
 }
 
 hipError_t launch_source64(int in_dtype, const void *rho, const void *u, const void *pp, const double *normal, int64_t P,

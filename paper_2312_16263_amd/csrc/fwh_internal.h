@@ -3,6 +3,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <cmath>
 #include <cstddef>
 #include <cstdint>
 
@@ -57,6 +58,16 @@ __host__ __device__ __forceinline__ const uint32_t *rbf_block(const PairBf *rbf,
 struct Flow {
     double M0, ca, sa, beta2, dtau, tau0;
 };
+
+// Observer window of Eqs. (t_start), (t_end), from the largest and smallest delay over the surface: first
+// and last time, number of samples (te >= ts).  One function for host and device: the same roundings.
+__host__ __device__ inline double obs_window(double d_max, double d_min, double tau0, double dtau, int64_t N, double &ts,
+                                             double &te) {
+#pragma clang fp contract(off)
+    ts = tau0 + d_max;
+    te = tau0 + (double)(N - 1) * dtau + d_min;
+    return floor((te - ts) / dtau + 1e-9) + 1.0;
+}
 
 // Row stride (elements) of a panel's coefficient series: indices 0..N+1 hold
 // the B-spline coefficients c_{-1}..c_N, the rest are zero padding so that
@@ -205,16 +216,21 @@ struct BatchIndex {
 // ---------------------------------------------------------------- launchers
 // All launchers enqueue on `stream` and return the launch status.
 
-hipError_t launch_delay(const double *y, const double *x_obs, int64_t P, int64_t O, Flow f, double *D,
+// D [O][P]; *zeroed (if not null) = 0
+hipError_t launch_delay(const double *y, const double *x_obs, int64_t P, int64_t O, Flow f, double *D, int *zeroed,
                         hipStream_t stream);
 hipError_t launch_minmax(const double *D, int64_t P, int64_t O, double *dmm, hipStream_t stream);
+// *width (zero before) = widest spread of n0, as the tables will hold it, over a tile of kYTile observers and
+// any panel
+hipError_t launch_spread(const double *D, const double *dmm, int64_t P, int64_t O, int64_t N, Flow f, int *width,
+                         hipStream_t stream);
 // mode 0: FP64 tables (8, 4 doubles and an index per pair; layout in fwh_f64.hip); mode 1/2: the pair tables (and
-// rbf, if not null), plus per (observer tile t, panel p) the lo/hi of n0 over the tile's observers
+// rbf, if not null), and mode 0 clears *spoiled; mode 1/2 plus per (observer tile t, panel p) the lo/hi of n0 over the tile's observers
 // -> tw[t][p], and per block of tile_window_panels() panels of one tile the largest hi - lo ->
 // wblk[block] (tile_window_blocks(P, O) blocks, tile-major).
 hipError_t launch_tables(int mode, const double *y, const double *dS, const double *x_obs, const double *t_start,
                          const int32_t *nt, int64_t P, int64_t O, int64_t N, Flow f, double *K64, double *W64,
-                         int32_t *N0, PairRec *rec_op, PairBf *rbf, int2 *tw, int32_t *wblk, hipStream_t stream);
+                         int32_t *N0, int *spoiled, PairRec *rec_op, PairBf *rbf, int2 *tw, int32_t *wblk, hipStream_t stream);
 // blocks of the FP32/BF16 table kernel, which also reduces the tile windows: ceil(P / 8) per tile of
 // kObsTile observers (8 panels x 32 observers per block)
 inline int64_t tile_window_panels() { return 256 / kObsTile; }
@@ -274,8 +290,6 @@ hipError_t launch_source64(int in_dtype, const void *rho, const void *u, const v
 hipError_t launch_source_adjoint64(int in_dtype, void *cbar, const void *rho, const void *u, const double *normal,
                                    int64_t P, int64_t N, int64_t NS, Flow f, const double *cp, void *scratch, int *spoiled,
                                    void *g_rho, void *g_u, void *g_p, hipStream_t stream);
-// *width (zeroed by the caller) = widest spread of n0 over a tile of kYTile observers
-hipError_t launch_spread64(const int32_t *N0, int64_t P, int64_t O, int *width, hipStream_t stream);
 // resident blocks per CU of the tiled gather; 0: windows too wide for it (one launch over all panels)
 int gather64_blocks_per_cu(int w16);
 // splits > 1: panel ranges summed separately into partial [splits][O][nt_max] doubles, then added

@@ -34,8 +34,10 @@ __device__ __forceinline__ void pair_geometry(const double *x, const double *y, 
 }
 
 __global__ __launch_bounds__(256) void delay_kernel(const double *__restrict__ y, const double *__restrict__ x_obs,
-                                                    int64_t P, int64_t O, Flow f, double *__restrict__ D) {
+                                                    int64_t P, int64_t O, Flow f, double *__restrict__ D,
+                                                    int *__restrict__ zeroed) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i == 0 && zeroed) *zeroed = 0;
     if (i >= P * O) return;
     const int64_t o = i / P, p = i - o * P;
     double R, Rh[3], MR;
@@ -71,6 +73,54 @@ __global__ __launch_bounds__(256) void minmax_kernel(const double *__restrict__ 
     }
 }
 
+// Fractional delay index s0 >= 0 of a pair and its integer part, kept below N - nt so that the window's last
+// sample stays in the record (holds by construction)
+__device__ __forceinline__ double delay_index(double ts, double D, const Flow &f, double n_max, double &s0) {
+    s0 = (ts - D - f.tau0) / f.dtau;
+    if (!(s0 > 0.0)) s0 = 0.0;
+    const double nf = floor(s0);
+    return nf > n_max ? n_max : nf;
+}
+
+// Widest spread of n0 over the observers of a 16-observer tile (any panel) -> *width (zero before), from
+// the delays and their extremes alone, so that the host reads it with the extremes and the tables are
+// written while it goes on.  Thread = a panel, block = 256 panels of a tile: the 16 loads of a thread are in
+// flight together, and one atomic per block (they all go to one word and queue).  8192 panels x 72
+// observers 4.9 us; a pair per thread, 16 panels per block, 19.7 us.
+__global__ __launch_bounds__(256) void spread_kernel(const double *__restrict__ D, const double *__restrict__ dmm,
+                                                     int64_t P, int64_t O, int64_t N, Flow f, int64_t pblocks,
+                                                     int *__restrict__ width) {
+    __shared__ double start[kYTile], n_max[kYTile];
+    __shared__ int sw[4];
+    const int tid = threadIdx.x;
+    const int64_t t = blockIdx.x / pblocks, p = (blockIdx.x - t * pblocks) * 256 + tid;
+    const int c = rec_tile_obs(t, O);
+    const double *Dt = D + t * kYTile * P + (p < P ? p : P - 1);
+    double d[kYTile];
+#pragma unroll
+    for (int s = 0; s < kYTile; ++s) d[s] = Dt[(s < c ? s : c - 1) * P];
+    if (tid < kYTile) {
+        const int64_t o = t * kYTile + (tid < c ? tid : c - 1);
+        double ts, te;
+        n_max[tid] = (double)N - obs_window(dmm[2 * o], dmm[2 * o + 1], f.tau0, f.dtau, N, ts, te);
+        start[tid] = ts;
+    }
+    __syncthreads();
+    double lo = HUGE_VAL, hi = -HUGE_VAL, s0;
+#pragma unroll
+    for (int s = 0; s < kYTile; ++s) {
+        const double n0 = delay_index(start[s], d[s], f, n_max[s], s0);
+        lo = fmin(lo, n0);
+        hi = fmax(hi, n0);
+    }
+    int w = (int)fmin(hi - lo, (double)N);  // (beyond N: an empty window, which the host refuses)
+#pragma unroll
+    for (int m = 32; m > 0; m >>= 1) w = max(w, __shfl_xor(w, m));
+    if ((tid & 63) == 0) sw[tid >> 6] = w;
+    __syncthreads();
+    if (tid == 0) atomicMax(width, max(max(sw[0], sw[1]), max(sw[2], sw[3])));
+}
+
 // Per pair: fractional delay index s0 = (t_start - delay - tau0)/dtau of observer
 // sample k = 0 (sample k sits at s0 + k), its integer part n0 and the uniform
 // cubic B-spline taps of frac = s0 - n0 acting on coefficients c[n0-1..n0+2];
@@ -97,11 +147,8 @@ __device__ __forceinline__ PairTab pair_tables(const double *__restrict__ y, con
 #pragma clang fp contract(off)
         D = f.M0 * R;
     }
-    double s0 = (t_start[o] - D - f.tau0) / f.dtau;
-    if (!(s0 > 0.0)) s0 = 0.0;
-    double nf = floor(s0);
-    const double nmax = (double)(N - nt[o]);  // keeps n0 + N_t - 1 <= N - 1 (holds by construction)
-    if (nf > nmax) nf = nmax;
+    double s0;
+    const double nf = delay_index(t_start[o], D, f, (double)(N - nt[o]), s0);
     double t = s0 - nf;
     if (t > 1.0) t = 1.0;
     pt.n0 = (int32_t)nf;
@@ -131,8 +178,10 @@ __global__ __launch_bounds__(256) void tables_f64_kernel(const double *__restric
                                                          const double *__restrict__ t_start,
                                                          const int32_t *__restrict__ nt, int64_t P, int64_t O,
                                                          int64_t N, Flow f, double *__restrict__ K64,
-                                                         double *__restrict__ W64, int32_t *__restrict__ N0) {
+                                                         double *__restrict__ W64, int32_t *__restrict__ N0,
+                                                         int *__restrict__ spoiled) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;  // pair index: tile, panel, slot
+    if (i == 0) *spoiled = 0;
     if (i >= P * O) return;
     const int64_t t = i / (kYTile * P);
     const int c = rec_tile_obs(t, O);
@@ -262,10 +311,17 @@ __global__ __launch_bounds__(256) void tables_tile_kernel(const double *__restri
 
 }  // namespace
 
-hipError_t launch_delay(const double *y, const double *x_obs, int64_t P, int64_t O, Flow f, double *D,
+hipError_t launch_delay(const double *y, const double *x_obs, int64_t P, int64_t O, Flow f, double *D, int *zeroed,
                         hipStream_t stream) {
     const int64_t n = P * O;
-    delay_kernel<<<dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream>>>(y, x_obs, P, O, f, D);
+    delay_kernel<<<dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream>>>(y, x_obs, P, O, f, D, zeroed);
+    return hipGetLastError();
+}
+
+hipError_t launch_spread(const double *D, const double *dmm, int64_t P, int64_t O, int64_t N, Flow f, int *width,
+                         hipStream_t stream) {
+    const int64_t tiles = (O + kYTile - 1) / kYTile, pblocks = (P + 255) / 256;
+    spread_kernel<<<dim3((unsigned)(tiles * pblocks)), dim3(256), 0, stream>>>(D, dmm, P, O, N, f, pblocks, width);
     return hipGetLastError();
 }
 
@@ -276,11 +332,12 @@ hipError_t launch_minmax(const double *D, int64_t P, int64_t O, double *dmm, hip
 
 hipError_t launch_tables(int mode, const double *y, const double *dS, const double *x_obs, const double *t_start,
                          const int32_t *nt, int64_t P, int64_t O, int64_t N, Flow f, double *K64, double *W64,
-                         int32_t *N0, PairRec *rec_op, PairBf *rbf, int2 *tw, int32_t *wblk, hipStream_t stream) {
+                         int32_t *N0, int *spoiled, PairRec *rec_op, PairBf *rbf, int2 *tw, int32_t *wblk, hipStream_t stream) {
     if (mode == 0) {
         const int64_t n = P * O;
         tables_f64_kernel<<<dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream>>>(y, dS, x_obs, t_start, nt, P,
-                                                                                        O, N, f, K64, W64, N0);
+                                                                                        O, N, f, K64, W64, N0,
+                                                                                        spoiled);
     } else {
         tables_tile_kernel<<<dim3((unsigned)tile_window_blocks(P, O)), dim3(256), 0, stream>>>(
             y, dS, x_obs, t_start, nt, P, O, N, f, (P + kTabPanels - 1) / kTabPanels, rec_op, rbf, tw, wblk);
