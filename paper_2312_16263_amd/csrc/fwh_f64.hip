@@ -15,6 +15,7 @@
 // observers' taps and weights from scalar registers, four indices per lane.  Both are bound by FP64
 // issue (the 16x16x4 product takes 77 cycles).  FP64 step, 8192 panels x 72 observers x 1024 frames: gather 7.8 -> 0.67 ms,
 // transposed 1.6 -> 0.98, source stage 1.5 -> 0.79, its adjoint 1.25 -> 0.86.
+#include <algorithm>
 #include <climits>
 #include <type_traits>
 
@@ -611,10 +612,10 @@ struct AdjGather64Args {
 __global__ __launch_bounds__(256) void pad64_kernel(const double *__restrict__ gbar, const int32_t *__restrict__ nt,
                                                     int64_t O, int64_t nt_max, int64_t LR, int64_t padlo,
                                                     double *__restrict__ g) {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= O * LR) return;
-    const int64_t o = i / LR, k = i - o * LR - padlo;
-    g[i] = k >= 0 && k < nt[o] ? gbar[o * nt_max + k] : 0.0;
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < O * LR; i += (int64_t)gridDim.x * 256) {
+        const int64_t o = i / LR, k = i - o * LR - padlo;
+        g[i] = k >= 0 && k < nt[o] ? gbar[o * nt_max + k] : 0.0;
+    }
 }
 
 // A wave owns panel p and kAdjIdx indices: lane l the indices ib + 4 (l - 1) .. + 3 (lane 0 only supplies
@@ -782,7 +783,9 @@ hipError_t launch_adj_gather64(const double *K64, const double *W64, const int32
         adj_gather64_plain_kernel<<<dim3((unsigned)(ibl * P)), dim3(256), 0, stream>>>(a, nt_max, ibl);
         return hipGetLastError();
     }
-    pad64_kernel<<<dim3((unsigned)((O * LR + 255) / 256)), dim3(256), 0, stream>>>(gbar, nt, O, nt_max, LR, padlo, pad);
+    // (a launch holds fewer than 2^32 threads, a copy of 34 GB or more has as many elements)
+    const unsigned pad_blocks = (unsigned)std::min<int64_t>((O * LR + 255) / 256, (int64_t)1 << 23);
+    pad64_kernel<<<dim3(pad_blocks), dim3(256), 0, stream>>>(gbar, nt, O, nt_max, LR, padlo, pad);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const AdjGather64Args a{K64, W64, N0, nt, pad, P, O, N, NS, LR, padlo, nib, cbar};
