@@ -709,7 +709,8 @@ struct fwh_batch {
     std::vector<double> case_units;    // per case: target panel-observer-samples per forward item
     std::vector<int> case_rows;        // per case: rows of 61 samples per block (matrix-core gather)
     int64_t max_items = 0, n_items = 0, units = 0, grid = 0;
-    int64_t max_adj_items = 0, n_adj_items = 0;
+    int64_t max_adj_items = 0, n_adj_items = 0, n_adj16 = 0;  // n_adj16: of the form for short records
+    int64_t adj_waves = 0;                                    // waves of all cases in the other form
     int64_t blocks_src = 0, blocks_srcg = 0, blocks_red = 0, blocks_pad = 0, waves_adj = 0, blocks_sadj = 0,
             blocks_sadjg = 0;
     size_t shmem = 0;
@@ -735,7 +736,7 @@ int fwh_batch_create(const fwh_batch_case *cases, int32_t n, int32_t in_dtype, f
     if (!cases || !out || n < 1) return fail(FWH_EINVAL, "fwh_batch_create: need cases, out and n_cases >= 1");
     if (in_dtype != FWH_F64 && in_dtype != FWH_F32) return fail(FWH_EINVAL, "fwh_batch_create: bad in_dtype");
     int mode = -1;
-    int64_t max_items = 0, max_adj_items = 0;
+    int64_t max_items = 0, max_adj_items = 0, adj_waves = 0;
     for (int c = 0; c < n; ++c) {
         const fwh_batch_case &k = cases[c];
         if (!k.plan || !k.rho || !k.u || !k.p_prime || !k.p_out || !k.grad_p || !k.g_rho || !k.g_u || !k.g_p)
@@ -751,7 +752,8 @@ int fwh_batch_create(const fwh_batch_case *cases, int32_t n, int32_t in_dtype, f
         const int64_t tiles = ceil_div(k.plan->O, fwh::kYTile),
                       kbs = ceil_div(k.plan->n_t_max, 2 * fwh::kLdsLanesOut);
         max_items += tiles * kbs * k.plan->max_splits;
-        const int64_t nib = fwh::adj_blocks(k.plan->N);
+        adj_waves += k.plan->P * fwh::adj_blocks(k.plan->N);
+        const int64_t nib = std::max(fwh::adj_blocks(k.plan->N), fwh::adj16_blocks(k.plan->NS));
         max_adj_items += ceil_div(k.plan->P * nib, 4);
     }
     if (max_adj_items > INT32_MAX) return fail(FWH_ESIZE, "fwh_batch_create: too many adjoint work items");
@@ -764,6 +766,11 @@ int fwh_batch_create(const fwh_batch_case *cases, int32_t n, int32_t in_dtype, f
     b->mode = mode;
     b->max_items = max_items;
     b->max_adj_items = max_adj_items;
+    // the transposed gather's form for short records goes by the whole batch's waves where every case then
+    // takes it, else by the records alone: two launches of a few waves each would not fill the device
+    for (int c = 0; c < n; ++c)
+        if (!fwh::adj_takes_16(cases[c].plan->O, cases[c].plan->NS, adj_waves)) adj_waves = INT64_MAX;
+    b->adj_waves = adj_waves;
     // the matrix-core gather when it is the faster one for every case and the batch is large enough to
     // fill the device with its items, every plan asked for it (fwh_plan_tune) or only it takes the windows
     // of every case; else the LDS-staged one
@@ -869,6 +876,7 @@ int fwh_batch_bind(fwh_batch *b, void *workspace, size_t workspace_bytes, void *
     };
     std::vector<Item> items;
     struct AdjItem {
+        bool narrow;  // form for short records and small surfaces: these first
         double cost;
         int2 w;
     };
@@ -891,7 +899,8 @@ int fwh_batch_bind(fwh_batch *b, void *workspace, size_t workspace_bytes, void *
         S = std::max<int64_t>(1, std::min<int64_t>(S, pl->max_splits));
         const int64_t p_chunk = ceil_div(P, S);
         const int64_t LR = fwh::adj_pad_row(N, NS), padlo = fwh::adj_pad_lo(N);
-        const int64_t nib = fwh::adj_blocks(N);
+        const bool narrow = fwh::adj_takes_16(O, NS, b->adj_waves);
+        const int64_t nib = narrow ? fwh::adj16_blocks(NS) : fwh::adj_blocks(N);
         fwh::BatchCase &d = desc[c];
         d.src = fwh::SrcFwdArgs{k.rho, k.u, k.p_prime, pl->at<double>(pl->off_n), P, N, NS, pl->flow,
                                 pl->at<double>(pl->off_cp), pl->scratch(), pl->ws + pl->off_coef};
@@ -903,7 +912,7 @@ int fwh_batch_bind(fwh_batch *b, void *workspace, size_t workspace_bytes, void *
         d.pad = fwh::PadArgs{static_cast<const float *>(k.grad_p), pl->at<int32_t>(pl->off_nt), O, ntm, LR, padlo,
                              pl->at<float>(pl->off_gpad)};
         d.adj = fwh::AdjArgs{pl->at<fwh::PairRec>(pl->off_rec_op), pl->at<int32_t>(pl->off_nt),
-                             pl->at<float>(pl->off_gpad), P, O, N, NS, LR, padlo, nib, pl->at<float>(pl->off_coef),
+                             pl->at<float>(pl->off_gpad), P, O, N, NS, LR, padlo, nib, ntm, pl->at<float>(pl->off_coef),
                              N - nt_min(pl), nt_min(pl) + 2};
         d.sadj = fwh::SrcAdjArgs{pl->at<float>(pl->off_coef), k.rho, k.u, pl->at<double>(pl->off_n), P, N, NS,
                                  pl->flow, pl->at<double>(pl->off_cp), k.g_rho, k.g_u, k.g_p};
@@ -931,7 +940,7 @@ int fwh_batch_bind(fwh_batch *b, void *workspace, size_t workspace_bytes, void *
         const int64_t groups = ceil_div(P * nib, 4);
         for (int64_t g = 0; g < groups; ++g) {
             const int64_t waves = std::min<int64_t>(4, P * nib - 4 * g);
-            adj_items.push_back({(double)waves * O, make_int2(c, (int)g)});
+            adj_items.push_back({narrow, (double)waves * O, make_int2(c, (int)g)});
         }
         int64_t sum_nt = 0;
         for (int64_t o = 0; o < O; ++o) sum_nt += pl->n_t[o];
@@ -940,7 +949,9 @@ int fwh_batch_bind(fwh_batch *b, void *workspace, size_t workspace_bytes, void *
     // longest first (the paper's greedy partition by size), ties in case order
     std::stable_sort(items.begin(), items.end(), [](const Item &x, const Item &y) { return x.cost > y.cost; });
     std::stable_sort(adj_items.begin(), adj_items.end(),
-                     [](const AdjItem &x, const AdjItem &y) { return x.cost > y.cost; });
+                     [](const AdjItem &x, const AdjItem &y) { return x.narrow != y.narrow ? x.narrow : x.cost > y.cost; });
+    b->n_adj16 = 0;
+    for (const AdjItem &x : adj_items) b->n_adj16 += x.narrow;
     std::vector<int4> wl(items.size());
     for (size_t i = 0; i < items.size(); ++i) wl[i] = items[i].w;
     std::vector<int2> wla(adj_items.size());
@@ -1000,7 +1011,7 @@ int fwh_batch_adjoint(fwh_batch *b, void *stream_) {
     if (!b || !b->bound) return fail(FWH_ESTATE, "fwh_batch_adjoint: batch is not bound");
     hipError_t e = fwh::launch_batch_adjoint(b->in_dtype == FWH_F64 ? 0 : 1, b->at<fwh::BatchCase>(b->off_cases),
                                              batch_index(b), b->blocks_pad, b->at<int2>(b->off_adj_items),
-                                             (int)b->n_adj_items, b->blocks_sadj, b->blocks_sadjg,
+                                             (int)b->n_adj_items, (int)b->n_adj16, b->blocks_sadj, b->blocks_sadjg,
                                              as_stream(stream_));
     if (e) return hip_fail("fwh_batch_adjoint", e);
     return FWH_OK;

@@ -153,6 +153,7 @@ struct AdjArgs {
     const int32_t *nt;
     const float *gpad;
     int64_t P, O, N, NS, LR, padlo, nib;
+    int64_t nt_max;  // longest observer window
     float *cbar;
     // every observer's gradient reaches every index in [edge_lo, edge_hi] (N - shortest window, and
     // shortest window + 2): index blocks inside need no check for blocks that get only zeros
@@ -377,6 +378,20 @@ constexpr int kAdjIdx = 252;
 constexpr int kAdjPT = 64;  // panels per tile of the transposed gather's wave order
 // waves per panel: the indices 0 .. N + 1
 inline int64_t adj_blocks(int64_t N) { return (N + 2 + kAdjMW * kAdjIdx - 1) / (kAdjMW * kAdjIdx); }
+// Short records and small surfaces: waves of kAdj16MW blocks of 64 indices, four observers at a time (the same sums
+// bit for bit).  Waves per panel, and when it is the better form; `waves`: of the other one, in the
+// whole launch.  The other one spends a whole block of kAdjIdx indices on each observer in turn, so it loses on
+// records of one wave here (NS <= 320) except with few observers, and where its waves, each a chain of O
+// observers, do not fill the device.  Measured (us, this form / the other; panels x observers x frames): 51200 x 640 x
+// 50 1394 / 4170, 12800 x 160 x 240 253 / 306, 3200 x 16 x 110 25.6 / 27.8, 200 x 160 x 1000 41 / 82, 800 x 160 x 740
+// 71 / 92; on the other side of the line 3200 x 4 x 110 23.5 / 21.8, 12800 x 16 x 240 52 / 45, 800 x 16 x 1000 24.7 /
+// 20.5, 12800 x 160 x 500 493 / 412, 12800 x 640 x 740 2712 / 2472.
+constexpr int kAdj16MW = 5;
+inline int64_t adj16_blocks(int64_t NS) { return (NS + 64 * kAdj16MW - 1) / (64 * kAdj16MW); }
+inline bool adj_takes_16(int64_t O, int64_t NS, int64_t waves) {
+    return (NS <= 64 * kAdj16MW && O >= 8 * (NS / 64 - 1)) ||
+           (O >= 12 && waves <= (640 + 32 * O < 8192 ? 640 + 32 * O : 8192));
+}
 inline int64_t adj_pad_row(int64_t N, int64_t NS) { return ((N + NS + 8 + 64 * 6 + 63) / 64) * 64; }
 // nt_min, nt_max: shortest and longest observer window
 hipError_t launch_adj_gather(const PairRec *rec_op, const int32_t *nt, const float *gbar, int64_t P, int64_t O,
@@ -405,9 +420,10 @@ hipError_t launch_batch_forward(int in_dtype, int coef_type, bool mfma, const Ba
                                 const int4 *items, int n_items, int *counter, int grid, size_t shmem,
                                 int64_t blocks_src, int64_t blocks_srcg, int64_t blocks_red, hipStream_t stream);
 // adjoint: zero-padded dJ/dp' of all cases, then the transposed gather over adj_items (case, group of
-// 4 waves) in their longest-first order, one block per item, then the chunked source adjoint
+// 4 waves), one block per item, the first n_adj16 of them in the form for short records and small surfaces, each
+// part longest first, then the chunked source adjoint
 hipError_t launch_batch_adjoint(int in_dtype, const BatchCase *cases, BatchIndex idx, int64_t blocks_pad,
-                                const int2 *adj_items, int n_adj_items, int64_t blocks_sadj, int64_t blocks_sadjg,
+                                const int2 *adj_items, int n_adj_items, int n_adj16, int64_t blocks_sadj, int64_t blocks_sadjg,
                                 hipStream_t stream);
 
 // Post-processing: per-observer RMS and one-sided Welch PSD (segments of L
