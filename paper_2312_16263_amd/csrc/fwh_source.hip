@@ -672,11 +672,13 @@ __device__ __forceinline__ void src_adj_block(const SrcAdjArgs &a, int64_t pbk, 
 // Interior: (panel block, chunk) pairs, chunks fastest, renumbered per XCD: the chunks of
 // one panel block run together on one XCD, so the coefficient-adjoint rows that neighbouring chunks
 // both read (the recurrences' overlap) come from that XCD's L2 rather than from HBM twice.
-template <typename TIn>
+// INT: there are interior chunks (records without any run the boundary form alone, a smaller kernel: 8281 panels x 76
+// frames 38 us, 46 with both).
+template <typename TIn, bool INT>
 __global__ __launch_bounds__(256) void src_adj_kernel(SrcAdjArgs a, int64_t pb, int64_t ngen, int64_t nint,
                                                       int64_t gen_blocks) {
     const int64_t h = blockIdx.x;
-    if (h < gen_blocks) {
+    if (!INT || h < gen_blocks) {
         if (h < pb * ngen) src_adj_block<TIn>(a, h % pb, src_general_chunk(h / pb, nint), false);
     } else {
         const int64_t L = xcd_block(h - gen_blocks, gridDim.x - gen_blocks), pbk = L / nint;
@@ -684,12 +686,12 @@ __global__ __launch_bounds__(256) void src_adj_kernel(SrcAdjArgs a, int64_t pb, 
     }
 }
 // batched: the boundary chunks of all cases, then the interior ones
-template <typename TIn>
+template <typename TIn, bool INT>
 __global__ __launch_bounds__(256) void src_adj_batched(const BatchCase *__restrict__ cases,
                                                        const int64_t *__restrict__ start,
                                                        const int64_t *__restrict__ startg, int n, int64_t gen_blocks) {
     const int64_t g = blockIdx.x;
-    if (g < gen_blocks) {
+    if (!INT || g < gen_blocks) {
         if (g >= startg[n]) return;
         const int c = find_case(startg, n, g);
         const int64_t local = g - startg[c], N = cases[c].sadj.N;
@@ -710,7 +712,9 @@ template <typename TIn>
 hipError_t src_adj_chunk_launch_t(const SrcAdjArgs &a, hipStream_t stream) {
     const int64_t pb = (a.P + kSrcPanels - 1) / kSrcPanels;
     const int64_t nint = adj_interior_chunks(a.N), ngen = adj_chunks(a.N) - nint, gb = round_xcd(pb * ngen);
-    src_adj_kernel<TIn><<<dim3((unsigned)(gb + pb * nint)), dim3(256), 0, stream>>>(a, pb, ngen, nint, gb);
+    const dim3 grid((unsigned)(gb + pb * nint));
+    if (nint > 0) src_adj_kernel<TIn, true><<<grid, dim3(256), 0, stream>>>(a, pb, ngen, nint, gb);
+    else src_adj_kernel<TIn, false><<<grid, dim3(256), 0, stream>>>(a, pb, ngen, nint, gb);
     return hipGetLastError();
 }
 
@@ -789,8 +793,13 @@ hipError_t launch_batch_source_adjoint(int in_dtype, const BatchCase *cases, con
                                        hipStream_t stream) {
     const int64_t gb = round_xcd(blocks_gen);
     const dim3 g((unsigned)(blocks_int + gb)), b(256);
-    if (in_dtype == 0) src_adj_batched<double><<<g, b, 0, stream>>>(cases, start_int, start_gen, n, gb);
-    else src_adj_batched<float><<<g, b, 0, stream>>>(cases, start_int, start_gen, n, gb);
+    if (in_dtype == 0) {
+        if (blocks_int > 0) src_adj_batched<double, true><<<g, b, 0, stream>>>(cases, start_int, start_gen, n, gb);
+        else src_adj_batched<double, false><<<g, b, 0, stream>>>(cases, start_int, start_gen, n, gb);
+    } else {
+        if (blocks_int > 0) src_adj_batched<float, true><<<g, b, 0, stream>>>(cases, start_int, start_gen, n, gb);
+        else src_adj_batched<float, false><<<g, b, 0, stream>>>(cases, start_int, start_gen, n, gb);
+    }
     return hipGetLastError();
 }
 
