@@ -340,8 +340,8 @@ __device__ __forceinline__ void unroll(F &&f) {
 }
 
 // Pair tables of the FP64 form, in tiles of kYTile observers like the FP32 ones: pair index of (tile
-// t with c observers, panel p, slot s) = (t 16 P + p c + s); K64[(t 16 P + p c) 8 + f c + s],
-// W64[4 pair + j], N0[pair].
+// t with c observers, panel p, slot s) = (t 16 P + p c + s); K64[8 pair + f], W64[4 pair + j],
+// N0[pair].
 __device__ __forceinline__ int64_t pair64(int64_t t, int64_t p, int64_t P, int c) { return t * kYTile * P + p * c; }
 
 struct Gather64Args {
@@ -433,7 +433,7 @@ __device__ __forceinline__ void gather64_panels(const Gather64Args &a, int64_t t
         wwd = hi - lo;
     };
     const int voff = Y64Block::lane_offset(lane);
-    const double *kp = a.K64 + pair64(t, pb, P, nobs) * 8 + lq * nobs + slot;
+    const double *kp = a.K64 + (pair64(t, pb, P, nobs) + slot) * 8 + lq;
     Y64Block A, T;
     double b0 = 0.0, b1 = 0.0;
     int need = 0, soff = 0, tb = 0, lo = 0;
@@ -447,7 +447,7 @@ __device__ __forceinline__ void gather64_panels(const Gather64Args &a, int64_t t
             const_cast<unsigned char *>(reinterpret_cast<const unsigned char *>(a.coef)) + (size_t)p * 2 * (size_t)rowb,
             0, 2 * rowb, 0x00020000);
         b0 = kp[0];
-        b1 = kp[4 * nobs];
+        b1 = kp[4];
         kp += nobs * 8;
         if (wv < NSUB) A.load(rsrc, voff, soff + wv * 64 * EB, rowb);
         tb = NSUB + ((wv + (int)p) & (kY64Waves - 1));
@@ -583,15 +583,20 @@ __global__ __launch_bounds__(256) void gather64_wide_kernel(Gather64Args a, int6
     if (k < a.nt[o]) {
         const int64_t t = o / kYTile;
         const int s = (int)(o - t * kYTile), nc = rec_tile_obs(t, a.O);
+        // (uniform tables by scalar loads, the delay index a panel ahead: the chain per panel is one read of
+        // its coefficients)
+        const const_i32_t N0 = (const_i32_t)a.N0;
+        int n0 = N0[pair64(t, 0, a.P, nc) + s];
         for (int64_t p = 0; p < a.P; ++p) {
-            const int64_t b = pair64(t, p, a.P, nc);
-            const int64_t base = (int64_t)a.N0[b + s] + k;
+            const int64_t b = pair64(t, p, a.P, nc) + s;
+            const const_f64_t K = (const_f64_t)(a.K64 + b * 8), W = (const_f64_t)(a.W64 + b * 4);
+            const int64_t base = (int64_t)n0 + k;
+            n0 = N0[p + 1 < a.P ? b + nc : b];
             double v = 0.0;
             for (int jj = 0; jj < 4; ++jj) {
                 double g = 0.0;
-                for (int c = 0; c < 8; ++c)
-                    g += a.K64[b * 8 + c * nc + s] * a.coef[((p * 2 + (c >> 2)) * a.NS + base + jj) * 4 + (c & 3)];
-                v += a.W64[(b + s) * 4 + jj] * g;
+                for (int c = 0; c < 8; ++c) g += K[c] * a.coef[((p * 2 + (c >> 2)) * a.NS + base + jj) * 4 + (c & 3)];
+                v += W[jj] * g;
             }
             acc += v;
         }
@@ -657,7 +662,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void a
             h[3] = fma(w3, x.x, fma(w2, x.y, fma(w1, x.z, w0 * x.w)));
 #pragma unroll
             for (int ch = 0; ch < 8; ++ch) {
-                const double k = K[ch * c + s];
+                const double k = K[8 * s + ch];
 #pragma unroll
                 for (int e = 0; e < 4; ++e) acc[ch][e] = fma(k, h[e], acc[ch][e]);
             }
@@ -691,7 +696,7 @@ __global__ __launch_bounds__(256) void adj_gather64_plain_kernel(AdjGather64Args
             const int64_t k = kb - jj;
             if (k >= 0 && k < ntl) h += a.W64[(b + s) * 4 + jj] * a.g[o * nt_max + k];
         }
-        for (int c = 0; c < 8; ++c) acc[c] += a.K64[b * 8 + c * nc + s] * h;
+        for (int c = 0; c < 8; ++c) acc[c] += a.K64[(b + s) * 8 + c] * h;
     }
     for (int c = 0; c < 8; ++c) a.cbar[((int64_t)c * a.P + p) * a.NS + i] = acc[c];
 }

@@ -188,8 +188,7 @@ __global__ __launch_bounds__(256) void tables_f64_kernel(const double *__restric
     const int64_t e = i - t * kYTile * P, p = e / c;
     const int s = (int)(e - p * c);
     const PairTab pt = pair_tables(y, dS, x_obs, t_start, nt, N, f, t * kYTile + s, p);
-    double *K = K64 + (i - s) * 8;
-    for (int f8 = 0; f8 < 8; ++f8) K[f8 * c + s] = pt.K[f8];
+    for (int f8 = 0; f8 < 8; ++f8) K64[i * 8 + f8] = pt.K[f8];
     for (int j = 0; j < 4; ++j) W64[i * 4 + j] = pt.w[j];
     N0[i] = pt.n0;
 }
