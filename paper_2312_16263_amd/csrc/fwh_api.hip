@@ -67,6 +67,7 @@ struct fwh_plan {
     int tail_nw = 0, tail_pt = 0;  // the same for a last tile of at most 16 observers (2 x 8 wave shape; 0: none)
     int wmax = 0, w16 = 0;       // widest delay-index window over a tile of 32 / of 16 observers
     int mfma_few_bpc = 0;        // the same of its form for few blocks
+    bool tiled64 = false;        // the FP64 form's tiled gather is the one to run
     int64_t few_blocks = 0;      // blocks that fit the device at once in that form
     int mfma_bpc = 0;            // resident blocks per CU of the matrix-core gather (0: not usable)
     bool prefer_mfma = false;    // the matrix-core gather is the faster of the tiled ones
@@ -481,6 +482,10 @@ int fwh_setup(fwh_plan *pl, void *workspace, size_t workspace_bytes, void *strea
     for (int64_t c = 1; c <= smax; ++c)
         if (rounds(c) <= best * 1.03 && (c == 1 || blocks * c <= 32 * resident)) s = c;
     if (pl->forced_splits > 0) s = pl->forced_splits;
+    if (f64) {
+        pl->tiled64 = pl->mfma_bpc > 0 && fwh::gather64_tiles_better(P, O, pl->n_t_max, blocks, s, resident);
+        if (!pl->tiled64) s = 1;
+    }
     pl->splits = (int)s;
     if (!f64) {
         // one launch: a 1-D grid of at most 2^32 work-items
@@ -556,8 +561,9 @@ int fwh_forward(fwh_plan *pl, int32_t in_dtype, const void *rho, const void *u, 
         // the panel ranges' sums take the place of the source stage's scratch
         e = fwh::launch_gather64(pl->at<double>(pl->off_K64), pl->at<double>(pl->off_W64),
                                  pl->at<int32_t>(pl->off_N0), pl->at<int32_t>(pl->off_nt),
-                                 pl->at<double>(pl->off_coef), pl->P, pl->O, pl->NS, pl->n_t_max, pl->w16, pl->splits,
-                                 pl->at<double>(pl->off_scr), pl->spoiled(), static_cast<double *>(p_out), st);
+                                 pl->at<double>(pl->off_coef), pl->P, pl->O, pl->NS, pl->n_t_max, pl->tiled64, pl->w16,
+                                 pl->splits, pl->at<double>(pl->off_scr), pl->spoiled(), static_cast<double *>(p_out),
+                                 st);
     } else {
         const int kind = forward_gather(pl, in_dtype);
         {

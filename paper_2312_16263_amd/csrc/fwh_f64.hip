@@ -573,7 +573,7 @@ __global__ __launch_bounds__(256) void reduce64_kernel(const double *__restrict_
     out[e] = s;
 }
 
-// Windows too wide for the LDS tile: one thread per (observer, sample), loop over panels.
+// Windows too wide for the LDS tile, and small surfaces: one thread per (observer, sample), loop over panels.
 __global__ __launch_bounds__(256) void gather64_wide_kernel(Gather64Args a, int64_t kblocks) {
     if (blockIdx.x == 0 && threadIdx.x == 0) *a.spoiled = 0;
     const int64_t o = blockIdx.x / kblocks;
@@ -707,6 +707,19 @@ int chunk_frames(int64_t P, int64_t N) { return (P + 63) / 64 * 2 * ((N + 127) /
 
 }  // namespace
 
+// Whether the tiled gather, in `splits` panel ranges of `blocks` blocks each (`resident` fit the device at once), is
+// the faster one.  Times in us as measured: the plain form's loop takes 0.6 per panel (windows below 128
+// samples, else 0.8), or 0.6 ns per wave of 64 samples where these fill the device; a range of the
+// tiled one 1.3 per panel, and 8 to start, 4 more to add the ranges.  Forward gather, us, plain / tiled: 24
+// panels x 8 observers x 250 frames 21 / 41, 64 x 30 x 20 29 / 30, 140 x 8 x 250 104 / 35, 384 x 2000 x 20 390 /
+// 602, 384 x 2000 x 100 786 / 659.
+bool gather64_tiles_better(int64_t P, int64_t O, int64_t nt_max, int64_t blocks, int64_t splits, int64_t resident) {
+    const double waves = (double)O * (double)((nt_max + 63) / 64), fill = (double)(blocks * splits) / (double)resident;
+    const double plain = (double)P * std::max(nt_max < 128 ? 0.6 : 0.8, 6e-4 * waves);
+    const double tiled = 8.0 + (splits > 1 ? 4.0 : 0.0) + 1.3 * (double)((P + splits - 1) / splits) * std::max(1.0, fill);
+    return tiled < plain;
+}
+
 int gather64_y_row(int w16) { return ((w16 + kLdsK + kLdsHalo + 15) / 16) * 16 + 4; }
 bool gather64_tiled(int w16) { return (size_t)kYTile * gather64_y_row(w16) * sizeof(double) <= kYShmemMax; }
 
@@ -756,9 +769,8 @@ hipError_t launch_source_adjoint64(int in_dtype, void *cbar, const void *rho, co
 }
 
 hipError_t launch_gather64(const double *K64, const double *W64, const int32_t *N0, const int32_t *nt,
-                           const double *coef, int64_t P, int64_t O, int64_t NS, int64_t nt_max, int w16, int splits,
-                           double *partial, int *spoiled, double *out, hipStream_t stream) {
-    const bool tiled = gather64_tiled(w16);
+                           const double *coef, int64_t P, int64_t O, int64_t NS, int64_t nt_max, bool tiled, int w16,
+                           int splits, double *partial, int *spoiled, double *out, hipStream_t stream) {
     if (!tiled) splits = 1;
     const int64_t p_chunk = (P + splits - 1) / splits;
     const Gather64Args a{K64, W64, N0, nt, coef, P, O, NS, nt_max, p_chunk, gather64_y_row(w16), splits,

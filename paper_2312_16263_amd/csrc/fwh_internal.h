@@ -293,10 +293,11 @@ hipError_t launch_source_adjoint64(int in_dtype, void *cbar, const void *rho, co
                                    void *g_rho, void *g_u, void *g_p, hipStream_t stream);
 // resident blocks per CU of the tiled gather; 0: windows too wide for it (one launch over all panels)
 int gather64_blocks_per_cu(int w16);
-// splits > 1: panel ranges summed separately into partial [splits][O][nt_max] doubles, then added
+bool gather64_tiles_better(int64_t P, int64_t O, int64_t nt_max, int64_t blocks, int64_t splits, int64_t resident);
+// tiled: else a thread per output; splits > 1: panel ranges summed separately into partial [splits][O][nt_max] doubles, then added
 hipError_t launch_gather64(const double *K64, const double *W64, const int32_t *N0, const int32_t *nt,
-                           const double *coef, int64_t P, int64_t O, int64_t NS, int64_t nt_max, int w16, int splits,
-                           double *partial, int *spoiled, double *out, hipStream_t stream);
+                           const double *coef, int64_t P, int64_t O, int64_t NS, int64_t nt_max, bool tiled, int w16,
+                           int splits, double *partial, int *spoiled, double *out, hipStream_t stream);
 // pad (pad_bytes): room for a zero-padded copy of gbar, O x adj_pad_row(N, NS) doubles (else a slower form)
 hipError_t launch_adj_gather64(const double *K64, const double *W64, const int32_t *N0, const int32_t *nt,
                                const double *gbar, int64_t P, int64_t O, int64_t N, int64_t NS, int64_t nt_max,
