@@ -63,9 +63,10 @@ struct SrcTerm {
 };
 
 // Block = the 4 channels of one group (a wave each) for 64 panels, rows [r0, r0 + T) of the system rows
-// 1 .. N-2: reduced right-hand sides d_r -> scr[channel][r][p] (time-major).
-template <typename TIn>
-__global__ __launch_bounds__(256) void src64_sweep_kernel(SrcFwdArgs a, int T, int *spoiled) {
+// 1 .. N-2, r0 = 1 + z T: reduced right-hand sides d_r -> scr[channel][r][p] (time-major); returns the last
+// and, of the record ends that the rows reach, the channel's values there.
+template <typename TIn, int PF = 8>  // PF: rows loaded ahead
+__device__ __forceinline__ double src64_sweep(const SrcFwdArgs &a, int T, int64_t z, double &f0, double &fN1) {
     const int64_t P = a.P, N = a.N;
     const int lane = threadIdx.x & 63, ch = (int)blockIdx.y * 4 + (int)(threadIdx.x >> 6);
     const bool deriv = channel_deriv(ch);
@@ -73,13 +74,13 @@ __global__ __launch_bounds__(256) void src64_sweep_kernel(SrcFwdArgs a, int T, i
     const bool active = p < P;
     const SrcTerm<TIn> X(a, active ? p : P - 1, channel_base(ch));
     const double i2h = 1.0 / (2.0 * a.f.dtau);
-    const int64_t r0 = 1 + (int64_t)blockIdx.z * T, r1 = min<int64_t>(N - 2, r0 + T - 1);
+    const int64_t r0 = 1 + z * T, r1 = min<int64_t>(N - 2, r0 + T - 1);
     const int64_t rs = max<int64_t>(1, r0 - kF64H);
-    const double f0 = rs == 1 ? X.first(deriv, i2h) : 0.0, fN1 = r1 == N - 2 ? X.last(N, deriv, i2h) : 0.0;
+    f0 = rs == 1 ? X.first(deriv, i2h) : 0.0;
+    fN1 = r1 == N - 2 ? X.last(N, deriv, i2h) : 0.0;
     const double *__restrict__ cp = a.cp;
     double *scr = static_cast<double *>(a.scr) + (int64_t)ch * N * P + p;
     double Xm = X(rs - 1), Xc = X(rs), dprev = 0.0;
-    constexpr int PF = 8;  // rows loaded ahead
     for (int64_t rb = rs; rb <= r1; rb += PF) {
         double Xf[PF];
 #pragma unroll
@@ -99,7 +100,7 @@ __global__ __launch_bounds__(256) void src64_sweep_kernel(SrcFwdArgs a, int T, i
             }
         }
     }
-    if (!__builtin_isfinite(dprev)) *spoiled = 1;
+    return dprev;
 }
 
 // Whether the forward sweep of some chunk of T rows met a value that is not finite (scr: the channel's
@@ -110,31 +111,21 @@ __device__ __forceinline__ bool record_spoiled(const double *scr, int64_t P, int
     return bad | !__builtin_isfinite(scr[(N - 2) * P]);
 }
 
-// Back substitution of the storage indices [i0, i0 + T) (index i: coefficient c_{i-1}; past N + 1:
-// zero), coefficients out panel-major with the 4 channels of a group interleaved, through LDS.
-template <typename TIn>
-__global__ __launch_bounds__(256) void src64_back_kernel(SrcFwdArgs a, int T, const int *__restrict__ spoiled) {
-    constexpr int CH = 16, RS = CH * 4 + 1;
-    __shared__ double stage[64 * RS];
+// Back substitution of the storage indices [i0, i0 + T), i0 = z T (index i: coefficient c_{i-1}; past N + 1:
+// zero), coefficients out panel-major with the 4 channels of a group interleaved, through LDS.  f0, fN1: the
+// channel's end values, xN2: its reduced row N - 2 (where the indices reach them); x_above: 0, or NaN where the
+// panel's record is spoiled.
+constexpr int kB64CH = 16, kB64RS = kB64CH * 4 + 1;
+__device__ __forceinline__ void src64_back(const SrcFwdArgs &a, int T, int64_t z, double f0, double fN1, double xN2,
+                                           double x_above, double *stage) {
+    constexpr int CH = kB64CH, RS = kB64RS;
     const int64_t P = a.P, N = a.N, NS = a.NS;
     const int lane = threadIdx.x & 63, cc = threadIdx.x >> 6, by = blockIdx.y, ch = by * 4 + cc;
-    const bool deriv = channel_deriv(ch);
     const int64_t pbase = (int64_t)blockIdx.x * 64, p = pbase + lane, pc = p < P ? p : P - 1;
-    const int64_t i0 = (int64_t)blockIdx.z * T, i1 = min<int64_t>(NS, i0 + T);
+    const int64_t i0 = z * T, i1 = min<int64_t>(NS, i0 + T);
     const double *__restrict__ cp = a.cp;
     const double *scr = static_cast<const double *>(a.scr) + (int64_t)ch * N * P + pc;
     double *coef = static_cast<double *>(a.coef);
-    const double x_above = *spoiled && record_spoiled(scr, P, N, T) ? __builtin_nan("") : 0.0;
-    double f0 = 0.0, fN1 = 0.0, xN2 = 0.0;
-    if (i0 == 0 || i1 > N) {
-        const SrcTerm<TIn> X(a, pc, channel_base(ch));
-        const double i2h = 1.0 / (2.0 * a.f.dtau);
-        if (i0 == 0) f0 = X.first(deriv, i2h);
-        if (i1 > N) {
-            fN1 = X.last(N, deriv, i2h);
-            xN2 = scr[(N - 2) * P] + x_above;
-        }
-    }
     // x_r = d_r - cp_r x_{r+1} (x_{N-1} = 0) from kF64H rows above the chunk
     double x = x_above;
     constexpr int PF = 8;
@@ -147,10 +138,16 @@ __global__ __launch_bounds__(256) void src64_back_kernel(SrcFwdArgs a, int T, co
         for (int q = 0; q < PF; ++q)
             if (rb - q >= above) x = d[q] - cp[rb - q] * x;
     }
-    for (int64_t ib = i1 - CH; ib >= i0; ib -= CH) {
-        double d[CH];
+    double d[CH], dn[CH];  // rows of this pass and of the next
+    auto load = [&](int64_t ib, double (&v)[CH]) {
 #pragma unroll
-        for (int q = 0; q < CH; ++q) d[q] = scr[min<int64_t>(max<int64_t>(1, ib + q - 1), N - 2) * P];
+        for (int q = 0; q < CH; ++q) v[q] = scr[min<int64_t>(max<int64_t>(1, ib + q - 1), N - 2) * P];
+    };
+    if (i1 - CH <= N) load(i1 - CH, dn);
+    for (int64_t ib = i1 - CH; ib >= i0; ib -= CH) {
+#pragma unroll
+        for (int q = 0; q < CH; ++q) d[q] = dn[q];
+        if (ib > i0 && ib - CH <= N) load(ib - CH, dn);  // (indices past N + 1 have no row)
 #pragma unroll
         for (int q = CH - 1; q >= 0; --q) {
             const int64_t i = ib + q, n = i - 1;
@@ -177,6 +174,43 @@ __global__ __launch_bounds__(256) void src64_back_kernel(SrcFwdArgs a, int T, co
         }
         __syncthreads();
     }
+}
+
+template <typename TIn>
+__global__ __launch_bounds__(256) void src64_sweep_kernel(SrcFwdArgs a, int T, int *spoiled) {
+    double f0, fN1;
+    if (!__builtin_isfinite(src64_sweep<TIn>(a, T, blockIdx.z, f0, fN1))) *spoiled = 1;
+}
+template <typename TIn>
+__global__ __launch_bounds__(256) void src64_back_kernel(SrcFwdArgs a, int T, const int *__restrict__ spoiled) {
+    __shared__ double stage[64 * kB64RS];
+    const int64_t P = a.P, N = a.N, i0 = (int64_t)blockIdx.z * T, i1 = min(a.NS, i0 + T);
+    const int ch = (int)(blockIdx.y * 4 + (threadIdx.x >> 6));
+    const int64_t p = min((int64_t)blockIdx.x * 64 + (threadIdx.x & 63), P - 1);
+    const double *scr = static_cast<const double *>(a.scr) + (int64_t)ch * N * P + p;
+    const double x_above = *spoiled && record_spoiled(scr, P, N, T) ? __builtin_nan("") : 0.0;
+    double f0 = 0.0, fN1 = 0.0, xN2 = 0.0;
+    if (i0 == 0 || i1 > N) {
+        const SrcTerm<TIn> X(a, p, channel_base(ch));
+        const bool deriv = channel_deriv(ch);
+        const double i2h = 1.0 / (2.0 * a.f.dtau);
+        if (i0 == 0) f0 = X.first(deriv, i2h);
+        if (i1 > N) {
+            fN1 = X.last(N, deriv, i2h);
+            xN2 = scr[(N - 2) * P] + x_above;
+        }
+    }
+    src64_back(a, T, blockIdx.z, f0, fN1, xN2, x_above, stage);
+}
+// Records of one chunk of 64 indices: a thread reads back the scratch that it wrote itself, one launch instead of two
+// (30 panels x 35 frames 32 us, 38 in two), four rows ahead rather than eight: such a call is as long as the
+// fetch of its instructions (sixteen: 35 us).
+template <typename TIn>
+__global__ __launch_bounds__(256) void src64_short_kernel(SrcFwdArgs a, int T) {
+    __shared__ double stage[64 * kB64RS];
+    double f0, fN1;
+    const double d = src64_sweep<TIn, 4>(a, T, 0, f0, fN1);
+    src64_back(a, T, 0, f0, fN1, d, __builtin_isfinite(d) ? 0.0 : __builtin_nan(""), stage);
 }
 
 // ------------------------------------------------------------------ source adjoint
@@ -739,6 +773,11 @@ hipError_t launch_source64(int in_dtype, const void *rho, const void *u, const v
     const int T = chunk_frames(P, N);
     const unsigned pb = (unsigned)((P + 63) / 64);
     const dim3 g1(pb, 2, (unsigned)((N - 2 + T - 1) / T)), g2(pb, 2, (unsigned)((NS + T - 1) / T)), b(256);
+    if (NS <= 64) {
+        if (in_dtype == 0) src64_short_kernel<double><<<dim3(pb, 2), b, 0, stream>>>(a, T);
+        else src64_short_kernel<float><<<dim3(pb, 2), b, 0, stream>>>(a, T);
+        return hipGetLastError();
+    }
     if (in_dtype == 0) src64_sweep_kernel<double><<<g1, b, 0, stream>>>(a, T, spoiled);
     else src64_sweep_kernel<float><<<g1, b, 0, stream>>>(a, T, spoiled);
     const hipError_t e = hipGetLastError();
