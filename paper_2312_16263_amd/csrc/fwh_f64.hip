@@ -735,9 +735,14 @@ __global__ __launch_bounds__(256) void adj_gather64_plain_kernel(AdjGather64Args
     for (int c = 0; c < 8; ++c) a.cbar[((int64_t)c * a.P + p) * a.NS + i] = acc[c];
 }
 
-// frames per chunk of the recurrences: shorter chunks (more of them, more warm-up) where whole-length
+// frames per chunk of the recurrences: shorter chunks (more of them, more warm-up) where longer
 // ones would leave the chip idle (2 channel groups x P / 64 blocks of 4 waves per chunk)
-int chunk_frames(int64_t P, int64_t N) { return (P + 63) / 64 * 2 * ((N + 127) / 128) >= 1024 ? 128 : 64; }
+int chunk_frames(int64_t P, int64_t N) {
+    int T = 64;
+    for (int t = 128; t <= 1024; t *= 2)
+        if ((P + 63) / 64 * 2 * ((N + t - 1) / t) >= (t == 128 ? 1024 : 1900)) T = t;
+    return T;
+}
 
 }  // namespace
 
