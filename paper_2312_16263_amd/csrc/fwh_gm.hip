@@ -38,6 +38,7 @@
 //     cycles), LDS reads (55 %) and the address unit (45 %): 8192 panels x 1024
 //     frames x 72 observers take 9.3 ms; 12.85 ms with the B-spline weights, divides
 //     and taps of every Newton step taken anew.
+#include <algorithm>
 #include <climits>
 
 #include "fwh_internal.h"
@@ -429,7 +430,9 @@ typedef __attribute__((address_space(3))) void *gm_lds_ptr_t;
 
 // Block = 4 waves = observers 4 og .. 4 og + 3 (wave wv: observer 4 og + wv), the same 64 samples
 // k0 .. k0 + 63 and panel range; logical blocks run with the observer group fastest, regrouped per XCD.
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void gm_gather_kernel(GmGatherArgs a) {
+// WAVES: waves per SIMD the registers are held to.
+template <int WAVES>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WAVES))) void gm_gather_kernel(GmGatherArgs a) {
     __shared__ double stage[2][kGmStaged][kGmSpanB];
     __shared__ int span_lo[2][4], span_hi[2][4];
     const int lane = threadIdx.x & 63;
@@ -613,7 +616,8 @@ hipError_t launch_gm_source(const GmChanArgs &a, const double *inv_beta, hipStre
     if (e != hipSuccess) return e;
     const int64_t rows = a.P * kGmRows;
     if (a.N <= kPsMaxN) {
-        const int nr = 256 / ps_segments(a.N);
+        // as many rows as a block has threads for, fewer where that would leave most of the chip idle
+        const int nr = (int)std::max<int64_t>(1, std::min<int64_t>(256 / ps_segments(a.N), rows / 512));
         const size_t shmem = (size_t)nr * (ps_at((int)a.NS) + 1) * sizeof(double);
         gm_prefilter_rows_kernel<<<dim3((unsigned)((rows + nr - 1) / nr)), dim3(256), shmem, stream>>>(
             a.coef, rows, (int)a.N, nr, inv_beta);
@@ -631,7 +635,10 @@ hipError_t launch_gm_window(const GmWinArgs &a, hipStream_t stream) {
 
 hipError_t launch_gm_gather(const GmGatherArgs &a, double *out, hipStream_t stream) {
     const int64_t blocks = (int64_t)a.splits * a.nkb * ((a.O + 3) / 4);
-    gm_gather_kernel<<<dim3((unsigned)blocks), dim3(256), 0, stream>>>(a);
+    // launches of at most two blocks per CU are as long as a block's chain of panels, which more registers make
+    // shorter (72 panels x 8 observers x 130 frames 59 -> 48 us); the others need the waves
+    if (blocks <= 2 * 256) gm_gather_kernel<2><<<dim3((unsigned)blocks), dim3(256), 0, stream>>>(a);
+    else gm_gather_kernel<4><<<dim3((unsigned)blocks), dim3(256), 0, stream>>>(a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const int64_t n = a.O * a.nt_stride;
