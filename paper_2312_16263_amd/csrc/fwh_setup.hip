@@ -171,8 +171,8 @@ __device__ __forceinline__ PairTab pair_tables(const double *__restrict__ y, con
     return pt;
 }
 
-// plain FP64 form: the tables as FP64 arrays in tiles of kYTile observers (layout in fwh_f64.hip);
-// observer slots fastest, so that neighbouring threads write neighbouring elements
+// plain FP64 form: the tables as FP64 arrays in tiles of kYTile observers (layout in fwh_f64.hip), a pair per
+// thread, observer slots fastest; written through LDS, so that the stores of a wave are consecutive
 __global__ __launch_bounds__(256) void tables_f64_kernel(const double *__restrict__ y, const double *__restrict__ dS,
                                                          const double *__restrict__ x_obs,
                                                          const double *__restrict__ t_start,
@@ -180,17 +180,23 @@ __global__ __launch_bounds__(256) void tables_f64_kernel(const double *__restric
                                                          int64_t N, Flow f, double *__restrict__ K64,
                                                          double *__restrict__ W64, int32_t *__restrict__ N0,
                                                          int *__restrict__ spoiled) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;  // pair index: tile, panel, slot
+    __shared__ double sk[256 * 9], sw[256 * 5];
+    const int64_t i0 = (int64_t)blockIdx.x * 256, i = i0 + threadIdx.x;  // pair index: tile, panel, slot
     if (i == 0) *spoiled = 0;
-    if (i >= P * O) return;
-    const int64_t t = i / (kYTile * P);
-    const int c = rec_tile_obs(t, O);
-    const int64_t e = i - t * kYTile * P, p = e / c;
-    const int s = (int)(e - p * c);
-    const PairTab pt = pair_tables(y, dS, x_obs, t_start, nt, N, f, t * kYTile + s, p);
-    for (int f8 = 0; f8 < 8; ++f8) K64[i * 8 + f8] = pt.K[f8];
-    for (int j = 0; j < 4; ++j) W64[i * 4 + j] = pt.w[j];
-    N0[i] = pt.n0;
+    if (i < P * O) {
+        const int64_t t = i / (kYTile * P);
+        const int c = rec_tile_obs(t, O);
+        const int64_t e = i - t * kYTile * P, p = e / c;
+        const int s = (int)(e - p * c);
+        const PairTab pt = pair_tables(y, dS, x_obs, t_start, nt, N, f, t * kYTile + s, p);
+        for (int f8 = 0; f8 < 8; ++f8) sk[threadIdx.x * 9 + f8] = pt.K[f8];
+        for (int j = 0; j < 4; ++j) sw[threadIdx.x * 5 + j] = pt.w[j];
+        N0[i] = pt.n0;
+    }
+    __syncthreads();
+    const int np = (int)min<int64_t>(256, P * O - i0);
+    for (int q = threadIdx.x; q < np * 8; q += 256) K64[i0 * 8 + q] = sk[(q >> 3) * 9 + (q & 7)];
+    for (int q = threadIdx.x; q < np * 4; q += 256) W64[i0 * 4 + q] = sw[(q >> 2) * 5 + (q & 3)];
 }
 
 // FP32/BF16 forms: block = two observer tiles (kObsTile = 2 kYTile observers) x kTabPanels panels; thread
