@@ -82,7 +82,9 @@ __device__ __forceinline__ double src64_sweep(const SrcFwdArgs &a, int T, int64_
     double *scr = static_cast<double *>(a.scr) + (int64_t)ch * N * P + p;
     double Xm = X(rs - 1), Xc = X(rs), dprev = 0.0;
     for (int64_t rb = rs; rb <= r1; rb += PF) {
-        double Xf[PF];
+        double Xf[PF], pv[PF];
+#pragma unroll
+        for (int i = 0; i < PF; ++i) pv[i] = cp[min<int64_t>(rb + i, N - 2)];
 #pragma unroll
         for (int i = 0; i < PF; ++i) Xf[i] = X(min<int64_t>(rb + i + 1, N - 1));
 #pragma unroll
@@ -92,7 +94,7 @@ __device__ __forceinline__ double src64_sweep(const SrcFwdArgs &a, int T, int64_
                 double rhs = 6.0 * (deriv ? (Xf[i] - Xm) * i2h : Xc);
                 if (r == 1) rhs -= f0;
                 if (r == N - 2) rhs -= fN1;
-                const double d = (rhs - dprev) * cp[r];
+                const double d = (rhs - dprev) * pv[i];
                 if (r >= r0 && active) scr[r * P] = d;
                 dprev = d;
                 Xm = Xc;
@@ -131,12 +133,14 @@ __device__ __forceinline__ void src64_back(const SrcFwdArgs &a, int T, int64_t z
     constexpr int PF = 8;
     const int64_t above = i1 - 1;  // first row past the chunk's
     for (int64_t rb = min<int64_t>(N - 2, above + kF64H - 1); rb >= above; rb -= PF) {
-        double d[PF];
+        double d[PF], pv[PF];
+#pragma unroll
+        for (int q = 0; q < PF; ++q) pv[q] = cp[max<int64_t>(1, rb - q)];
 #pragma unroll
         for (int q = 0; q < PF; ++q) d[q] = scr[max<int64_t>(1, rb - q) * P];
 #pragma unroll
         for (int q = 0; q < PF; ++q)
-            if (rb - q >= above) x = d[q] - cp[rb - q] * x;
+            if (rb - q >= above) x = d[q] - pv[q] * x;
     }
     double d[CH], dn[CH];  // rows of this pass and of the next
     auto load = [&](int64_t ib, double (&v)[CH]) {
@@ -148,15 +152,18 @@ __device__ __forceinline__ void src64_back(const SrcFwdArgs &a, int T, int64_t z
 #pragma unroll
         for (int q = 0; q < CH; ++q) d[q] = dn[q];
         if (ib > i0 && ib - CH <= N) load(ib - CH, dn);  // (indices past N + 1 have no row)
+        double pv[CH];
+#pragma unroll
+        for (int q = 0; q < CH; ++q) pv[q] = cp[min<int64_t>(max<int64_t>(1, ib + q - 1), N - 2)];
 #pragma unroll
         for (int q = CH - 1; q >= 0; --q) {
-            const int64_t i = ib + q, n = i - 1;
+            const int64_t i = ib + q;
             double v;
             if (i >= N + 2) v = 0.0;
             else if (i == N + 1) v = 2.0 * fN1 - xN2;
             else if (i == N) v = fN1;
             else if (i >= 2) {
-                x = d[q] - cp[n] * x;
+                x = d[q] - pv[q] * x;
                 v = x;
             } else if (i == 1) v = f0;
             else v = 2.0 * f0 - x;
@@ -203,8 +210,8 @@ __global__ __launch_bounds__(256) void src64_back_kernel(SrcFwdArgs a, int T, co
     src64_back(a, T, blockIdx.z, f0, fN1, xN2, x_above, stage);
 }
 // Records of one chunk of 64 indices: a thread reads back the scratch that it wrote itself, one launch instead of two
-// (30 panels x 35 frames 32 us, 38 in two), four rows ahead rather than eight: such a call is as long as the
-// fetch of its instructions (sixteen: 35 us).
+// (30 panels x 35 frames 38 -> 32 us), four rows ahead rather than eight: such a call is as long as the
+// fetch of its instructions (sixteen: 35 us).  With the pivots read ahead, out of the chain: 28 us.
 template <typename TIn>
 __global__ __launch_bounds__(256) void src64_short_kernel(SrcFwdArgs a, int T) {
     __shared__ double stage[64 * kB64RS];
