@@ -45,12 +45,19 @@
  *
  * Streams.  `stream` is a hipStream_t (0 = legacy default stream); all work is
  * enqueued on it.  fwh_setup synchronises `stream`: it reads two doubles per
- * observer back to size the observer window and, in the FP32/BF16 modes, the
- * per-tile window widths to size the gather's LDS staging.  fwh_forward and
+ * observer back to size the observer window, and the widths of the delay windows
+ * of the observer tiles to size the gather's LDS staging.  fwh_forward and
  * fwh_adjoint do not synchronise.  Forward and adjoint calls on one plan share
  * workspace regions (coefficients and scratch), so the caller must order all
  * calls on one plan (one stream, or events between streams); plans with
  * different workspaces are independent.
+ *
+ * Values that are not finite.  A NaN or infinity in the surface data is no error;
+ * it reaches the results.  In FWH_MODE_F64 and in the general-motion form it spoils
+ * its panel's whole record (the spline is fitted over all frames), and so every
+ * signal; in FWH_MODE_F32 and FWH_MODE_BF16, whose splines are fitted in chunks of
+ * 64 frames, the chunks that it lies in or within 20 frames of, and the samples
+ * that these reach.
  *
  * Errors.  Every call returns FWH_OK (0) or a negative code; fwh_last_error()
  * returns a message for the calling thread's most recent failure.  Nothing is
@@ -118,8 +125,8 @@ int fwh_setup(fwh_plan *plan, void *workspace, size_t workspace_bytes, void *str
 
 /* Launch choices of the FP32/BF16 forward gather, for tests and measurements
  * (the defaults pick by themselves).  gather: FWH_GATHER_AUTO (the first of
- * STREAM, MFMA, LDS, DIRECT that applies; MFMA up to a spread of 450 samples over
- * 16 observers; in FWH_MODE_BF16 calls with FP64 data run LDS in its place; up to
+ * STREAM, MFMA, LDS, DIRECT that applies; MFMA where LDS applies too, up to a
+ * spread of 450 samples over 16 observers; in FWH_MODE_BF16 calls with FP64 data run LDS in its place; up to
  * 8 observers on a small surface run a form of STREAM with the same sums),
  * FWH_GATHER_STREAM (whole coefficient
  * rows of each panel staged once, two waves per observer: at most 8 observers

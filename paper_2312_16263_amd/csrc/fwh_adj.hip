@@ -1,9 +1,10 @@
 // Transposed gather of the adjoint (gfx950, FP32/BF16 forms): the coefficient adjoints
 //   cbar_c(p, i) = sum_o K_c(o, p) sum_j w_j(o, p) gbar(o, i - n0(o, p) - j),
 // a contraction over observers for every (panel, index): it runs on the matrix cores.  Bound by
-// matrix and vector issue (80 % of the slots) and by the data return of 16-byte loads at dword
-// alignment (84 % busy).  32768 panels x 360 observers x 2048 frames: 8.25 ms against 10.1 as 16x16x4
-// products; 240000 panels x 72 observers x 4096 frames: 24.8 against 31.4.
+// matrix and vector issue (76 % of the slots) and by the data return of 16-byte loads at dword
+// alignment (82 % busy).  Two forms, the same sums bit for bit: products of one observer each (4x4x1), and of
+// four (16x16x4) for short records and small surfaces.  32768 panels x 360 observers x 2048 frames: 8.25 ms
+// against 10.1 in the second form; 240000 panels x 72 observers x 4096 frames: 24.8 against 31.4.
 #include <type_traits>
 
 #include "fwh_internal.h"

@@ -98,11 +98,12 @@ bool finite3(const double *v) { return std::isfinite(v[0]) && std::isfinite(v[1]
 // Largest number of panel splits of the FP32/BF16 gathers (single-case and batched): at most
 // kMaxPanelSplits and at least kMinSplitPanels panels per split.  The partial-signal region is sized for it.
 constexpr int64_t kMinSplitPanels = 128;
-// asked for by name (fwh_plan_tune), the matrix-core gather takes 32-observer tiles up to this spread of
-// the delay index
+// Asked for by name (fwh_plan_tune), the matrix-core gather takes plans up to this spread of the delay index
+// over 32 observers: an interface's limit, not the kernel's, whose tiles of 16 observers hold up to 889.
 constexpr int kMfmaWmax = 265;
-// Spread over a 16-observer tile up to which FWH_GATHER_AUTO takes it instead of the LDS-staged gather
-// (each panel's product covers 247 + spread indices).
+// Spread over a 16-observer tile up to which FWH_GATHER_AUTO takes it instead of the LDS-staged gather, where that
+// one's window fits (each panel's product covers 247 + spread indices, so it loses with the spread; the
+// crossover itself is not measured).
 constexpr int kMfmaBest = 450;
 // Panel-observer-samples of a batch from which it does so in batched calls: a panel of the matrix-core
 // gather is one chain of product, LDS and taps, about 1.2 us long, which few items per CU do not cover.
@@ -125,9 +126,10 @@ int64_t nt_min(const fwh_plan *pl) {
 bool mfma_takes(const fwh_plan *pl) { return pl->mfma_bpc > 0 && pl->wmax <= kMfmaWmax; }
 
 // Forward gather of a call.  The matrix-core and the LDS-staged one give the same sums bit for bit in
-// FP32 storage (same splits, same order of the same FMAs).  In BF16 storage they round differently
-// (2e-7 of the signal): a caller with FP64 data gets FP64 gradients, which stay exactly those of the
-// LDS-staged sums; with FP32 data, where that is below the gradients' own rounding, the faster one runs.
+// FP32 storage (same splits, same order of the same FMAs).  In BF16 storage they differ by 2e-7 of the signal
+// (the storage itself is off by 1e-3): with FP64 data, whose gradients are FP64, calls keep the LDS-staged
+// sums; with FP32 data the faster one runs.  The price, 32768 panels x 360 observers x 2048 frames with FP64
+// data: 11.0 ms a forward call, of which the gather is 10.3; matrix-core 5.3.
 int forward_gather(const fwh_plan *pl, int in_dtype) {
     if (pl->gather_kind == FWH_GATHER_MFMA && pl->gather_variant == FWH_GATHER_AUTO && pl->mode == FWH_MODE_BF16 &&
         in_dtype == FWH_F64 && pl->lds_pt > 0)
@@ -138,8 +140,8 @@ int forward_gather(const fwh_plan *pl, int in_dtype) {
 // Whether a streaming-gather plan runs the few-observer form instead (the same sums): while its time, 3.6 ps
 // per panel-observer-sample (its coefficient loads from L2), stays below the streaming form's chain of
 // 128 panels per split, about 100 us and at least 0.12 us per sample of the window.  Measured (us, streaming
-// / few, FP32, 8 observers): 2048 panels x 512 frames 112 / 28, 2048 x 1900 252 / 98, 8192 x 512
-// 111 / 104, 8192 x 1024 159 / 201, 16384 x 512 127 / 194.
+// / few, FP32, 8 observers): 2048 panels x 512 frames 112 / 28, 2048 x 1900 252 / 98, 8192 x 1024 159 / 201,
+// 16384 x 512 127 / 194; 8192 x 512, 111 / 104, is near the crossing and on the streaming side of the line.
 bool few_observers(const fwh_plan *pl) {
     return pl->P * pl->O * pl->n_t_max < std::max<int64_t>(24000000, 30000 * pl->n_t_max);
 }
@@ -176,8 +178,8 @@ int layout(fwh_plan *pl) {
     const size_t real_sz = pl->mode == FWH_MODE_F64 ? sizeof(double) : sizeof(float);
     pl->off_coef = take(8 * P * NS * real_sz);
     pl->off_D = O * P * sizeof(double) <= 8 * P * NS * real_sz ? pl->off_coef : take(O * P * sizeof(double));
-    // time-major scratch of the sequential FP64 source stage, forward and adjoint
-    // (the chunked FP32/BF16 stages need none)
+    // FP64 form: time-major scratch of the source stage and its adjoint (the FP32/BF16 stages need none); between
+    // them, the panel ranges' sums of the forward gather, and the padded gradient of the transposed one
     if (pl->mode == FWH_MODE_F64) pl->off_scr = take(8 * N * P * real_sz);
     if (pl->mode != FWH_MODE_F64) {
         // FP32 partial signals of the panel splits, [max_splits][O][n_t_max <= N]
@@ -411,8 +413,8 @@ int fwh_setup(fwh_plan *pl, void *workspace, size_t workspace_bytes, void *strea
         pl->mfma_few_bpc = fwh::gather_mfma_blocks_per_cu(ctype, w16, true);
         pl->prefer_mfma = pl->mfma_bpc > 0 && pl->lds_pt > 0 && w16 <= kMfmaBest;
         pl->stream_bpc = O <= fwh::kLdsWaves ? fwh::gather_stream_blocks_per_cu(ctype, pl->NS, pl->n_t_max) : 0;
-        // kernel: the streaming gather for a few observers, else the LDS-staged one when a panel's
-        // window over a tile fits its staging, else the matrix-core one, else direct loads
+        // kernel: the streaming gather for a few observers, else, when a panel's window over a tile fits the
+        // LDS staging, the matrix-core one up to kMfmaBest and the LDS-staged one beyond, else direct loads
         switch (pl->gather_variant) {
             case FWH_GATHER_STREAM:
                 if (pl->stream_bpc <= 0)
@@ -441,8 +443,8 @@ int fwh_setup(fwh_plan *pl, void *workspace, size_t workspace_bytes, void *strea
         }
     }
     // panel splits of the tuned gathers.  A split's block takes P/s panels, so a launch of B*s blocks
-    // on R resident blocks (the LDS gather's occupancy at its staging size times the CU count; 2 per
-    // CU for the direct-load gather) lasts about ceil(B*s/R)/s block-times of the unsplit work.  Among
+    // on R resident blocks (the kernel's occupancy, for the LDS gather at its staging size, times the CU
+    // count; 2 per CU for the direct-load gather) lasts about ceil(B*s/R)/s block-times of the unsplit work.  Among
     // the s (at most kMaxPanelSplits, at least 128 panels per split) within 3 % of its minimum, take
     // the largest that keeps B*s within 32 rounds: whole rounds (no last round that leaves most CUs
     // idle), and enough of them that blocks of unequal work even out
@@ -470,8 +472,8 @@ int fwh_setup(fwh_plan *pl, void *workspace, size_t workspace_bytes, void *strea
                         : as_lds ? fwh::gather_lds_blocks_per_cu(ctype_s, pl->lds_nw, pl->lds_pt)
                         : pl->gather_kind == FWH_GATHER_MFMA ? pl->mfma_bpc
                                                              : 2);
-    // (FP64: at least 16 panels per split, the partial signals within the source stage's scratch; the form for
-    // wide windows has no splits)
+    // (FP64: at least 16 panels per split, the partial signals within the source stage's scratch; the
+    // thread-per-output form has no splits)
     const int64_t smax = f64 && pl->mfma_bpc == 0 ? 1 : f64 ? std::max<int64_t>(1, std::min({(int64_t)fwh::kMaxPanelSplits, P / 16,
                                                               8 * N * P / (O * pl->n_t_max)}))
                              : split_cap(P);

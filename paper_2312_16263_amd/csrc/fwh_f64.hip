@@ -11,10 +11,12 @@
 // of every chunk.  The last launch of the call clears it again.
 //
 // Gathers: the forward one as in fwh_gather_mfma.hip (channel combine by v_mfma_f64_16x16x4f64 for a
-// tile of 16 observers, taps on the vector ALU after a pass through LDS); the transposed one with the
-// observers' taps and weights from scalar registers, four indices per lane.  Both are bound by FP64
-// issue (the 16x16x4 product takes 77 cycles).  FP64 step, 8192 panels x 72 observers x 1024 frames: gather 7.8 -> 0.67 ms,
-// transposed 1.6 -> 0.98, source stage 1.5 -> 0.79, its adjoint 1.25 -> 0.86.
+// tile of 16 observers, taps on the vector ALU after a pass through LDS), or a thread per output for small
+// surfaces; the transposed one with the observers' taps and weights from scalar registers, four indices
+// per lane, no matrix product.  FP64 step, 8192 panels x 72 observers x 1024 frames: gather 7.8 -> 0.68 ms (data
+// return 80 % busy, issue 47 %, half of it the products), transposed 1.6 -> 0.55 (FP64 issue 63 %, data return 71 %),
+// source stage 1.5 -> 0.74 and its adjoint 1.25 -> 0.86 (data return 90 % busy; 2.7 and 3.6 GB of HBM traffic,
+// most of it through the time-major scratch).
 #include <algorithm>
 #include <climits>
 #include <type_traits>

@@ -35,8 +35,8 @@
 //     its own taps when the span is too wide), and adds the integrand of
 //     Eqs. (pT) + (pL) times dS/(4 pi) in FP64.  Panel ranges (splits) are
 //     summed by gm_reduce_kernel in fixed order.  Bound by FP64 issue (65 % of the
-//     cycles), LDS reads (55 %) and the address unit (45 %): 8192 panels x 1024
-//     frames x 72 observers take 9.3 ms; 12.85 ms with the B-spline weights, divides
+//     cycles), the data-return path (65 %), LDS reads (55 %) and the address
+//     unit (45 %): 8192 panels x 1024 frames x 72 observers take 9.5 ms; 12.85 ms with the B-spline weights, divides
 //     and taps of every Newton step taken anew.
 #include <algorithm>
 #include <climits>
@@ -362,8 +362,8 @@ __device__ __forceinline__ void bspline_w(double u, double w[4]) {
 // Interval j in [0, N-2] of the source time s, in frames and within [0, N-1]
 __device__ __forceinline__ int gm_interval(double s, int last) { return min((int)s, last); }
 
-// sqrt(x) to the last bit or so, and y = 1/sqrt(x) to about 2^-45: the hardware estimate (2^-24 or better),
-// one coupled step for both, one residual step for the root.
+// sqrt(x) to the last bit or so, and y = 1/sqrt(x) to about 2^-45: Goldschmidt's coupled iteration from the
+// hardware estimate (2^-24 or better), one step for both, then one residual step for the root.
 __device__ __forceinline__ double gm_sqrt(double x, double &y) {
     const double e0 = __builtin_amdgcn_rsq(x);
     double g = x * e0, h = 0.5 * e0;

@@ -13,11 +13,11 @@ constexpr int kChannels = 8;  // [Qdot, Q, Ldot_1, Ldot_2, Ldot_3, L_1, L_2, L_3
 
 // Pair tables of the FP32/BF16 forms: per (observer, panel) pair 16 dwords -- the integrand weights of
 // the 8 source channels (dS/(4 pi) included), the four cubic B-spline taps of the fixed fractional
-// delay, the integer part n0 of the delay index, n0w, d16 and w16 (below).  Observers go in tiles of
+// delay, n0w, the integer part n0 of the delay index, d16 and w16 (below).  Observers go in tiles of
 // kYTile; the pairs of tile t (c observers, c < kYTile only in a last tile) with panel p form one block
 // of 16 c consecutive dwords, in it, for observer slot s, at dword
-//   8 s + 2 q + e: K_{q + 4 e} (q = 0 .. 3, e = 0, 1); 8 c + 4 s + j: tap w_j; 12 c + s: n0;
-//   13 c + s: n0w; 14 c + s: d16; 15 c + s: w16
+//   8 s + 2 q + e: K_{q + 4 e} (q = 0 .. 3, e = 0, 1); 8 c + 4 s + j: tap w_j; 12 c + s: n0w;
+//   13 c + s: n0; 14 c + s: d16; 15 c + s: w16
 // so that the 16 observers' values lie together: the matrix-core kernels take an operand with one load
 // over a few cache lines (of [O][P] records of 64 bytes each lane touched a line of its own, and the
 // texture addresser was the limit), and the LDS-staged gather copies a panel's block as it is.
@@ -291,10 +291,11 @@ hipError_t launch_source64(int in_dtype, const void *rho, const void *u, const v
 hipError_t launch_source_adjoint64(int in_dtype, void *cbar, const void *rho, const void *u, const double *normal,
                                    int64_t P, int64_t N, int64_t NS, Flow f, const double *cp, void *scratch, int *spoiled,
                                    void *g_rho, void *g_u, void *g_p, hipStream_t stream);
-// resident blocks per CU of the tiled gather; 0: windows too wide for it (one launch over all panels)
+// resident blocks per CU of the tiled gather; 0: windows too wide for it (the thread-per-output form over all panels)
 int gather64_blocks_per_cu(int w16);
 bool gather64_tiles_better(int64_t P, int64_t O, int64_t nt_max, int64_t blocks, int64_t splits, int64_t resident);
-// tiled: else a thread per output; splits > 1: panel ranges summed separately into partial [splits][O][nt_max] doubles, then added
+// not tiled: a thread per output, one range; splits > 1: panel ranges summed separately into partial
+// [splits][O][nt_max] doubles, then added
 hipError_t launch_gather64(const double *K64, const double *W64, const int32_t *N0, const int32_t *nt,
                            const double *coef, int64_t P, int64_t O, int64_t NS, int64_t nt_max, bool tiled, int w16,
                            int splits, double *partial, int *spoiled, double *out, hipStream_t stream);
@@ -368,12 +369,12 @@ hipError_t launch_gather_few(int coef_type, const PairRec *rec, const PairBf *rb
 // out[i] = sum over splits of partial[z][i], in FP64 and fixed order, rounded to float.
 hipError_t launch_reduce_splits(const float *partial, int splits, int64_t total, float *out, hipStream_t stream);
 
-// Transposed gather via a zero-padded copy of gbar (gpad: [O][adj_pad_row(N, NS)] floats).
+// Transposed gather via a zero-padded copy of gbar (gpad: [O][adj_pad_row(N, NS)] floats), sample 0 at padlo: either
+// form reads a row from -n0 - 4 past padlo, n0 < N.
 inline int64_t adj_pad_lo(int64_t N) { return N + 4; }
 // A wave of the transposed gather owns kAdjMW blocks of kAdjIdx coefficient indices (lane l: indices
-// 4 l - 4 .. 4 l - 1 of a block; lane 0 only supplies the values below lane 1's); a gpad row covers every
-// position it reads: from -n0 - 4 to N + 253 - n0 past padlo, n0 < N (a wave's second block is read only
-// if it starts below N + 2).
+// 4 l - 4 .. 4 l - 1 of a block; lane 0 only supplies the values below lane 1's) and reads up to N + 253 - n0
+// past padlo (its second block only if it starts below N + 2).
 constexpr int kAdjMW = 2;
 constexpr int kAdjIdx = 252;
 constexpr int kAdjPT = 64;  // panels per tile of the transposed gather's wave order
@@ -387,7 +388,7 @@ inline int64_t adj_blocks(int64_t N) { return (N + 2 + kAdjMW * kAdjIdx - 1) / (
 // 50 1394 / 4170, 12800 x 160 x 240 253 / 306, 3200 x 16 x 110 25.6 / 27.8, 200 x 160 x 1000 41 / 82, 800 x 160 x 740
 // 71 / 92; on the other side of the line 3200 x 4 x 110 23.5 / 21.8, 12800 x 16 x 240 52 / 45, 800 x 16 x 1000 24.7 /
 // 20.5, 12800 x 160 x 500 493 / 412, 12800 x 640 x 740 2712 / 2472.
-constexpr int kAdj16MW = 5;
+constexpr int kAdj16MW = 5;  // a wave reads whole blocks of 64, below NS + 64 - n0 past padlo
 inline int64_t adj16_blocks(int64_t NS) { return (NS + 64 * kAdj16MW - 1) / (64 * kAdj16MW); }
 inline bool adj_takes_16(int64_t O, int64_t NS, int64_t waves) {
     return (NS <= 64 * kAdj16MW && O >= 8 * (NS / 64 - 1)) ||

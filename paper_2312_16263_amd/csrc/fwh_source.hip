@@ -126,10 +126,10 @@ __device__ __forceinline__ void src_flush(const float *tile, TOut *coef, int64_t
 // copies into three buffers: groups m + 1 and m + 2 are in flight while group m
 // is used, one barrier per group.  The four waves (four base quantities) read
 // their inputs from LDS (both half-waves read the same panel's row: a broadcast).
-// Bound by vector issue (about 60 % of the cycles) and memory latency behind it
-// (three blocks of 150 registers per CU): 18252 panels x 6535 frames, FP32 data,
-// 1.61 ms (6.3 GB, 3.9 TB/s), 1.77 ms with one group in flight and per-lane copy
-// addresses; 32768 x 2048, FP64 data, 1.23 ms (4.9 GB) against 1.44.
+// Bound by the data-return path (90 % busy: 4 bytes a lane), in FP32 data also by vector
+// issue (60 % of the cycles; 38 % in FP64), with three blocks of 150 registers per CU: 18252
+// panels x 6535 frames, FP32 data, 1.61 ms (6.3 GB, 3.9 TB/s), 1.77 ms with one group in flight and
+// per-lane copy addresses; 32768 x 2048, FP64 data, 1.22 ms (4.9 GB) against 1.44.
 //
 // GEN = false: interior chunk (every row in [kSrcPivotRows, N - 3]): central
 // differences, constant pivot, no end rows, no branches.  GEN = true: a chunk
@@ -158,7 +158,8 @@ typedef __attribute__((address_space(3))) void *src_lds_ptr_t;
 // pbase + 31.  A piece of 64 dwords (4 bytes per lane) is one (variable, row) in
 // FP64 and two rows of a variable in FP32; the lane's panel (clamped to P - 1),
 // dword half and row within the piece are fixed.  Wave wv issues the pieces wv,
-// wv + 4, ...; pieces whose first row lies past the staged rows are skipped.
+// wv + 4, ...; one whose first row lies past the staged rows takes the last of them instead, since the waits
+// count the pieces issued.
 template <typename TIn>
 struct SrcDma {
     static constexpr int DW = (int)sizeof(TIn) / 4;  // dwords per value
